@@ -7,6 +7,7 @@
 // pencil, and writes the tile back.  Loads can fuse the spectral product
 // (delta_hat * kernel_hat) or read a real field; stores can fuse a spectral
 // multiply-accumulate.  The radix stages are in fft_core.h.
+#include <algorithm>
 #include <utility>
 
 #include "fft_core.h"
@@ -750,10 +751,17 @@ __global__ __launch_bounds__(P * (N / R0), 4) void mid_rs_kernel(FftPass a, int 
     }
 }
 
+// Tiles per workgroup of a persistent pass: `tiles`, fewer where the launch would have under 2048
+// workgroups (64^3, 6 arrays: 4 and 16 tiles per workgroup took 19 and 55 us against 12 for one).
+int fit_tiles(int64_t ntile, int batch, int tiles) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(tiles, ntile * batch / 2048));
+}
+
 template <int R1, int R2, int P>
 hipError_t launch_mid_reg(const FftPass &a, hipStream_t s, int tiles) {
     constexpr int N = R1 * R2;
     const int64_t ntile = (a.ng / N + P - 1) / P;
+    tiles = fit_tiles(ntile, a.batch, tiles);
     dim3 grid((unsigned)((ntile + tiles - 1) / tiles), (unsigned)a.batch);
     if (a.sign < 0) hipLaunchKernelGGL((mid_reg_kernel<R1, R2, P, -1>), grid, dim3(P * R2), 0, s, a, tiles);
     else hipLaunchKernelGGL((mid_reg_kernel<R1, R2, P, 1>), grid, dim3(P * R2), 0, s, a, tiles);
@@ -764,6 +772,7 @@ template <int N, int TPP, int NT, int... RAD>
 hipError_t launch_pf(const FftPass &a, hipStream_t s, int tiles) {
     constexpr int P = NT / TPP;
     const int64_t ntile = (a.ng / N + P - 1) / P;
+    tiles = fit_tiles(ntile, a.batch, tiles);
     dim3 grid((unsigned)((ntile + tiles - 1) / tiles), (unsigned)a.batch);
     if (a.sign < 0)
         hipLaunchKernelGGL((fft_pass_pf_kernel<N, TPP, NT, -1, RAD...>), grid, dim3(NT), 0, s, a, tiles);
@@ -801,7 +810,7 @@ hipError_t launch_fft_pass(const FftPass &a, hipStream_t s) {
     if (v >= 6 && a.load == LOAD_C && a.store == STORE_C && a.stride > 1 && a.stride % 16 == 0 && off32) {
         const bool x64 = v >= 8 && a.stride % 64 == 0;
         const bool wide = v != 7 && a.stride % 32 == 0;
-        const int tiles = v == 7 ? 16 : (v == 9 ? 4 : 8);
+        int tiles = v == 7 ? 16 : (v == 9 ? 4 : 8);
         if (a.n == 256)
             return x64 ? launch_mid_reg<16, 16, 64>(a, s, tiles)
                        : wide ? launch_mid_reg<16, 16, 32>(a, s, tiles) : launch_mid_reg<16, 16, 16>(a, s, tiles);
@@ -814,6 +823,7 @@ hipError_t launch_fft_pass(const FftPass &a, hipStream_t s) {
         if (a.n == 512) {
             constexpr int P = 16;
             const int64_t ntile = (a.ng / 512 + P - 1) / P;
+            tiles = fit_tiles(ntile, a.batch, tiles);
             dim3 grid((unsigned)((ntile + tiles - 1) / tiles), (unsigned)a.batch);
             // variant 7 keeps the next tile's loads in flight
             if (v == 6) {
@@ -834,6 +844,7 @@ hipError_t launch_fft_pass(const FftPass &a, hipStream_t s) {
                 constexpr int P = decltype(p_c)::value;
                 constexpr bool PF = decltype(pf_c)::value;
                 const int64_t ntile = (a.ng / a.n + P - 1) / P;
+                tiles = fit_tiles(ntile, a.batch, tiles);
                 dim3 grid((unsigned)((ntile + tiles - 1) / tiles), (unsigned)a.batch);
                 auto l3 = [&](auto kern, int t) { hipLaunchKernelGGL(kern, grid, dim3(P * t), 0, s, a, tiles); };
                 if (a.n == 96) {
@@ -868,6 +879,7 @@ hipError_t launch_fft_pass(const FftPass &a, hipStream_t s) {
             auto go = [&](auto p_c) {
                 constexpr int P = decltype(p_c)::value;
                 const int64_t ntile = (a.ng / 1024 + P - 1) / P;
+                tiles = fit_tiles(ntile, a.batch, tiles);
                 dim3 grid((unsigned)((ntile + tiles - 1) / tiles), (unsigned)a.batch);
                 if (a.sign < 0) hipLaunchKernelGGL((mid_rs_kernel<1024, P, -1, false, 16, 16, 4>), grid, dim3(64 * P), 0, s, a, tiles);
                 else hipLaunchKernelGGL((mid_rs_kernel<1024, P, 1, false, 16, 16, 4>), grid, dim3(64 * P), 0, s, a, tiles);

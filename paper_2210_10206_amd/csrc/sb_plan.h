@@ -138,16 +138,38 @@ struct sb_plan {
     const float *d_coefw = nullptr;   // weighted 3j values, every term, per canonical Lambda
     std::vector<int> coefw_off;
     bool quad_mfma = false;       // full 4PCF contraction on the matrix cores (l <= 4, <= 8 bins)
+    // Launch shape of an untuned pass, by what every variant measured on 104 (strided axis 1) and 30
+    // (contiguous last axis) arrays of cubes and uneven grids.  Strided: the register-resident
+    // passes from 96 points on, 64-pencil tiles where the stride allows (us, variant 0 / chosen:
+    // 96^3 531 / 267, 128^3 706 / 587, 160^3 3755 / 1280, 192^3 4567 / 2196, 256^3 7897 / 4714, 512 of
+    // 64 x 512 x 64 1413 / 631); at 64 points the persistent wide-radix pass (84 / 72 us, the
+    // register-resident one 85).  Contiguous: persistent passes with wide radices (96^3 122 / 88,
+    // 160^3 1137 / 453, 192^3 1341 / 670), with the plain radices at 128 and 512 points, where they
+    // need less LDS (200 / 186, 380 / 224), and the one-tile shape with 32 threads per pencil at 256
+    // (105 / 85).  The short lengths are fastest one tile per workgroup.
+    static int default_fft_variant(int n, bool strided) {
+        if (strided) {
+            if (n == 1024) return 6;
+            if (n == 512) return 7;
+            if (n >= 96) return 9;
+            return n == 64 ? 4 : 0;
+        }
+        switch (n) {
+            case 96: case 192: return 4;
+            case 128: case 512: case 1024: return 2;
+            case 160: return 5;
+            case 256: return 1;
+            default: return 0;
+        }
+    }
     bool fused = true;            // fused last pass + contraction for the 3PCFs (flag SB_FLAG_UNFUSED clears it)
     bool adj_fused = true;        // adjoint: last pass fused with the adjoint weights (SB_FLAG_UNFUSED clears it)
     int quad_tile = 32, proj4_tile = 64;
     std::map<std::pair<int, int>, int> fft_var;   // (length, axis) -> variant
-    // untuned default: variant 0, except the register-resident 16-pencil pass along a strided axis
-    // of length 1024 (about 3x the LDS-staged pass there, where autotuning takes long)
     int fft_variant(int n, int axis) const {
         auto it = fft_var.find({n, axis});
         if (it != fft_var.end()) return it->second;
-        return n == 1024 && axis < prob.ndim - 1 ? 6 : 0;
+        return default_fft_variant(n, axis < prob.ndim - 1);
     }
     // per-launch timing
     bool timing = false;
