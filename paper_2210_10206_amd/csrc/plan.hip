@@ -132,10 +132,23 @@ static sb_status build_gather(sb_plan *p, std::vector<int> &gptr, std::vector<in
     return SB_OK;
 }
 
-// cpb: cells per workgroup (0: the plan's current choice)
+// Cells per workgroup of the cell-parallel contraction on a grid of ng cells: the contraction tile
+// (cpb, 0: the plan's current choice), halved for the 4PCFs while the launch would have under 1024
+// workgroups (a launch of the full 4PCF covers one Lambda, one of the projected 4PCF every triple),
+// down to two of the 64-cell tiles that its kernels stage, or one where that leaves under 128.  A
+// 32^3 grid is 32 workgroups of 1024 cells for 256 compute units.  Depends on the grid alone, so that a field's sums do not depend
+// on the batch.
+static int contract_cells(const sb_plan *p, int64_t ng, int cpb = 0) {
+    if (cpb == 0) cpb = p->contract_tile();
+    if (p->prob.npcf == 3) return cpb;
+    const int64_t per = p->prob.ndim == 3 ? 1 : (int64_t)p->p4_canon.size();
+    while ((cpb > 128 && (ng + cpb - 1) / cpb * per < 1024) || (cpb > 64 && (ng + cpb - 1) / cpb * per < 128)) cpb /= 2;
+    return cpb;
+}
+
 static void contraction_shape(const sb_plan *p, int64_t ng, int *groups, int *nvals, int *nblocks, int cpb = 0) {
     const int NB = p->prob.nbins;
-    if (cpb == 0) cpb = p->contract_tile();
+    cpb = contract_cells(p, ng, cpb);
     if (p->prob.npcf == 3) {
         *groups = p->nlm;
         *nvals = NB * (NB + 1) / 2 * (p->prob.ndim == 2 ? 2 : 1);
@@ -204,7 +217,11 @@ void layout_scratch(sb_plan *p) {
     }
     int groups = 0, nvals = 0, nblocks = 0, tile_lo = 0, tile_hi = 0;
     p->contract_tile_range(&tile_lo, &tile_hi);
-    contraction_shape(p, p->max_ng, &groups, &nvals, &nblocks, tile_lo);
+    for (const auto &G : p->groups) {
+        int nb = 0;
+        contraction_shape(p, G.ng, &groups, &nvals, &nb, tile_lo);
+        nblocks = std::max(nblocks, nb);
+    }
     for (const auto &G : p->groups)
         if (G.rows > 0 && prob->npcf == 3) {
             const int64_t nrows = G.ng / G.n[prob->ndim - 1];
@@ -234,6 +251,9 @@ static void table_pointers(sb_plan *p) {
         p->d_lam_l = reinterpret_cast<const int *>(base + p->off_laml);
         p->d_stage = reinterpret_cast<const int *>(base + p->off_stage);
         p->d_coefw = reinterpret_cast<const float *>(base + p->off_coefw);
+        p->d_gterms = reinterpret_cast<const QuadGTerm *>(base + p->off_gterms);
+        p->d_gtptr = reinterpret_cast<const int *>(base + p->off_gtptr);
+        p->d_glam = reinterpret_cast<const int *>(base + p->off_glam);
     }
     if (p->prob.npcf == 4 && p->prob.ndim == 2) p->d_pairs = reinterpret_cast<const int *>(base + p->off_pairs);
     if (p->npack > 0) {
@@ -409,10 +429,8 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
         p->idx_cols = 1;
         for (int l = 0; l <= L; ++l) p->idx_table.push_back(l);
     } else if (prob->ndim == 3) {
-        // the matrix-core kernels cover l <= 4 and <= 8 bins; their canonical orderings are
-        // chosen for that kernel
-        const bool mfma = (prob->flags & SB_FLAG_NO_MFMA) == 0 && L <= 4 && NB <= 8;
-        p->f4 = make_full4_plan(L, NB, (prob->flags & SB_FLAG_ODD_PARITY) == 0, mfma);
+        // the canonical orderings are chosen for the kernel of each Lambda
+        p->f4 = make_full4_plan(L, NB, (prob->flags & SB_FLAG_ODD_PARITY) == 0, (prob->flags & SB_FLAG_NO_MFMA) == 0);
         p->zeta_doubles = (int64_t)p->f4.out_lams.size() * NB * NB * NB;
         p->idx_rows = (int32_t)p->f4.out_lams.size();
         p->idx_cols = 3;
@@ -488,13 +506,56 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
             p->max_cols = std::max(p->max_cols, ncol);
             stage.insert(stage.end(), st.begin(), st.end());
         }
+        // terms of the run-time matrix-core contraction: per Lambda mc outer, ma inner, vanishing
+        // symbols left out; negative orders as a_{l,-m} = (-1)^m conj(a_{l,m}); mc = 0 keeps ma >= 0,
+        // the pair (ma, -ma) as one product (even Lambda: real, 2 (-1)^ma C; odd: imaginary)
+        std::vector<QuadGTerm> gterms;
+        std::vector<int> gtptr(1, 0), glam;
+        const int nbp = 4 * quad_gen_side(NB);
+        const bool odd = (prob->flags & SB_FLAG_ODD_PARITY) != 0;
+        for (size_t c = 0; c < p->f4.canon.size(); ++c) {
+            if (p->f4.kind[c] == QUAD_GEN) {
+                glam.push_back((int)c);
+                const int *st = stage.data() + c * kStageStride;
+                int last_mc = -1;
+                for (const auto &t : p->f4.terms[c]) {
+                    if (t.c == 0.0 || (t.mc == 0 && (t.ma < 0 || (odd && t.ma == 0)))) continue;
+                    QuadGTerm q{};
+                    q.off = (uint32_t)((st[0] + std::abs(t.ma)) * nbp) | (uint32_t)((st[1] + std::abs(t.mb)) * nbp) << 16;
+                    if (t.mc == 0) {
+                        q.c = (float)(t.ma == 0 ? t.c : (t.ma & 1) ? -2.0 * t.c : 2.0 * t.c);
+                        q.flags = kGPaired;
+                    } else {
+                        double sign = 1.0;
+                        if (t.ma < 0 && (t.ma & 1)) sign = -sign;
+                        if (t.mb < 0 && (t.mb & 1)) sign = -sign;
+                        q.c = (float)(sign * t.c);
+                        q.flags = (t.ma < 0 ? kGConj1 : 0u) | (t.mb < 0 ? kGConj2 : 0u);
+                    }
+                    if (last_mc == t.mc) gterms.back().flags &= ~kGLast;
+                    last_mc = t.mc;
+                    q.flags |= kGLast | (uint32_t)t.mc << 8;
+                    gterms.push_back(q);
+                }
+            }
+            while (gterms.size() % kGRun) gterms.push_back(QuadGTerm{});
+            gtptr.push_back((int)gterms.size());
+        }
+        // most terms first: the launch runs a cell block's Lambda in this order, so it ends on short ones
+        std::stable_sort(glam.begin(), glam.end(), [&](int x, int y) {
+            return gtptr[x + 1] - gtptr[x] > gtptr[y + 1] - gtptr[y];
+        });
+        p->nglam = (int)glam.size();
+        p->off_gterms = put(gterms.data(), gterms.size() * sizeof(QuadGTerm));
+        p->off_gtptr = put(gtptr.data(), gtptr.size() * sizeof(int));
+        p->off_glam = put(glam.data(), glam.size() * sizeof(int));
         p->off_terms = put(terms.data(), terms.size() * sizeof(QuadTerm));
         p->off_tptr = put(tptr.data(), tptr.size() * sizeof(int));
         p->off_laml = put(laml.data(), laml.size() * sizeof(int));
         p->off_stage = put(stage.data(), stage.size() * sizeof(int));
         p->off_coefw = put(coefw.data(), coefw.size() * sizeof(float));
-        p->quad_mfma = (prob->flags & SB_FLAG_NO_MFMA) == 0;
-        for (const Lam &C : p->f4.canon) p->quad_mfma &= quad_mfma_available(C.l[0], C.l[1], C.l[2], prob->nbins);
+        p->quad_mfma = true;
+        for (const int k : p->f4.kind) p->quad_mfma &= k == QUAD_MFMA;
     }
     if (prob->npcf == 4 && prob->ndim == 2) {
         std::vector<int> pr;
@@ -901,7 +962,7 @@ sb_status contract(sb_plan *p, const ShapeGroup &G, double *const *zout, int nf,
         a.terms = p->d_terms;
         a.stage = p->d_stage;
         a.max_cols = p->max_cols;
-        a.cells_per_block = p->cpb_quad;
+        a.cells_per_block = contract_cells(p, G.ng);
         a.tile = p->quad_tile;
         a.nlm = p->nlm;
         a.partial = part;
@@ -941,10 +1002,11 @@ sb_status contract(sb_plan *p, const ShapeGroup &G, double *const *zout, int nf,
             fma += NB * (1.0 + 2.0 * lc);
             return pairs * 2.0 * fma + 2.0 * NB * (lc + 1);
         };
-        if (p->quad_mfma) {
-            // one launch per canonical Lambda: its coefficients stay in registers
+        if ((p->prob.flags & SB_FLAG_NO_MFMA) == 0) {
+            // compile-time kernels: one launch per canonical Lambda, its coefficients in registers
             double by = 0.0;
             for (size_t c = 0; c < p->f4.canon.size() && e == hipSuccess; ++c) {
+                if (p->f4.kind[c] != QUAD_MFMA) continue;
                 const Lam &C = p->f4.canon[c];
                 QuadMArgs m{};
                 m.coef = coef;
@@ -953,7 +1015,7 @@ sb_status contract(sb_plan *p, const ShapeGroup &G, double *const *zout, int nf,
                 m.nbins = NB;
                 m.lam = (int)c;
                 m.coefw = p->d_coefw + p->coefw_off[c];
-                m.cells_per_block = p->cpb_quad;
+                m.cells_per_block = a.cells_per_block;
                 m.nblocks = nblocks;
                 m.precision = p->prob.precision == SB_PREC_SPLIT_BF16 ? 1 : 0;
                 m.partial = part;
@@ -973,6 +1035,19 @@ sb_status contract(sb_plan *p, const ShapeGroup &G, double *const *zout, int nf,
                                     [&]() { return launch_quad_mfma(C.l[0], C.l[1], C.l[2], m, s); }, 0, 0, nf, by,
                                     (double)nf * G.ng * lam_flops_mfma(c));
             }
+            // the other Lambda: one launch of the run-time kernel
+            if (p->nglam > 0 && e == hipSuccess) {
+                a.gterms = p->d_gterms;
+                a.gptr = p->d_gtptr;
+                a.glam = p->d_glam;
+                a.nglam = p->nglam;
+                double fl = 0.0;
+                for (size_t c = 0; c < p->f4.canon.size(); ++c)
+                    if (p->f4.kind[c] == QUAD_GEN) fl += lam_flops_mfma(c);
+                by = (double)nf * G.ng * (8.0 * p->nk + 4.0);
+                e = p->timed_launch(STAGE_CONTRACT, K_QUAD_MFMA, s, [&]() { return launch_quad_gen(a, s); }, 0, 0,
+                                    nf * p->nglam, by, (double)nf * G.ng * fl);
+            }
         } else {
             double fl = 0.0;
             for (size_t c = 0; c < p->f4.canon.size(); ++c) fl += lam_flops(c);
@@ -989,7 +1064,7 @@ sb_status contract(sb_plan *p, const ShapeGroup &G, double *const *zout, int nf,
         a.npairs = groups;
         a.pairs = p->d_pairs;
         a.mmax = p->prob.lmax;
-        a.cells_per_block = p->cpb_proj4;
+        a.cells_per_block = contract_cells(p, G.ng);
         a.tile = p->proj4_tile;
         a.partial = part;
         a.nblocks = nblocks;

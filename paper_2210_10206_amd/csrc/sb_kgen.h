@@ -58,6 +58,19 @@ struct QuadTerm {             // one (m3 >= 0, m1) term of a canonical Lambda
     int32_t ma, mb, mc;       // signed orders of the three coefficients (mc >= 0)
     float c;                  // 3j value times the m3 >= 0 weight (1 or 2)
 };
+// One term of the run-time matrix-core contraction (quad_gen.hip): LDS columns of the two operands
+// in float2 (column * padded bins; the first in the low half), with the signs of negative orders
+// folded in: L += (x.x, s1 x.y) * c (y.x, s2 y.y), s = -1 with kGConj1 / kGConj2.
+struct QuadGTerm {
+    uint32_t off;
+    float c;
+    uint32_t flags;            // kG*, mc << 8
+    uint32_t pad;              // 16 bytes: four terms in one scalar load
+};
+constexpr uint32_t kGPaired = 1;   // mc = 0: the terms +-ma together (one real or imaginary product)
+constexpr uint32_t kGLast = 2;     // last term of its mc
+constexpr uint32_t kGConj1 = 1u << 30, kGConj2 = 1u << 31;
+constexpr int kGRun = 4;      // terms read together: a Lambda's list is filled up with vanishing ones
 constexpr int kStageStride = 4 + 3 * (kMaxL + 1);
 struct QuadArgs {
     const float2 *coef;       // [lm][bin][ng], lm = l(l+1)/2 + m, m >= 0
@@ -81,7 +94,16 @@ struct QuadArgs {
                               // 1 / 2: the real / imaginary part of a packed m = 0 array)
     int fields;               // fields of one shape in the launch (grid.z; 0 counts as 1)
     int64_t coef_fs, w_fs, part_fs;
+    // quad_gen.hip only: its terms (gptr[lam] .. gptr[lam + 1]) and the
+    // nglam canonical Lambdas it computes
+    const QuadGTerm *gterms;
+    const int *gptr, *glam;
+    int nglam;
 };
+// Matrix-core form for run-time (la, lb, lc) and at most 10 bins; quad_gen_side: its tiles of 4
+// bins per side of a lane's pair block.
+hipError_t launch_quad_gen(const QuadArgs &a, hipStream_t s);
+int quad_gen_side(int nbins);
 hipError_t launch_quad_contract(const QuadArgs &a, hipStream_t s);
 
 // Matrix-core form for one ordered Lambda with l <= 4 and at most 8 bins (quad_mfma.h).

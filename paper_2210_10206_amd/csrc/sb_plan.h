@@ -75,6 +75,8 @@ struct sb_plan {
     std::vector<char> host_tab;
     size_t tab_bytes = 0;
     std::map<int, size_t> tw_off;
+    size_t off_gterms = 0, off_gtptr = 0, off_glam = 0;   // run-time matrix-core contraction
+    int nglam = 0;                                        // its canonical Lambdas
     size_t off_terms = 0, off_tptr = 0, off_laml = 0, off_stage = 0, off_pairs = 0, off_coefw = 0;
     size_t off_kmap = 0, off_rowmap = 0, off_lmsrc = 0, off_gptr = 0, off_gidx = 0, off_gcoef = 0;
     std::map<int, const float2 *> tw;
@@ -82,6 +84,8 @@ struct sb_plan {
     const int *d_term_ptr = nullptr, *d_lam_l = nullptr, *d_stage = nullptr, *d_pairs = nullptr;
     const int *d_gptr = nullptr, *d_gidx = nullptr;
     const double *d_gcoef = nullptr;
+    const sb::QuadGTerm *d_gterms = nullptr;
+    const int *d_gtptr = nullptr, *d_glam = nullptr;
     int gather_nout = 0;
     int max_cols = 0;
     // workspace (caller-owned)
@@ -137,7 +141,7 @@ struct sb_plan {
     }
     const float *d_coefw = nullptr;   // weighted 3j values, every term, per canonical Lambda
     std::vector<int> coefw_off;
-    bool quad_mfma = false;       // full 4PCF contraction on the matrix cores (l <= 4, <= 8 bins)
+    bool quad_mfma = false;       // every canonical Lambda has a compile-time matrix-core kernel (l <= 4, <= 8 bins)
     // Launch shape of an untuned pass, by what every variant measured on 104 (strided axis 1) and 30
     // (contiguous last axis) arrays of cubes and uneven grids.  Strided: the register-resident
     // passes from 96 points on, 64-pencil tiles where the stride allows (us, variant 0 / chosen:

@@ -14,6 +14,7 @@ struct QuadTermH { int ma, mb, mc; double c; };
 struct Full4Plan {
     std::vector<Lam> out_lams;                    // output order (Alg. 6 loops, one parity)
     std::vector<Lam> canon;                       // computed orderings (la, lb, lc)
+    std::vector<int> kind;                        // per canonical: QuadKind
     std::vector<std::vector<QuadTermH>> terms;    // per canonical: (ma, mb, mc >= 0, weighted 3j)
     std::vector<int> out_canon;                   // per output Lambda: canonical index
     std::vector<std::array<int, 3>> out_pos;      // canonical position k <- output position out_pos[k]
@@ -24,6 +25,10 @@ bool exact_floor_square(double e, int64_t *out);
 double ylm_norm(int l, int m);
 double wigner3j(int j1, int j2, int j3, int m1, int m2, int m3);
 std::vector<Lam> full4_lambdas(int lmax, bool even);
+// Contraction kernel of a canonical Lambda: the vector kernel, the compile-time matrix-core
+// kernels (l <= 4, at most 8 bins) or the run-time matrix-core kernel (the others).
+enum QuadKind : int { QUAD_VALU = 0, QUAD_MFMA = 1, QUAD_GEN = 2 };
+// mfma: kinds 1 and 2 where they apply, else every Lambda takes the vector kernel.
 Full4Plan make_full4_plan(int lmax, int nbins, bool even = true, bool mfma = false);
 std::vector<std::pair<int, int>> proj4_pairs(int mmax);
 

@@ -112,11 +112,26 @@ static double mfma_cost(int la, int lb, int lc, const std::vector<QuadTermH> &t,
     return std::max(4.0 * valu, 32.0 * mfma) + 0.01 * (4.0 * valu + 32.0 * mfma);
 }
 
+// The same of the run-time kernel (quad_gen.hip): T x T pairs of a lane per term from 2 T LDS reads
+// (8 T cycles of the LDS that four SIMDs share), la == lb computing T (T + 1) / 2 of the T^2 tiles.
+static double gen_cost(int la, int lb, int lc, const std::vector<QuadTermH> &t, int nbins, bool even) {
+    const int T = nbins <= 4 ? 1 : nbins <= 8 ? 2 : 3;
+    const double nt = la == lb ? T * (T + 1) / 2 : T * T;
+    double valu = 0.0, lds = 0.0;
+    for (const QuadTermH &q : t) {
+        if (q.c == 0.0 || (q.mc == 0 && (q.ma < 0 || (!even && q.ma == 0)))) continue;
+        valu += 2.0 * (q.mc == 0 ? 2 * T + 2 * nt + 4 : 3 * T + 4 * nt + 4);
+        lds += 32.0 * T;
+    }
+    const double mfma = 32.0 * nt * (2.0 * lc + 1.0);
+    return std::max({valu, lds, mfma}) + 0.2 * (valu + lds + mfma);
+}
+
 Full4Plan make_full4_plan(int lmax, int nbins, bool even, bool mfma) {
     Full4Plan p;
     p.out_lams = full4_lambdas(lmax, even);
     // canonical = sorted triples; pick the cheapest ordering: fewest flops per cell for the
-    // vector kernel, fewest issue cycles (mfma_cost) for the matrix-core kernels
+    // vector kernel, fewest issue cycles (mfma_cost, gen_cost) for the matrix-core kernels
     std::vector<Lam> sorted;
     for (const Lam &L : p.out_lams) {
         Lam s = L;
@@ -128,6 +143,8 @@ Full4Plan make_full4_plan(int lmax, int nbins, bool even, bool mfma) {
     const double nb2 = (double)nbins * nbins, nb3 = nb2 * nbins;
     for (const Lam &s : sorted) {
         int perm[3] = {0, 1, 2};
+        // s.l[2] is the largest l; the compile-time kernels exist up to 4 and for at most 8 bins
+        const int kind = !mfma ? QUAD_VALU : s.l[2] <= 4 && nbins <= 8 ? QUAD_MFMA : QUAD_GEN;
         double best = 1e300;
         Lam bestL = s;
         std::vector<QuadTermH> bestT;
@@ -135,11 +152,13 @@ Full4Plan make_full4_plan(int lmax, int nbins, bool even, bool mfma) {
             const int la = s.l[perm[0]], lb = s.l[perm[1]], lc = s.l[perm[2]];
             std::vector<QuadTermH> t;
             terms_of(la, lb, lc, &t);
-            const double cost = mfma ? mfma_cost(la, lb, lc, t, even)
-                                     : (double)t.size() * nb2 * 8.0 + (double)(lc + 1) * nb3 * 4.0;
+            const double cost = kind == QUAD_MFMA ? mfma_cost(la, lb, lc, t, even)
+                                : kind == QUAD_GEN ? gen_cost(la, lb, lc, t, nbins, even)
+                                                   : (double)t.size() * nb2 * 8.0 + (double)(lc + 1) * nb3 * 4.0;
             if (cost < best) { best = cost; bestL = {la, lb, lc}; bestT = t; }
         } while (std::next_permutation(perm, perm + 3));
         p.canon.push_back(bestL);
+        p.kind.push_back(kind);
         p.terms.push_back(bestT);
     }
     // each output Lambda: its canonical index and position map
