@@ -1,6 +1,9 @@
 // Last inverse pass (contiguous axis) fused with the two-coefficient contraction,
 // instantiated for the lengths listed at the end of the including file.
 #pragma once
+#include <algorithm>
+#include <type_traits>
+
 #include "fft_core.h"
 
 namespace sb {
@@ -108,8 +111,9 @@ struct PairSums {
     // PLANE > 0 (not PS_COMPLEX): the stage holds separate real and imaginary planes, the part of
     // (c, b) at float offset off(c) + b * bstride + part * PLANE, so each lane reads its own part.
     template <int NCELL, int NW, int PLANE = 0, class Off>
+    // Bins from nbl on read as zero.
     __device__ __forceinline__ void accumulate(const float2 *stage, int bstride, const float *wsm, Off off, int wave,
-                                               int lane) {
+                                               int lane, int nbl = NBT) {
         static_assert(PLANE == 0 || MODE != PS_COMPLEX, "the complex form reads both parts");
         constexpr int NG = (NCELL + CPG - 1) / CPG;
         const int slot = lane >> 2, j = lane & 3;
@@ -126,7 +130,7 @@ struct PairSums {
                 float x[Q], xo[Q];
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
-                    const bool in = ok && (NBT % 4 == 0 || 4 * q + j < NBT);
+                    const bool in = ok && 4 * q + j < nbl;
                     if constexpr (PLANE > 0) {
                         const float *sf = reinterpret_cast<const float *>(stage);
                         x[q] = in ? sf[off(c) + (4 * q + j) * bstride + (im_slot ? PLANE : 0)] : 0.f;
@@ -533,15 +537,92 @@ hipError_t launch_last_reg(const LastArgs &a, hipStream_t s) {
     return a.prec ? launch_last_reg_p<R1, R2, 1>(a, s) : launch_last_reg_p<R1, R2, 0>(a, s);
 }
 
-// Register-resident form for any radix list R0, ... (each radix divides R0; see reg_stages):
-// a tile is one row of the NBT (padded) bins of one (l, m); thread q < T = n / R0 of a
-// pencil loads elements q + T s.  The stages exchange through one LDS buffer laid out
-// [position][bin], which, once the last stage has read it, takes the transformed row as the
-// [cell][bin] tile of the MFMA pair sums (one more barrier per row).  Two buffers (one barrier
-// fewer) would not fit the LDS at 1024 points, and below that they held the workgroups per CU
-// under what the registers allow (one buffer: uneven 64-192^3 forward 401 -> 412 fields/s).
+// The stages after the first of a row transform whose threads are lanes of one wave (T = N / R0 of
+// them, 64 % T == 0), exchanging through the row's own LDS region: position j at own[j + (j >> GSH)].
+// As reg_stage_rest, without workgroup barriers; tws holds each stage's twiddles as [r][k mod NS],
+// stage after stage, so that the lanes read adjacent entries.
+template <int N, int T, int GSH, int NS, int R, int... REST>
+__device__ __forceinline__ void wave_stage_rest(float2 *v, float2 *own, const float2 *tws, int q) {
+    auto at = [](int j) { return j + (j >> GSH); };
+    constexpr int NBF = N / R;        // butterflies of this stage
+    constexpr int PER = NBF / T;      // per thread
+    static_assert(NBF % T == 0, "butterflies must split evenly over the threads");
+    constexpr bool LAST = sizeof...(REST) == 0;
+    float2 u[PER][R];
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+        const int k = q + T * t;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            float2 x = own[at(k + r * NBF)];
+            if (r > 0) {
+                const float2 w = tws[(r - 1) * NS + k % NS];   // the inverse takes the conjugate
+                x = cmul(x, make_float2(w.x, -w.y));
+            }
+            u[t][r] = x;
+        }
+        Dft<R, 1>::run(u[t]);
+    }
+    wave_lds_sync();   // the stage's inputs are read
+    if constexpr (LAST) {
+        static_assert(NS % T == 0, "the last radix must divide the first");
+#pragma unroll
+        for (int t = 0; t < PER; ++t)
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[t + (NS / T) * r] = u[t][r];
+    } else {
+#pragma unroll
+        for (int t = 0; t < PER; ++t) {
+            const int k = q + T * t;
+            const int base = (k / NS) * NS * R + k % NS;
+#pragma unroll
+            for (int r = 0; r < R; ++r) own[at(base + r * NS)] = u[t][r];
+        }
+        wave_lds_sync();
+        wave_stage_rest<N, T, GSH, NS * R, REST...>(v, own, tws + (R - 1) * NS, q);
+    }
+}
+
+// Entries of the twiddle tables of wave_stage_rest, and their fill.
+template <int NS, int R, int... REST>
+constexpr int wave_twiddles() {
+    if constexpr (sizeof...(REST) == 0) return (R - 1) * NS;
+    else return (R - 1) * NS + wave_twiddles<NS * R, REST...>();
+}
+template <int N, int NT, int NS, int R, int... REST>
+__device__ __forceinline__ void fill_wave_twiddles(float2 *tws, const float2 *tw, int tid) {
+    for (int i = tid; i < (R - 1) * NS; i += NT) tws[i] = tw[(i / NS + 1) * (i % NS) * (N / (NS * R))];
+    if constexpr (sizeof...(REST) > 0) fill_wave_twiddles<N, NT, NS * R, REST...>(tws + (R - 1) * NS, tw, tid);
+}
+
+// LDS region of a row in last_rs_kernel: its exchange positions (one skew slot every 2^row_skew: at 512
+// points and up every 16, which keeps the 16-point first stage's stores off one bank), then the
+// transformed row, as planes 8 mod 64 floats apart (split) or complex values.
+constexpr int row_skew(int n) { return n >= 512 ? 4 : 5; }
+constexpr int row_plane(int n) { return (n + 55) / 64 * 64 + 8; }
+template <int N> constexpr int row_region(bool split) {
+    static_assert(row_plane(N) >= N, "the real plane fits");
+    return pencil_region(N + ((N - 1) >> row_skew(N)), split ? (row_plane(N) + N + 1) / 2 : N);
+}
+
+// Waves per SIMD last_rs_kernel is compiled for: as many as its LDS allows without spilling more than
+// a few registers (16 bins with the complex sums hold 80 accumulators).
+constexpr int rs_waves(int n, int nbt, int mode) {
+    if (n >= 1024) return 1;
+    if (nbt > 12) return mode == PS_COMPLEX ? 2 : n == 160 ? 3 : 4;
+    return n == 96 || (n == 512 && nbt <= 8) ? 4 : 3;
+}
+
+// Register-resident form for the three-stage radix lists R0, ... (the last radix divides R0): a tile
+// is one row of the NBT (padded) bins of one (l, m); thread q < T = n / R0 of a pencil loads elements
+// q + T s.  As in last_reg_kernel a pencil's threads are lanes of one wave and its exchanges go
+// through its own LDS region, so the workgroup meets at two barriers a row, and the row ends in the
+// region as real and imaginary planes for the pair sums, flushed to float64 every FLUSH rows.  The
+// sequence of one row, not the bytes, bounds the pass: with one exchange buffer of all pencils it met
+// at seven barriers a row and flushed after each, 33.6 ms per 512^3 field of 6 bins and 13 array
+// groups (2.5 TB/s read), now 21.6 (3.9 TB/s); 1.66 -> 1.43 ms at 192^3, 8 bins, 13 groups.
 template <int N, int NBT, int MODE, int PREC, int R0, int... REST>
-__global__ __launch_bounds__(NBT * (N / R0)) void last_rs_kernel(LastArgs a) {
+__global__ __launch_bounds__(NBT * (N / R0), rs_waves(N, NBT, MODE)) void last_rs_kernel(LastArgs a) {
     a.in += (int64_t)blockIdx.z * a.in_fs;   // field of the launch (grid.z)
     a.w += (int64_t)blockIdx.z * a.w_fs;
     a.partial += (int64_t)blockIdx.z * a.part_fs;
@@ -551,22 +632,21 @@ __global__ __launch_bounds__(NBT * (N / R0)) void last_rs_kernel(LastArgs a) {
     constexpr int NT = P * T;
     constexpr int NW = NT / 64;
     constexpr int NOUT = PS::NOUT;
-    constexpr int PITCH = P + 1;
-    // the transform's stages at 512 and 1024 points (first radix 16) keep position j of pencil p
-    // at j PITCH + p + j / 16: the first stage writes positions q R0 + r, which without the skew
-    // put a pencil's threads a multiple of 16 float2 (the width of the 32 banks) apart, all in one
-    // bank.  The [cell][bin] view written after the last stage keeps the plain layout.
-    constexpr int SKEW = N >= 512 ? 1 : 0, GSH = 4;
-    constexpr int NSTAGE = 1 + sizeof...(REST);
+    constexpr int GSH = row_skew(N);
+    constexpr bool SPLIT = MODE != PS_COMPLEX;
+    constexpr int PLANE = row_plane(N);
+    constexpr int REG = row_region<N>(SPLIT);
     constexpr int WPT = (N + NT - 1) / NT;
-    static_assert(NT % 64 == 0 && NSTAGE >= 2, "whole waves, two stages or more");
-    __shared__ float2 ex[N * PITCH + (N >> GSH) * SKEW];
-    __shared__ float2 tw[N];
+    static_assert(NT % 64 == 0 && 64 % T == 0 && sizeof...(REST) >= 1, "whole waves, a pencil in one of them");
+    constexpr int FLUSH = NBT * PS::NACC <= 12 ? 8 : 1;   // larger accumulators would not stay in registers
+    extern __shared__ float2 lds[];        // one region per bin (dead pencils have none)
+    __shared__ float2 tws[wave_twiddles<R0, REST...>()];
     __shared__ float wsm[N];
     const int nb = a.nb;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int q = tid % T, pp = tid / T;        // element column, pencil (= bin)
-    for (int i = tid; i < N; i += NT) tw[i] = a.tw[i];
+    float2 *own = lds + pp * REG;
+    fill_wave_twiddles<N, NT, R0, REST...>(tws, a.tw, tid);
     PS ps;
     ps.zero();
     const int64_t nrows = a.ng / N;
@@ -583,10 +663,11 @@ __global__ __launch_bounds__(NBT * (N / R0)) void last_rs_kernel(LastArgs a) {
             wdst[e] = c < N ? a.w[row * N + c] : 0.f;
         }
     };
-    // PF: the next row's loads are in flight during this row.  The registers allow it except for
-    // the 1024-point tiles of more than 8 bins; there the next row loads into the row's own
-    // registers once they are stored to LDS, so its loads are in flight during the pair sums.
-    constexpr bool PF = N < 1024 || NBT <= 8;
+    // PF: the next row's loads are in flight during this row.  From 512 points on its registers would
+    // cost a wave per SIMD (512^3, 6 bins: 26.6 ms against 21.6), so there the next row loads into the
+    // row's own registers once they are stored to LDS, its loads in flight during the pair sums; the
+    // complex sums of more than 8 bins at 512 hold too many registers for that wave anyway.
+    constexpr bool PF = N < 512 || (N == 512 && NBT > 8 && MODE == PS_COMPLEX);
     float2 nx[PF ? R0 : 1];
     float nw[PF ? WPT : 1];
     float2 v[R0];
@@ -595,6 +676,7 @@ __global__ __launch_bounds__(NBT * (N / R0)) void last_rs_kernel(LastArgs a) {
         if constexpr (PF) load_row(r_begin, nx, nw);
         else load_row(r_begin, v, wv);
     }
+    __syncthreads();   // twiddles
     for (int64_t row = r_begin; row < r_end; ++row) {
         if constexpr (PF) {
 #pragma unroll
@@ -603,24 +685,44 @@ __global__ __launch_bounds__(NBT * (N / R0)) void last_rs_kernel(LastArgs a) {
             for (int e = 0; e < WPT; ++e) wv[e] = nw[e];
             if (row + 1 < r_end) load_row(row + 1, nx, nw);    // next row in flight
         }
-        __syncthreads();                                    // the previous row's pair sums are done
-        reg_stages<N, 1, R0, REST...>(v, ex, ex, tw, q, pp, PITCH, SKEW, GSH);
-        float2 *cs = ex;
-        __syncthreads();                                    // the last stage has read the buffer
+        asm volatile("" ::: "memory");   // the twiddles stay in LDS: held in registers they cost waves
+        if (live) Dft<R0, 1>::run(v);   // first stage: butterfly q on the own elements, no twiddles
+        __syncthreads();      // the previous row's pair sums are done
+        if (live) {
 #pragma unroll
-        for (int r = 0; r < R0; ++r) cs[(q + T * r) * PITCH + pp] = v[r];
+            for (int r = 0; r < R0; ++r) {
+                const int j = q * R0 + r;
+                own[j + (j >> GSH)] = v[r];
+            }
+            wave_lds_sync();
+            wave_stage_rest<N, T, GSH, R0, REST...>(v, own, tws, q);
+            if constexpr (SPLIT) {
+                float *ownf = reinterpret_cast<float *>(own);
+#pragma unroll
+                for (int r = 0; r < R0; ++r) {
+                    ownf[q + T * r] = v[r].x;
+                    ownf[PLANE + q + T * r] = v[r].y;
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R0; ++r) own[q + T * r] = v[r];
+            }
+        }
 #pragma unroll
         for (int e = 0; e < WPT; ++e)
             if (tid + e * NT < N) wsm[tid + e * NT] = wv[e];
         __syncthreads();
         if constexpr (!PF)
             if (row + 1 < r_end) load_row(row + 1, v, wv);   // in flight during the pair sums
-        ps.template tile<N, NW>(cs, 1, wsm, [](int c) { return c * PITCH; }, wave, lane);
+        if constexpr (SPLIT)
+            ps.template accumulate<N, NW, PLANE>(lds, 2 * REG, wsm, [](int c) { return c; }, wave, lane, nb);
+        else
+            ps.template accumulate<N, NW>(lds, REG, wsm, [](int c) { return c; }, wave, lane, nb);
+        if ((row - r_begin) % FLUSH == FLUSH - 1 || row + 1 == r_end) ps.flush(lane);
     }
     // float64 combine over the waves in wave order (as in last_contract_kernel)
     __syncthreads();
-    static_assert(PS::red_doubles(NW) * sizeof(double) <= sizeof(ex), "block reduction fits");
-    double *red = reinterpret_cast<double *>(ex);
+    double *red = reinterpret_cast<double *>(lds);
     ps.to_lds(red, wave, lane);
     __syncthreads();
     const int nv = nb * (nb + 1) / 2 * NOUT;
@@ -629,24 +731,29 @@ __global__ __launch_bounds__(NBT * (N / R0)) void last_rs_kernel(LastArgs a) {
             PS::block_value(red, NW, nb, vv);
 }
 
-// (1024 points: at most 12 bins, as last_rows<1024> allows; wider tiles would spill)
 template <int N, int PREC, int R0, int... REST>
 hipError_t launch_last_rs_p(const LastArgs &a, hipStream_t s) {
     constexpr int T = N / R0;
     dim3 grid((unsigned)a.nblocks, (unsigned)a.groups, (unsigned)(a.fields > 1 ? a.fields : 1));
     const int mode = pair_mode(a);
     const int nbt = reg_padded_bins(a.nb, T);
+    auto shm = [&](auto nbt_c, auto mode_c) -> size_t {
+        constexpr int NBT = decltype(nbt_c)::value, MODE = decltype(mode_c)::value;
+        return std::max<size_t>((size_t)a.nb * row_region<N>(MODE != PS_COMPLEX) * sizeof(float2),
+                                (size_t)PairSums<NBT, MODE, PREC>::red_doubles(NBT * T / 64) * sizeof(double));
+    };
 #define SB_LR(NBT)                                                                                                   \
     case NBT:                                                                                                         \
-        if constexpr ((NBT * T) % 64 == 0 && NBT * T <= 1024 && (N < 1024 || NBT <= 12)) {                           \
+        if constexpr ((NBT * T) % 64 == 0 && NBT * T <= 1024) {                                                       \
             if (mode == PS_COMPLEX)                                                                                   \
-                hipLaunchKernelGGL((last_rs_kernel<N, NBT, PS_COMPLEX, PREC, R0, REST...>), grid, dim3(NBT * T), 0, s, \
-                                   a);                                                                                \
+                hipLaunchKernelGGL((last_rs_kernel<N, NBT, PS_COMPLEX, PREC, R0, REST...>), grid, dim3(NBT * T),                   \
+                                   shm(std::integral_constant<int, NBT>{}, std::integral_constant<int, PS_COMPLEX>{}), s, a); \
             else if (mode == PS_PACKED)                                                                               \
-                hipLaunchKernelGGL((last_rs_kernel<N, NBT, PS_PACKED, PREC, R0, REST...>), grid, dim3(NBT * T), 0, s,  \
-                                   a);                                                                                \
+                hipLaunchKernelGGL((last_rs_kernel<N, NBT, PS_PACKED, PREC, R0, REST...>), grid, dim3(NBT * T),                   \
+                                   shm(std::integral_constant<int, NBT>{}, std::integral_constant<int, PS_PACKED>{}), s, a); \
             else                                                                                                      \
-                hipLaunchKernelGGL((last_rs_kernel<N, NBT, PS_REAL, PREC, R0, REST...>), grid, dim3(NBT * T), 0, s, a); \
+                hipLaunchKernelGGL((last_rs_kernel<N, NBT, PS_REAL, PREC, R0, REST...>), grid, dim3(NBT * T),                   \
+                                   shm(std::integral_constant<int, NBT>{}, std::integral_constant<int, PS_REAL>{}), s, a); \
             break;                                                                                                    \
         } else {                                                                                                      \
             return hipErrorInvalidValue;                                                                              \

@@ -13,6 +13,6 @@ template <> int last_rows<512>(int nb) { return nb <= 16 ? 1 : 0; }
 template <> hipError_t launch_last_for<1024>(const LastArgs &a, hipStream_t s) {
     return fftlast::launch_last_rs<1024, 16, 16, 4>(a, s);
 }
-template <> int last_rows<1024>(int nb) { return nb <= 12 ? 1 : 0; }   // 16-bin tiles would spill
+template <> int last_rows<1024>(int nb) { return nb <= 16 ? 1 : 0; }
 
 }  // namespace sb

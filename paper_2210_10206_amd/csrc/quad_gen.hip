@@ -12,8 +12,13 @@
 // is (i1, i2) = (i / 4, i % 4) and tile (t1, t2) holds the pairs b1 = i1 + 4 t1, b2 = i2 + 4 t2, which
 // takes 2 T reads for T^2 products (T = 3 for 9 or 10 bins: 6 reads of 512 B a wave, 24 LDS cycles,
 // for 36 FMAs, 72 cycles of one of the four SIMDs).  la = lb computes only the tiles t1 <= t2
-// (Z[b2][b1] = +-Z[b1][b2]).  The next term's values are in flight during the current one.
-// Measured on 64^3 cells, 10 bins, lmax 5, odd parity (14 canonical Lambda): see launch_quad_gen.
+// (Z[b2][b1] = +-Z[b1][b2]).  The next term's values are in flight during the current one, and the
+// table comes kGRun terms to a scalar load, a run ahead (read one by one, each term waited for its
+// scalar load: 2.8 ms against 2.3).
+// Measured on 64^3 cells, 10 bins, lmax 5, odd parity (14 canonical Lambda): 2.3 ms, where the vector
+// kernel (quad_kernel), with its two LDS reads for every product, takes 13.8.  What bounds it is the
+// issue of the coupling (at 3.5 waves a SIMD the vector ALUs are busy 41 % of the cycles, the LDS 37 %,
+// the matrix cores 24 %), 30 % of it spent on the bins that pad 10 to 12.
 //
 // LDS: one row of ncol x 4 T float2 per cell padded to an odd length; lane group g reads cells 4 apart,
 // so the 16 values of a read (4 cells, 4 bins) and the 16 cells of a store fall on distinct banks.
