@@ -159,6 +159,17 @@ __device__ __forceinline__ int acc_group(const Axis0Args &a, int t) {
     return a.kgroup0 + (a.kmap ? a.kmap[t / a.nb] : (a.kfirst + t) / a.nb);
 }
 
+// Mode 0: group and kernels [b0, b1) of this workgroup (grid row y: group y / nsplit, share y % nsplit).
+struct GroupShare {
+    int grp, b0, b1;
+    __device__ __forceinline__ explicit GroupShare(int nsplit, int nb) {
+        const int ns = nsplit > 1 ? nsplit : 1, y = (int)blockIdx.y, sh = y % ns;
+        grp = y / ns;
+        b0 = sh * nb / ns;
+        b1 = (sh + 1) * nb / ns;
+    }
+};
+
 template <int N, int TPP, int NT, int... RAD>
 __global__ __launch_bounds__(NT) void axis0_kernel(Axis0Args a) {
     // field of the launch (grid.z); local pointers, so the argument struct is never written
@@ -188,15 +199,16 @@ __global__ __launch_bounds__(NT) void axis0_kernel(Axis0Args a) {
         float2 dr[EPT];
 #pragma unroll
         for (int e = 0; e < EPT; ++e) dr[e] = ok ? dhat0[(int64_t)(q0 + e * TPP) * a.plane + g] : make_float2(0.f, 0.f);
-        const int64_t kbase = (int64_t)(a.kmap ? a.kmap[blockIdx.y] : blockIdx.y) * a.nb;   // kernel group
-        const int kgrp = a.kgroup0 + (int)(a.kmap ? a.kmap[blockIdx.y] : blockIdx.y);       // its global index
-        const int64_t obase = (int64_t)blockIdx.y * a.nb;                                 // output arrays
-        load_kernel(kbase, kgrp, nx);
-        for (int b = 0; b < a.nb; ++b) {
+        const GroupShare sh(a.nsplit, a.nb);
+        const int64_t kbase = (int64_t)(a.kmap ? a.kmap[sh.grp] : sh.grp) * a.nb;   // kernel group
+        const int kgrp = a.kgroup0 + (int)(a.kmap ? a.kmap[sh.grp] : sh.grp);       // its global index
+        const int64_t obase = (int64_t)sh.grp * a.nb;                             // output arrays
+        load_kernel(kbase + sh.b0, kgrp, nx);
+        for (int b = sh.b0; b < sh.b1; ++b) {
             __syncthreads();
 #pragma unroll
             for (int e = 0; e < EPT; ++e) sm[(q0 + e * TPP) * PITCH + p] = nx[e];
-            if (b + 1 < a.nb) load_kernel(kbase + b + 1, kgrp, nx);   // in flight during the transforms
+            if (b + 1 < sh.b1) load_kernel(kbase + b + 1, kgrp, nx);   // in flight during the transforms
             __syncthreads();
             stages<N, TPP, -1, 1, RAD...>(sm, tw, p, q0, PITCH);
 #pragma unroll
@@ -280,20 +292,29 @@ inline int support_rows(const Axis0Args &a, int r1, int r2) {
 // the two stage exchanges (positions R1 q + r written).  One exchange buffer with two barriers
 // per exchange keeps the workgroup at 34 KB of LDS, so four of them share a CU.  Loads and
 // stores take P adjacent pencils of the contiguous axes per row, as in the LDS-staged kernel.
+// 512 = 32 x 16 and 1024 = 32 x 32 take 32 rows a thread: one exchange a transform where three or four
+// shorter stages have two or three, and two 256-thread workgroups a CU (74 KB of LDS, up to 256
+// VGPRs), so that one's loads and stores run during the other's transforms.  With 16 x 8 x 4 stages
+// and two exchange buffers (143 KB, one workgroup a CU) the 512-point pass took 39.4 ms for 13 groups of
+// 6 bins at 512^3, now 27.3 (4.0 TB/s); 8 x 8 x 4 x 4 at 1024 points 962 us for the maps above
+// share_groups, now 447.
 // A compact kernel is nonzero on rows r <= KR and r >= R1 - KR of each thread at most (KR from
 // the support radius, see support_rows; KR >= R1 / 2 for a dense axis): the other rows are
 // compile-time zeros, so they are neither loaded nor held, and the first forward stage folds
 // them away.
 template <int R1, int R2, int P, int MODE, int KR>
-__global__ __launch_bounds__(P * R2, MODE == 0 ? (2 * KR < R1 ? 3 : 2) : 1) void axis0_reg_kernel(Axis0Args a) {
+__global__ __launch_bounds__(P * R2, MODE == 0 ? (R1 < 32 && 2 * KR < R1 ? 3 : 2) : 1) void axis0_reg_kernel(Axis0Args a) {
     // field of the launch (grid.z); local pointers, so the argument struct is never written
     const float2 *dhat0 = a.dhat + (int64_t)blockIdx.z * a.dhat_fs;
     float2 *out0 = a.out + (int64_t)blockIdx.z * a.out_fs;
     constexpr int N = R1 * R2;
     constexpr int T = R1 / R2;   // second-stage butterflies per thread
     static_assert(R1 % R2 == 0, "R2 must divide R1");
-    constexpr int PITCH = P + 1;
-    __shared__ float2 ex[N * PITCH];
+    // LDS position (j, p): a spare slot per row of P pencils, or, below 16 pencils, P spare slots after
+    // every R1 rows: either way neither exchange phase meets bank conflicts
+    constexpr bool WIDE = P >= 16;
+    constexpr int PITCH = WIDE ? P + 1 : P;
+    __shared__ float2 ex[N * PITCH + (WIDE ? 0 : R2 * P)];
     __shared__ float2 twl[N];    // [t][r][q]: second-stage twiddles w^{(q + R2 t) r}, w = e^{-2 pi i / N}
     const int tid = threadIdx.x;
     const int p = tid % P, q = tid / P;
@@ -302,6 +323,12 @@ __global__ __launch_bounds__(P * R2, MODE == 0 ? (2 * KR < R1 ? 3 : 2) : 1) void
     // 32-bit byte offsets within one array (the launcher checks that an array spans less than
     // 4 GiB): element (j, g) of an array is at j * pb + gb
     const uint32_t pb = (uint32_t)a.plane * (uint32_t)sizeof(float2), gb = (uint32_t)g * (uint32_t)sizeof(float2);
+    // element (q + R2 r, g): that offset, or for the long axes (arrays of 4 GiB and more) the uniform
+    // pointer of row R2 r plus the lane's offset
+    auto elem = [&](const float2 *base, int r) {
+        if constexpr (R1 >= 32) return at_bytes(base + (int64_t)(R2 * r) * a.plane, (uint32_t)q * pb + gb);
+        else return at_bytes(base, (uint32_t)(q + R2 * r) * pb + gb);
+    };
     for (int i = tid; i < N; i += P * R2) {
         const int t = i / (R2 * R2), r = i / R2 % R2, qq = i % R2;
         twl[i] = a.tw[((qq + R2 * t) * r) % N];
@@ -345,14 +372,14 @@ __global__ __launch_bounds__(P * R2, MODE == 0 ? (2 * KR < R1 ? 3 : 2) : 1) void
         Dft<R1, SIGN>::run(v);
         __syncthreads();                 // the previous exchange has been read
 #pragma unroll
-        for (int r = 0; r < R1; ++r) buf[(R1 * q + r) * PITCH + p] = v[r];
+        for (int r = 0; r < R1; ++r) buf[(R1 * q + r) * PITCH + p + (WIDE ? 0 : q * P)] = v[r];
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < T; ++t) {
             float2 u[R2];
 #pragma unroll
             for (int r = 0; r < R2; ++r) {
-                const float2 x = buf[(q + R2 * t + R1 * r) * PITCH + p];
+                const float2 x = buf[(q + R2 * t + R1 * r) * PITCH + p + (WIDE ? 0 : r * P)];
                 const float2 tv = twl[(t * R2 + r) * R2 + q];     // the inverse takes the conjugate
                 const float2 w = SIGN < 0 ? tv : make_float2(tv.x, -tv.y);
                 u[r] = r == 0 ? x : cmul(x, w);
@@ -368,7 +395,7 @@ __global__ __launch_bounds__(P * R2, MODE == 0 ? (2 * KR < R1 ? 3 : 2) : 1) void
         auto load_v = [&](int b, float2 *dst) {
             const float2 *vb = a.vin + (int64_t)b * a.ng;
 #pragma unroll
-            for (int r = 0; r < R1; ++r) dst[r] = ok ? *at_bytes(vb, (uint32_t)(q + R2 * r) * pb + gb) : make_float2(0.f, 0.f);
+            for (int r = 0; r < R1; ++r) dst[r] = ok ? *elem(vb, r) : make_float2(0.f, 0.f);
         };
         float2 acc[R1], nv[R1];
 #pragma unroll
@@ -389,7 +416,7 @@ __global__ __launch_bounds__(P * R2, MODE == 0 ? (2 * KR < R1 ? 3 : 2) : 1) void
                 if (ok)
 #pragma unroll
                     for (int r = 0; r < R1; ++r) {
-                        float2 *o = at_bytes(out0, (uint32_t)(q + R2 * r) * pb + gb);
+                        float2 *o = const_cast<float2 *>(elem(out0, r));
                         *o = cadd(*o, acc[r]);
                     }
 #pragma unroll
@@ -400,16 +427,24 @@ __global__ __launch_bounds__(P * R2, MODE == 0 ? (2 * KR < R1 ? 3 : 2) : 1) void
     }
     float2 dr[R1];
 #pragma unroll
-    for (int r = 0; r < R1; ++r) dr[r] = ok ? *at_bytes(dhat0, (uint32_t)(q + R2 * r) * pb + gb) : make_float2(0.f, 0.f);
-    const int64_t kbase = (int64_t)(a.kmap ? a.kmap[blockIdx.y] : blockIdx.y) * a.nb;   // kernel group
-    const int kgrp = a.kgroup0 + (int)(a.kmap ? a.kmap[blockIdx.y] : blockIdx.y);       // its global index
-    const int64_t obase = (int64_t)blockIdx.y * a.nb;                                 // output arrays
-    load_kernel(kbase, kgrp, nx);
-    for (int b = 0; b < a.nb; ++b) {
+    for (int r = 0; r < R1; ++r) dr[r] = ok ? *elem(dhat0, r) : make_float2(0.f, 0.f);
+    const GroupShare sh(a.nsplit, a.nb);
+    const int64_t kbase = (int64_t)(a.kmap ? a.kmap[sh.grp] : sh.grp) * a.nb;   // kernel group
+    const int kgrp = a.kgroup0 + (int)(a.kmap ? a.kmap[sh.grp] : sh.grp);       // its global index
+    const int64_t obase = (int64_t)sh.grp * a.nb;                             // output arrays
+    // the next kernel's rows are in flight during the transforms, except where 32 dense rows a thread
+    // leave no registers for them
+    constexpr bool PF = R1 < 32 || 2 * KR < R1;
+    if constexpr (PF) load_kernel(kbase + sh.b0, kgrp, nx);
+    for (int b = sh.b0; b < sh.b1; ++b) {
         float2 v[R1];
+        if constexpr (PF) {
 #pragma unroll
-        for (int r = 0; r < R1; ++r) v[r] = nx[r];
-        if (b + 1 < a.nb) load_kernel(kbase + b + 1, kgrp, nx);   // in flight during the transforms
+            for (int r = 0; r < R1; ++r) v[r] = nx[r];
+            if (b + 1 < sh.b1) load_kernel(kbase + b + 1, kgrp, nx);
+        } else {
+            load_kernel(kbase + b, kgrp, v);
+        }
         transform(v, ex, std::integral_constant<int, -1>{});
 #pragma unroll
         for (int r = 0; r < R1; ++r) v[r] = cmul(v[r], dr[r]);
@@ -417,7 +452,7 @@ __global__ __launch_bounds__(P * R2, MODE == 0 ? (2 * KR < R1 ? 3 : 2) : 1) void
         float2 *out = out0 + (obase + b) * a.ng;
         if (ok)
 #pragma unroll
-            for (int r = 0; r < R1; ++r) st_stream(at_bytes(out, (uint32_t)(q + R2 * r) * pb + gb), v[r]);
+            for (int r = 0; r < R1; ++r) st_stream(const_cast<float2 *>(elem(out, r)), v[r]);
     }
 }
 
@@ -426,15 +461,14 @@ __global__ __launch_bounds__(P * R2, MODE == 0 ? (2 * KR < R1 ? 3 : 2) : 1) void
 // pencil owns rows q + T s.  P adjacent pencils of the contiguous axes per workgroup.
 // KR as in axis0_reg_kernel: rows r <= KR and r >= R0 - KR of a thread are the only ones the
 // compact kernel support can reach (KR >= R0 / 2: all rows).
-template <int N, int P, int MODE, int KR, bool ONE, int R0, int... REST>
+template <int N, int P, int MODE, int KR, int R0, int... REST>
 __global__ __launch_bounds__(P * (N / R0)) void axis0_rs_kernel(Axis0Args a) {
     // field of the launch (grid.z); local pointers, so the argument struct is never written
     const float2 *dhat0 = a.dhat + (int64_t)blockIdx.z * a.dhat_fs;
     float2 *out0 = a.out + (int64_t)blockIdx.z * a.out_fs;
     constexpr int T = N / R0;
     constexpr int PITCH = P + 1;
-    __shared__ float2 ex[ONE ? 1 : 2][N * PITCH];   // ONE: a single exchange buffer
-    float2 *ex1 = ex[ONE ? 0 : 1];
+    __shared__ float2 ex[N * PITCH];   // one exchange buffer for all stages
     __shared__ float2 tw[N];
     const int tid = threadIdx.x;
     const int p = tid % P, q = tid / P;
@@ -482,10 +516,7 @@ __global__ __launch_bounds__(P * (N / R0)) void axis0_rs_kernel(Axis0Args a) {
     };
     float2 nx[R0];
     if constexpr (MODE == 1) {
-        // adjoint: out += sum_b FFT_0(v_b) FFT_0(kernel b); bin b + 1 loads during bin b.  The
-        // stage buffers alternate, so consecutive transforms need no barrier between them
-        // (odd stage counts: the last stage reads the buffer the next first stage does not write).
-        static_assert(sizeof...(REST) % 2 == 0, "odd number of stages");
+        // adjoint: out += sum_b FFT_0(v_b) FFT_0(kernel b); bin b + 1 loads during bin b
         auto load_v = [&](int b, float2 *dst) {
             const float2 *vb = a.vin + (int64_t)b * a.ng;
 #pragma unroll
@@ -503,10 +534,10 @@ __global__ __launch_bounds__(P * (N / R0)) void axis0_rs_kernel(Axis0Args a) {
 #pragma unroll
             for (int r = 0; r < R0; ++r) { v[r] = nv[r]; k[r] = nx[r]; }
             if (t + 1 < nt) { load_v(t + 1, nv); load_kernel(acc_kernel(a, t + 1), acc_group(a, t + 1), nx); }
-            if constexpr (ONE) __syncthreads();   // the previous transform has read the buffer
-            reg_stages<N, -1, R0, REST...>(v, ex[0], ex1, tw, q, p, PITCH);
-            if constexpr (ONE) __syncthreads();
-            reg_stages<N, -1, R0, REST...>(k, ex[0], ex1, tw, q, p, PITCH);
+            __syncthreads();   // the previous transform has read the buffer
+            reg_stages<N, -1, R0, REST...>(v, ex, ex, tw, q, p, PITCH);
+            __syncthreads();
+            reg_stages<N, -1, R0, REST...>(k, ex, ex, tw, q, p, PITCH);
 #pragma unroll
             for (int r = 0; r < R0; ++r) acc[r] = cadd(acc[r], cmul(v[r], k[r]));
             if (t % a.nb == a.nb - 1) {   // end of a group: out += its sum, as separate launches would
@@ -525,22 +556,23 @@ __global__ __launch_bounds__(P * (N / R0)) void axis0_rs_kernel(Axis0Args a) {
     float2 dr[R0];
 #pragma unroll
     for (int r = 0; r < R0; ++r) dr[r] = ok ? *at_bytes(row(dhat0, r), lane_off) : make_float2(0.f, 0.f);
-    const int64_t kbase = (int64_t)(a.kmap ? a.kmap[blockIdx.y] : blockIdx.y) * a.nb;   // kernel group
-    const int kgrp = a.kgroup0 + (int)(a.kmap ? a.kmap[blockIdx.y] : blockIdx.y);       // its global index
-    const int64_t obase = (int64_t)blockIdx.y * a.nb;                                 // output arrays
-    load_kernel(kbase, kgrp, nx);
+    const GroupShare sh(a.nsplit, a.nb);
+    const int64_t kbase = (int64_t)(a.kmap ? a.kmap[sh.grp] : sh.grp) * a.nb;   // kernel group
+    const int kgrp = a.kgroup0 + (int)(a.kmap ? a.kmap[sh.grp] : sh.grp);       // its global index
+    const int64_t obase = (int64_t)sh.grp * a.nb;                             // output arrays
+    load_kernel(kbase + sh.b0, kgrp, nx);
     __syncthreads();   // twiddle table
-    for (int b = 0; b < a.nb; ++b) {
+    for (int b = sh.b0; b < sh.b1; ++b) {
         float2 v[R0];
 #pragma unroll
         for (int r = 0; r < R0; ++r) v[r] = nx[r];
-        if (b + 1 < a.nb) load_kernel(kbase + b + 1, kgrp, nx);   // in flight during the transforms
-        if constexpr (ONE) __syncthreads();   // the previous transform has read the buffer
-        reg_stages<N, -1, R0, REST...>(v, ex[0], ex1, tw, q, p, PITCH);
+        if (b + 1 < sh.b1) load_kernel(kbase + b + 1, kgrp, nx);   // in flight during the transforms
+        __syncthreads();   // the previous transform has read the buffer
+        reg_stages<N, -1, R0, REST...>(v, ex, ex, tw, q, p, PITCH);
 #pragma unroll
         for (int r = 0; r < R0; ++r) v[r] = cmul(v[r], dr[r]);
-        if constexpr (ONE) __syncthreads();
-        reg_stages<N, 1, R0, REST...>(v, ex[0], ex1, tw, q, p, PITCH);
+        __syncthreads();
+        reg_stages<N, 1, R0, REST...>(v, ex, ex, tw, q, p, PITCH);
         float2 *out = out0 + (obase + b) * a.ng;
         if (ok)
 #pragma unroll
@@ -548,11 +580,27 @@ __global__ __launch_bounds__(P * (N / R0)) void axis0_rs_kernel(Axis0Args a) {
     }
 }
 
+// Launch of `tiles` pencil tiles per group: where that leaves under 2048 workgroups (eight a compute
+// unit), several share a group's kernels (each reads the density spectrum once more, from the caches).
+// Us, one workgroup a group / shared: 256 x 192 map, 16 bins, m <= 5 86 / 23; 1024^2 and 1024 x 512
+// 506 / 447; 512^2, 10 bins, m <= 10 97 / 93; 32^3, 4 bins, lmax 4 20.7 / 16.5.
+Axis0Args share_groups(const Axis0Args &a, int64_t tiles) {
+    constexpr int64_t kTarget = 2048;
+    Axis0Args b = a;
+    const int64_t wgs = tiles * a.groups * (a.fields > 1 ? a.fields : 1);
+    b.nsplit = a.mode == 0 && wgs < kTarget ? (int)std::min<int64_t>(a.nb, (kTarget + wgs - 1) / wgs) : 1;
+    return b;
+}
+dim3 axis0_grid(const Axis0Args &a, int64_t tiles) {
+    return dim3((unsigned)tiles, (unsigned)(a.groups * a.nsplit), (unsigned)(a.fields > 1 ? a.fields : 1));
+}
+
 template <int N, int TPP, int NT, int... RAD>
 hipError_t launch_axis0_t(const Axis0Args &a, hipStream_t s) {
     constexpr int P = NT / TPP;
-    dim3 grid((unsigned)((a.plane + P - 1) / P), (unsigned)a.groups, (unsigned)(a.fields > 1 ? a.fields : 1));
-    hipLaunchKernelGGL((axis0_kernel<N, TPP, NT, RAD...>), grid, dim3(NT), 0, s, a);
+    const int64_t tiles = (a.plane + P - 1) / P;
+    const Axis0Args b = share_groups(a, tiles);
+    hipLaunchKernelGGL((axis0_kernel<N, TPP, NT, RAD...>), axis0_grid(b, tiles), dim3(NT), 0, s, b);
     return hipGetLastError();
 }
 
@@ -930,47 +978,43 @@ hipError_t launch_fft_pass(const FftPass &a, hipStream_t s) {
 }
 
 hipError_t launch_axis0(const Axis0Args &a, hipStream_t s) {
-    if (a.n == 1024 && a.mode == 0) {
-        // 8 x 8 x 4 x 4 in registers, 128 threads per pencil (8 elements each, which leaves room
-        // for the density spectrum), 8 pencils (rows of 64 contiguous bytes) per 1024-thread
-        // workgroup, one exchange buffer (74 KB of LDS)
-        constexpr int P = 8;
-        dim3 grid((unsigned)((a.plane + P - 1) / P), (unsigned)a.groups, (unsigned)(a.fields > 1 ? a.fields : 1));
-        const int kr = support_rows(a, 8, 128);
-        if (kr <= 1) hipLaunchKernelGGL((axis0_rs_kernel<1024, P, 0, 1, true, 8, 8, 4, 4>), grid, dim3(128 * P), 0, s, a);
-        else if (kr <= 2) hipLaunchKernelGGL((axis0_rs_kernel<1024, P, 0, 2, true, 8, 8, 4, 4>), grid, dim3(128 * P), 0, s, a);
-        else hipLaunchKernelGGL((axis0_rs_kernel<1024, P, 0, 8, true, 8, 8, 4, 4>), grid, dim3(128 * P), 0, s, a);
+    if ((a.n == 1024 || a.n == 512) && a.mode == 0) {
+        auto go = [&](auto r2_c, auto p_c) {
+            constexpr int R2 = decltype(r2_c)::value, P = decltype(p_c)::value;
+            const int kr = support_rows(a, 32, R2);
+            const int64_t tiles = (a.plane + P - 1) / P;
+            const Axis0Args b = share_groups(a, tiles);
+            const dim3 grid = axis0_grid(b, tiles);
+            if (kr <= 1) hipLaunchKernelGGL((axis0_reg_kernel<32, R2, P, 0, 1>), grid, dim3(P * R2), 0, s, b);
+            else if (kr <= 2) hipLaunchKernelGGL((axis0_reg_kernel<32, R2, P, 0, 2>), grid, dim3(P * R2), 0, s, b);
+            else if (kr <= 4) hipLaunchKernelGGL((axis0_reg_kernel<32, R2, P, 0, 4>), grid, dim3(P * R2), 0, s, b);
+            else hipLaunchKernelGGL((axis0_reg_kernel<32, R2, P, 0, 32>), grid, dim3(P * R2), 0, s, b);
+        };
+        if (a.n == 512) go(std::integral_constant<int, 16>{}, std::integral_constant<int, 16>{});
+        else go(std::integral_constant<int, 32>{}, std::integral_constant<int, 8>{});
         return hipGetLastError();
     }
-    if ((a.n == 512 && a.mode == 0) || a.n == 192 || a.n == 160 || a.n == 96) {
-        // register-resident stages: 512 = 16 x 8 x 4, 192 = 12 x 4 x 4, 160 = 20 x 4 x 2, 96 = 12 x 4 x 2
-        // (the adjoint accumulation at 512 keeps the LDS-staged kernel: its registers would spill)
+    if (a.n == 192 || a.n == 160 || a.n == 96) {
+        // register-resident stages: 192 = 12 x 4 x 4, 160 = 20 x 4 x 2, 96 = 12 x 4 x 2
         constexpr int P = 16;
-        dim3 grid((unsigned)((a.plane + P - 1) / P), (unsigned)a.groups, (unsigned)(a.fields > 1 ? a.fields : 1));
+        const int64_t tiles = (a.plane + P - 1) / P;
+        const Axis0Args b = share_groups(a, tiles);
+        const dim3 grid = axis0_grid(b, tiles);
         auto go = [&](auto mode_c) {
             constexpr int M = decltype(mode_c)::value;
-            if constexpr (M == 0) {
-                if (a.n == 512) {
-                    const int kr = support_rows(a, 16, 32);
-                    if (kr <= 1) hipLaunchKernelGGL((axis0_rs_kernel<512, P, 0, 1, false, 16, 8, 4>), grid, dim3(32 * P), 0, s, a);
-                    else if (kr <= 2) hipLaunchKernelGGL((axis0_rs_kernel<512, P, 0, 2, false, 16, 8, 4>), grid, dim3(32 * P), 0, s, a);
-                    else hipLaunchKernelGGL((axis0_rs_kernel<512, P, 0, 16, false, 16, 8, 4>), grid, dim3(32 * P), 0, s, a);
-                    return;
-                }
-            }
             // rows of a thread that the compact support can reach: KR = 2 where it allows (r0 below
             // about a tenth of the axis), all rows otherwise.  One exchange buffer (one more barrier
             // per exchange): with two, the LDS (27-54 KB per workgroup) held these lengths to 2-5
             // workgroups per CU, below what their registers allow
             if (a.n == 192) {
-                if (support_rows(a, 12, 16) <= 2) hipLaunchKernelGGL((axis0_rs_kernel<192, P, M, 2, true, 12, 4, 4>), grid, dim3(16 * P), 0, s, a);
-                else hipLaunchKernelGGL((axis0_rs_kernel<192, P, M, 12, true, 12, 4, 4>), grid, dim3(16 * P), 0, s, a);
+                if (support_rows(a, 12, 16) <= 2) hipLaunchKernelGGL((axis0_rs_kernel<192, P, M, 2, 12, 4, 4>), grid, dim3(16 * P), 0, s, b);
+                else hipLaunchKernelGGL((axis0_rs_kernel<192, P, M, 12, 12, 4, 4>), grid, dim3(16 * P), 0, s, b);
             } else if (a.n == 160) {
-                if (support_rows(a, 20, 8) <= 2) hipLaunchKernelGGL((axis0_rs_kernel<160, P, M, 2, true, 20, 4, 2>), grid, dim3(8 * P), 0, s, a);
-                else hipLaunchKernelGGL((axis0_rs_kernel<160, P, M, 20, true, 20, 4, 2>), grid, dim3(8 * P), 0, s, a);
+                if (support_rows(a, 20, 8) <= 2) hipLaunchKernelGGL((axis0_rs_kernel<160, P, M, 2, 20, 4, 2>), grid, dim3(8 * P), 0, s, b);
+                else hipLaunchKernelGGL((axis0_rs_kernel<160, P, M, 20, 20, 4, 2>), grid, dim3(8 * P), 0, s, b);
             } else {
-                if (support_rows(a, 12, 8) <= 2) hipLaunchKernelGGL((axis0_rs_kernel<96, P, M, 2, true, 12, 4, 2>), grid, dim3(8 * P), 0, s, a);
-                else hipLaunchKernelGGL((axis0_rs_kernel<96, P, M, 12, true, 12, 4, 2>), grid, dim3(8 * P), 0, s, a);
+                if (support_rows(a, 12, 8) <= 2) hipLaunchKernelGGL((axis0_rs_kernel<96, P, M, 2, 12, 4, 2>), grid, dim3(8 * P), 0, s, b);
+                else hipLaunchKernelGGL((axis0_rs_kernel<96, P, M, 12, 12, 4, 2>), grid, dim3(8 * P), 0, s, b);
             }
         };
         if (a.mode == 1) go(std::integral_constant<int, 1>{});
@@ -980,21 +1024,23 @@ hipError_t launch_axis0(const Axis0Args &a, hipStream_t s) {
     // the register-resident kernels of 64-256 address an array by 32-bit byte offsets
     if ((a.n == 256 || a.n == 128 || a.n == 64) && a.ng * (int64_t)sizeof(float2) <= (int64_t)UINT32_MAX) {
         constexpr int P = 16;
-        dim3 grid((unsigned)((a.plane + P - 1) / P), (unsigned)a.groups, (unsigned)(a.fields > 1 ? a.fields : 1));
+        const int64_t tiles = (a.plane + P - 1) / P;
+        const Axis0Args b = share_groups(a, tiles);
+        const dim3 grid = axis0_grid(b, tiles);
         auto go = [&](auto mode_c) {
             constexpr int M = decltype(mode_c)::value;
             if (a.n == 256) {
                 const int kr = support_rows(a, 16, 16);
-                if (kr <= 2) hipLaunchKernelGGL((axis0_reg_kernel<16, 16, P, M, 2>), grid, dim3(16 * P), 0, s, a);
-                else if (kr <= 3) hipLaunchKernelGGL((axis0_reg_kernel<16, 16, P, M, 3>), grid, dim3(16 * P), 0, s, a);
-                else hipLaunchKernelGGL((axis0_reg_kernel<16, 16, P, M, 16>), grid, dim3(16 * P), 0, s, a);
+                if (kr <= 2) hipLaunchKernelGGL((axis0_reg_kernel<16, 16, P, M, 2>), grid, dim3(16 * P), 0, s, b);
+                else if (kr <= 3) hipLaunchKernelGGL((axis0_reg_kernel<16, 16, P, M, 3>), grid, dim3(16 * P), 0, s, b);
+                else hipLaunchKernelGGL((axis0_reg_kernel<16, 16, P, M, 16>), grid, dim3(16 * P), 0, s, b);
             } else if (a.n == 128) {
                 const int kr = support_rows(a, 16, 8);
-                if (kr <= 3) hipLaunchKernelGGL((axis0_reg_kernel<16, 8, P, M, 3>), grid, dim3(8 * P), 0, s, a);
-                else if (kr <= 4) hipLaunchKernelGGL((axis0_reg_kernel<16, 8, P, M, 4>), grid, dim3(8 * P), 0, s, a);
-                else hipLaunchKernelGGL((axis0_reg_kernel<16, 8, P, M, 16>), grid, dim3(8 * P), 0, s, a);
+                if (kr <= 3) hipLaunchKernelGGL((axis0_reg_kernel<16, 8, P, M, 3>), grid, dim3(8 * P), 0, s, b);
+                else if (kr <= 4) hipLaunchKernelGGL((axis0_reg_kernel<16, 8, P, M, 4>), grid, dim3(8 * P), 0, s, b);
+                else hipLaunchKernelGGL((axis0_reg_kernel<16, 8, P, M, 16>), grid, dim3(8 * P), 0, s, b);
             } else {
-                hipLaunchKernelGGL((axis0_reg_kernel<8, 8, P, M, 8>), grid, dim3(8 * P), 0, s, a);
+                hipLaunchKernelGGL((axis0_reg_kernel<8, 8, P, M, 8>), grid, dim3(8 * P), 0, s, b);
             }
         };
         if (a.mode == 1) go(std::integral_constant<int, 1>{});

@@ -139,6 +139,33 @@ template <int SIGN> struct Dft<16, SIGN> {
     }
 };
 
+template <int SIGN> struct Dft<32, SIGN> {
+    // Radix-2 split into two 16-point DFTs of the even and odd inputs.
+    __device__ __forceinline__ static void run(float2 *v) {
+        constexpr float c[16] = {1.f, 0.98078528040323044913f, 0.92387953251128675613f, 0.83146961230254523708f,
+                                 0.70710678118654752440f, 0.55557023301960222474f, 0.38268343236508977173f,
+                                 0.19509032201612826785f, 0.f, -0.19509032201612826785f, -0.38268343236508977173f,
+                                 -0.55557023301960222474f, -0.70710678118654752440f, -0.83146961230254523708f,
+                                 -0.92387953251128675613f, -0.98078528040323044913f};   // cos(k pi / 16)
+        float2 e[16], o[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            e[k] = v[2 * k];
+            o[k] = v[2 * k + 1];
+        }
+        Dft<16, SIGN>::run(e);
+        Dft<16, SIGN>::run(o);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            // sin(k pi / 16) = cos((8 - k) pi / 16)
+            const float2 t = k == 0 ? o[0] : k == 8 ? mul_i<SIGN>(o[8])
+                                                    : cmul(o[k], make_float2(c[k], SIGN * c[k < 8 ? 8 - k : k - 8]));
+            v[k] = cadd(e[k], t);
+            v[k + 16] = csub(e[k], t);
+        }
+    }
+};
+
 // e^{SIGN 2 pi i j / N} for the composite radices below (angles in steps of 30 and 18 degrees)
 template <int N, int SIGN>
 __device__ __forceinline__ float2 root_of_unity(int j) {

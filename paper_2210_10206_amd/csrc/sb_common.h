@@ -88,6 +88,8 @@ struct Axis0Args {
     const float2 *vin;    // mode 1: [b][ng] arrays already transformed along the other axes
     int nb;               // kernels per group (mode 0: per grid.y; mode 1: in this launch)
     int groups;           // grid.y (mode 0: kernel groups; mode 1: 1)
+    int nsplit;           // mode 0: workgroups sharing a group's nb kernels (0 counts as 1), set by the
+                          // launch; grid.y is then groups * nsplit
     int kfirst;           // mode 1: index of the first kernel of this launch
     int accgroups;        // mode 1: kernel groups accumulated in turn (0: one), nb arrays of vin
                           // each; group i reads kernels kmap[i] * nb + b (with kmap) or
