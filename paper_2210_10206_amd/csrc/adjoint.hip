@@ -134,7 +134,6 @@ sb_status backward(sb_plan *p, const void *const *delta, const double *grad_zeta
     float *dsum = reinterpret_cast<float *>(p->scratch + p->off_dsum);
     float2 *coef_w = reinterpret_cast<float2 *>(p->scratch + p->off_coef);
     const float2 *coef = coef_w;
-    const float *w = reinterpret_cast<const float *>(p->scratch + p->off_w);
     float *gtab = reinterpret_cast<float *>(p->scratch + p->off_gtab);
     const int nl = p->prob.lmax + 1;
     for (int f = 0; f < p->batch; ++f)
@@ -158,7 +157,8 @@ sb_status backward(sb_plan *p, const void *const *delta, const double *grad_zeta
     for (int f = 0; f < p->batch; ++f) {
         const ShapeGroup &G = p->groups[p->field_group[f]];
         const float2 *khat = reinterpret_cast<const float2 *>(p->persist + G.khat_off);
-        sb_status st = density_spectrum(p, G, delta[f], s);
+        const float *w = nullptr;   // kept arrays: the spectrum is not needed again
+        sb_status st = use_kept ? density_weights(p, G, delta[f], &w, s) : density_spectrum(p, G, delta[f], &w, s);
         if (st != SB_OK) return st;
         const int nt = 256;
         const unsigned nblk = (unsigned)((G.ng + nt - 1) / nt);

@@ -279,6 +279,21 @@ __global__ void gather_kernel(const double *src, const int *ptr, const int *idx,
     out[i] = s;
 }
 
+// block_sum_kernel and gather_kernel in one, a wave per output value: the sums in the same order.
+__global__ __launch_bounds__(64) void sum_gather_kernel(const double *partial, int64_t part_fs, int nblocks, const int *ptr,
+                                                        const int *idx, const double *coef, GatherOut out) {
+    const int i = blockIdx.x, f = blockIdx.y;
+    const double *pf = partial + f * part_fs;
+    double s = 0.0;
+    for (int t = ptr[i]; t < ptr[i + 1]; ++t) {
+        const double *p = pf + (int64_t)idx[t] * nblocks;
+        double v = 0.0;
+        for (int b = threadIdx.x; b < nblocks; b += 64) v += p[b];
+        s += coef[t] * wave_sum(v);
+    }
+    if (threadIdx.x == 0) out.z[f][i] = s;
+}
+
 __global__ void to_f32_kernel(const void *in, int dtype, int64_t n, float *out) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -319,20 +334,19 @@ __global__ __launch_bounds__(256) void density_sum_kernel(const void *in, int dt
     if (threadIdx.x == 0) partial[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// One block: N_gal = sum (delta + 1) from the partials (fixed order), nbar = N_gal / N_g and
-// norm[t] = N_gal prod_i nbar V_{b_i} for every bin tuple t of (npcf - 1) bins; then every value
+// N_gal = sum (delta + 1) from the partials (fixed order; every block sums them again), nbar = N_gal /
+// N_g and norm[t] = N_gal prod_i nbar V_{b_i} for every bin tuple t of (npcf - 1) bins; then every value
 // of the field's result (rows x tuples x parts) is divided by the norm of its tuple.
 __global__ __launch_bounds__(256) void normalize_kernel(const double *partial, int nparts, int64_t ng, NormArgs a,
                                                          double *zeta, int64_t nvals, double *norm_out) {
-    __shared__ double s_ngal;
+    __shared__ double red[4];
     __shared__ double s_norm[kMaxBins * kMaxBins * kMaxBins];
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int i = 0; i < nparts; ++i) s += partial[i];
-        s_ngal = s + (double)ng;
-    }
+    double s = 0.0;
+    for (int i = threadIdx.x; i < nparts; i += 256) s += partial[i];
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
-    const double ngal = s_ngal, nbar = ngal / (double)ng;
+    const double ngal = ((red[0] + red[1]) + (red[2] + red[3])) + (double)ng, nbar = ngal / (double)ng;
     int ntup = 1;
     for (int k = 0; k < a.order; ++k) ntup *= a.nbins;
     for (int t = threadIdx.x; t < ntup; t += blockDim.x) {
@@ -343,10 +357,11 @@ __global__ __launch_bounds__(256) void normalize_kernel(const double *partial, i
             rem /= a.nbins;
         }
         s_norm[t] = v;
-        if (norm_out) norm_out[t] = v;
+        if (norm_out && blockIdx.x == 0) norm_out[t] = v;
     }
     __syncthreads();
-    for (int64_t i = threadIdx.x; i < nvals; i += blockDim.x) zeta[i] /= s_norm[(i / a.parts) % ntup];
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvals; i += (int64_t)gridDim.x * blockDim.x)
+        zeta[i] /= s_norm[(i / a.parts) % ntup];
 }
 
 }  // namespace
@@ -407,10 +422,16 @@ hipError_t launch_proj4_contract(const Proj4Args &a, hipStream_t s) {
     }
 }
 
-hipError_t launch_block_sum(const double *partial, int ngroups, int nblocks, int nvals, double *tot,
-                            hipStream_t s) {
-    const int64_t n = (int64_t)ngroups * nvals;
+hipError_t launch_block_sum(const double *partial, int nf, int rows, int nblocks, double *tot, hipStream_t s) {
+    const int64_t n = (int64_t)nf * rows;
     hipLaunchKernelGGL(block_sum_kernel, dim3((unsigned)n), dim3(64), 0, s, partial, nblocks, tot);
+    return hipGetLastError();
+}
+
+hipError_t launch_sum_gather(const double *partial, int64_t part_fs, int nblocks, const int *ptr, const int *idx,
+                             const double *coef, int nout, const GatherOut &out, int fields, hipStream_t s) {
+    hipLaunchKernelGGL(sum_gather_kernel, dim3((unsigned)nout, (unsigned)fields), dim3(64), 0, s, partial, part_fs, nblocks,
+                       ptr, idx, coef, out);
     return hipGetLastError();
 }
 
@@ -443,7 +464,8 @@ hipError_t launch_normalize(const void *delta, int dtype, int64_t ng, const Norm
     hipLaunchKernelGGL(density_sum_kernel, dim3(nparts), dim3(256), 0, s, delta, dtype, ng, chunk, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(normalize_kernel, dim3(1), dim3(256), 0, s, partial, nparts, ng, a, zeta, nvals, norm_out);
+    const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>((nvals + 255) / 256, 256));
+    hipLaunchKernelGGL(normalize_kernel, dim3(blocks), dim3(256), 0, s, partial, nparts, ng, a, zeta, nvals, norm_out);
     return hipGetLastError();
 }
 

@@ -272,18 +272,24 @@ __device__ __forceinline__ int64_t partial_row(const LastArgs &a, int y, int nv,
     return (int64_t)a.rowmap[2 * y + v / npn] * npn + v % npn;
 }
 
+// A launch covers the packed array groups (grid rows below npk) and the others, or the complex sums
+// (CPLX): the kernels below run the body of the workgroup's mode.
+#define SB_LAST_MODES(BODY, ...)                                              \
+    a.in += (int64_t)blockIdx.z * a.in_fs;   /* field of the launch (grid.z) */ \
+    a.w += (int64_t)blockIdx.z * a.w_fs;                                       \
+    a.partial += (int64_t)blockIdx.z * a.part_fs;                              \
+    if constexpr (CPLX) BODY(PS_COMPLEX)(a, __VA_ARGS__);                      \
+    else if ((int)blockIdx.y < a.npk) BODY(PS_PACKED)(a, __VA_ARGS__);         \
+    else BODY(PS_REAL)(a, __VA_ARGS__);
+
 template <int N, int TPP, int NBT, int R, int MODE, int PREC, int... RAD>
-__global__ __launch_bounds__(NBT * R * TPP) void last_contract_kernel(LastArgs a) {
-    a.in += (int64_t)blockIdx.z * a.in_fs;   // field of the launch (grid.z)
-    a.w += (int64_t)blockIdx.z * a.w_fs;
-    a.partial += (int64_t)blockIdx.z * a.part_fs;
+__device__ __forceinline__ void last_contract_body(const LastArgs &a, float2 *smem) {
     using PS = PairSums<NBT, MODE, PREC>;
     constexpr int P = NBT * R, PITCH = P + 1, NT = P * TPP;
     constexpr int NW = NT / 64;       // waves
     constexpr int NOUT = PS::NOUT;
     constexpr int EPT = N / TPP;      // tile elements loaded per thread
     static_assert(NT % 64 == 0, "whole waves");
-    extern __shared__ float2 smem[];
     const int nb = a.nb;
     float2 *sm = smem;
     float2 *tw = smem + N * PITCH;
@@ -346,6 +352,14 @@ __global__ __launch_bounds__(NBT * R * TPP) void last_contract_kernel(LastArgs a
             PS::block_value(red, NW, nb, v);
 }
 
+template <int N, int TPP, int NBT, int R, bool CPLX, int PREC, int... RAD>
+__global__ __launch_bounds__(NBT * R * TPP) void last_contract_kernel(LastArgs a) {
+    extern __shared__ float2 smem[];
+#define SB_BODY(M) last_contract_body<N, TPP, NBT, R, M, PREC, RAD...>
+    SB_LAST_MODES(SB_BODY, smem)
+#undef SB_BODY
+}
+
 // LDS region of one pencil in the register-resident last pass: it holds the pencil's exchange
 // rows and then its transformed row.  The size is 8 mod 16 float2, so the pair sums' reads of
 // 4 bins (regions) at 8 adjacent cells fall into distinct banks.
@@ -373,11 +387,11 @@ __device__ __forceinline__ void wave_lds_sync() {
 // (regions written, regions read).  The second-stage twiddles come from an LDS table ordered so
 // that the threads of a pencil read adjacent entries, and the pair sums are flushed to float64
 // every FLUSH (8) rows.
+template <int R1, int R2> constexpr int reg_region(bool split) {
+    return pencil_region(R2 * (R1 + 1), split ? R1 * R2 + 8 : R1 * R2);
+}
 template <int R1, int R2, int NBT, int MODE, int PREC>
-__global__ __launch_bounds__(NBT * R2, NBT <= 12 ? 4 : 3) void last_reg_kernel(LastArgs a) {
-    a.in += (int64_t)blockIdx.z * a.in_fs;   // field of the launch (grid.z)
-    a.w += (int64_t)blockIdx.z * a.w_fs;
-    a.partial += (int64_t)blockIdx.z * a.part_fs;
+__device__ __forceinline__ void last_reg_body(const LastArgs &a, float2 *lds, float2 *twl, float *wsm) {
     using PS = PairSums<NBT, MODE, PREC>;
     constexpr int N = R1 * R2;
     constexpr int T = R1 / R2;             // second-stage butterflies per thread
@@ -392,13 +406,11 @@ __global__ __launch_bounds__(NBT * R2, NBT <= 12 ? 4 : 3) void last_reg_kernel(L
     constexpr bool SPLIT = MODE != PS_COMPLEX;
     constexpr int PLANE = N + 8;
     static_assert(N % 64 == 0, "plane offset 8 mod 64");
-    constexpr int REG = pencil_region(R2 * EXR, SPLIT ? PLANE : N);
+    constexpr int REG = reg_region<R1, R2>(SPLIT);
     constexpr int WPT = (N + NT - 1) / NT;
     static_assert(NT % 64 == 0, "whole waves");
     constexpr int FLUSH = NBT * PS::NACC <= 12 ? 8 : 1;   // larger accumulators would not stay in registers
-    __shared__ float2 lds[P * REG];
-    __shared__ float2 twl[N];              // [t][r][q]: w^{(q + R2 t) r}, w = e^{-2 pi i / N}
-    __shared__ float wsm[N];
+    // twl [t][r][q]: w^{(q + R2 t) r}, w = e^{-2 pi i / N}
     const int nb = a.nb;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int q = tid % R2, pp = tid / R2;  // element column, pencil (= bin)
@@ -484,7 +496,7 @@ __global__ __launch_bounds__(NBT * R2, NBT <= 12 ? 4 : 3) void last_reg_kernel(L
     }
     // float64 combine over the waves in wave order (as in last_contract_kernel)
     __syncthreads();
-    static_assert(PS::red_doubles(NW) * sizeof(double) <= sizeof(lds), "block reduction fits");
+    static_assert(PS::red_doubles(NW) * sizeof(double) <= P * REG * sizeof(float2), "block reduction fits");
     double *red = reinterpret_cast<double *>(lds);   // [wave][part][quad pair][4 x 4]
     ps.to_lds(red, wave, lane);
     __syncthreads();
@@ -492,6 +504,16 @@ __global__ __launch_bounds__(NBT * R2, NBT <= 12 ? 4 : 3) void last_reg_kernel(L
     for (int vv = tid; vv < nv; vv += NT)
         a.partial[partial_row(a, blockIdx.y, nv, nv / NOUT, vv) * a.nblocks + blockIdx.x] =
             PS::block_value(red, NW, nb, vv);
+}
+
+template <int R1, int R2, int NBT, bool CPLX, int PREC>
+__global__ __launch_bounds__(NBT * R2, NBT <= 12 ? 4 : 3) void last_reg_kernel(LastArgs a) {
+    __shared__ float2 lds[NBT * reg_region<R1, R2>(!CPLX)];
+    __shared__ float2 twl[R1 * R2];
+    __shared__ float wsm[R1 * R2];
+#define SB_BODY(M) last_reg_body<R1, R2, NBT, M, PREC>
+    SB_LAST_MODES(SB_BODY, lds, twl, wsm)
+#undef SB_BODY
 }
 
 // bins padded to the instantiated tile widths 4, 8, 12, 16 so that NBT * t threads make whole
@@ -502,26 +524,20 @@ constexpr int reg_padded_bins(int nb, int t) {
     return 0;
 }
 
-// Pair-sum mode of a launch.
-inline int pair_mode(const LastArgs &a) { return a.want_imag ? PS_COMPLEX : (a.packed ? PS_PACKED : PS_REAL); }
-
 template <int R1, int R2, int PREC>
 hipError_t launch_last_reg_p(const LastArgs &a, hipStream_t s) {
     dim3 grid((unsigned)a.nblocks, (unsigned)a.groups, (unsigned)(a.fields > 1 ? a.fields : 1));
-    const int mode = pair_mode(a);
     const int nbt = reg_padded_bins(a.nb, R2);
-#define SB_LR(NBT)                                                                                                  \
-    case NBT:                                                                                                        \
-        if constexpr ((NBT * R2) % 64 == 0) {                                                                        \
-            if (mode == PS_COMPLEX)                                                                                  \
-                hipLaunchKernelGGL((last_reg_kernel<R1, R2, NBT, PS_COMPLEX, PREC>), grid, dim3(NBT * R2), 0, s, a); \
-            else if (mode == PS_PACKED)                                                                              \
-                hipLaunchKernelGGL((last_reg_kernel<R1, R2, NBT, PS_PACKED, PREC>), grid, dim3(NBT * R2), 0, s, a);  \
-            else                                                                                                     \
-                hipLaunchKernelGGL((last_reg_kernel<R1, R2, NBT, PS_REAL, PREC>), grid, dim3(NBT * R2), 0, s, a);    \
-            break;                                                                                                   \
-        } else {                                                                                                     \
-            return hipErrorInvalidValue;                                                                             \
+#define SB_LR(NBT)                                                                                               \
+    case NBT:                                                                                                     \
+        if constexpr ((NBT * R2) % 64 == 0) {                                                                     \
+            if (a.want_imag)                                                                                      \
+                hipLaunchKernelGGL((last_reg_kernel<R1, R2, NBT, true, PREC>), grid, dim3(NBT * R2), 0, s, a);    \
+            else                                                                                                  \
+                hipLaunchKernelGGL((last_reg_kernel<R1, R2, NBT, false, PREC>), grid, dim3(NBT * R2), 0, s, a);   \
+            break;                                                                                                \
+        } else {                                                                                                  \
+            return hipErrorInvalidValue;                                                                          \
         }
     switch (nbt) {
         SB_LR(4) SB_LR(8) SB_LR(12) SB_LR(16)
@@ -607,9 +623,9 @@ template <int N> constexpr int row_region(bool split) {
 
 // Waves per SIMD last_rs_kernel is compiled for: as many as its LDS allows without spilling more than
 // a few registers (16 bins with the complex sums hold 80 accumulators).
-constexpr int rs_waves(int n, int nbt, int mode) {
+constexpr int rs_waves(int n, int nbt, bool cplx) {
     if (n >= 1024) return 1;
-    if (nbt > 12) return mode == PS_COMPLEX ? 2 : n == 160 ? 3 : 4;
+    if (nbt > 12) return cplx ? 2 : n == 160 ? 3 : 4;
     return n == 96 || (n == 512 && nbt <= 8) ? 4 : 3;
 }
 
@@ -622,10 +638,7 @@ constexpr int rs_waves(int n, int nbt, int mode) {
 // at seven barriers a row and flushed after each, 33.6 ms per 512^3 field of 6 bins and 13 array
 // groups (2.5 TB/s read), now 21.6 (3.9 TB/s); 1.66 -> 1.43 ms at 192^3, 8 bins, 13 groups.
 template <int N, int NBT, int MODE, int PREC, int R0, int... REST>
-__global__ __launch_bounds__(NBT * (N / R0), rs_waves(N, NBT, MODE)) void last_rs_kernel(LastArgs a) {
-    a.in += (int64_t)blockIdx.z * a.in_fs;   // field of the launch (grid.z)
-    a.w += (int64_t)blockIdx.z * a.w_fs;
-    a.partial += (int64_t)blockIdx.z * a.part_fs;
+__device__ __forceinline__ void last_rs_body(const LastArgs &a, float2 *lds, float2 *tws, float *wsm) {
     using PS = PairSums<NBT, MODE, PREC>;
     constexpr int T = N / R0;
     constexpr int P = NBT;
@@ -639,9 +652,6 @@ __global__ __launch_bounds__(NBT * (N / R0), rs_waves(N, NBT, MODE)) void last_r
     constexpr int WPT = (N + NT - 1) / NT;
     static_assert(NT % 64 == 0 && 64 % T == 0 && sizeof...(REST) >= 1, "whole waves, a pencil in one of them");
     constexpr int FLUSH = NBT * PS::NACC <= 12 ? 8 : 1;   // larger accumulators would not stay in registers
-    extern __shared__ float2 lds[];        // one region per bin (dead pencils have none)
-    __shared__ float2 tws[wave_twiddles<R0, REST...>()];
-    __shared__ float wsm[N];
     const int nb = a.nb;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int q = tid % T, pp = tid / T;        // element column, pencil (= bin)
@@ -731,32 +741,38 @@ __global__ __launch_bounds__(NBT * (N / R0), rs_waves(N, NBT, MODE)) void last_r
             PS::block_value(red, NW, nb, vv);
 }
 
+template <int N, int NBT, bool CPLX, int PREC, int R0, int... REST>
+__global__ __launch_bounds__(NBT * (N / R0), rs_waves(N, NBT, CPLX)) void last_rs_kernel(LastArgs a) {
+    extern __shared__ float2 lds[];        // one region per bin (dead pencils have none)
+    __shared__ float2 tws[wave_twiddles<R0, REST...>()];
+    __shared__ float wsm[N];
+#define SB_BODY(M) last_rs_body<N, NBT, M, PREC, R0, REST...>
+    SB_LAST_MODES(SB_BODY, lds, tws, wsm)
+#undef SB_BODY
+}
+
 template <int N, int PREC, int R0, int... REST>
 hipError_t launch_last_rs_p(const LastArgs &a, hipStream_t s) {
     constexpr int T = N / R0;
     dim3 grid((unsigned)a.nblocks, (unsigned)a.groups, (unsigned)(a.fields > 1 ? a.fields : 1));
-    const int mode = pair_mode(a);
     const int nbt = reg_padded_bins(a.nb, T);
-    auto shm = [&](auto nbt_c, auto mode_c) -> size_t {
-        constexpr int NBT = decltype(nbt_c)::value, MODE = decltype(mode_c)::value;
-        return std::max<size_t>((size_t)a.nb * row_region<N>(MODE != PS_COMPLEX) * sizeof(float2),
-                                (size_t)PairSums<NBT, MODE, PREC>::red_doubles(NBT * T / 64) * sizeof(double));
+    auto shm = [&](auto nbt_c) -> size_t {
+        constexpr int NW = decltype(nbt_c)::value * T / 64;
+        constexpr int red = std::max(PairSums<decltype(nbt_c)::value, PS_PACKED, PREC>::red_doubles(NW),
+                                     PairSums<decltype(nbt_c)::value, PS_COMPLEX, PREC>::red_doubles(NW));
+        return std::max<size_t>((size_t)a.nb * row_region<N>(!a.want_imag) * sizeof(float2), red * sizeof(double));
     };
-#define SB_LR(NBT)                                                                                                   \
-    case NBT:                                                                                                         \
-        if constexpr ((NBT * T) % 64 == 0 && NBT * T <= 1024) {                                                       \
-            if (mode == PS_COMPLEX)                                                                                   \
-                hipLaunchKernelGGL((last_rs_kernel<N, NBT, PS_COMPLEX, PREC, R0, REST...>), grid, dim3(NBT * T),                   \
-                                   shm(std::integral_constant<int, NBT>{}, std::integral_constant<int, PS_COMPLEX>{}), s, a); \
-            else if (mode == PS_PACKED)                                                                               \
-                hipLaunchKernelGGL((last_rs_kernel<N, NBT, PS_PACKED, PREC, R0, REST...>), grid, dim3(NBT * T),                   \
-                                   shm(std::integral_constant<int, NBT>{}, std::integral_constant<int, PS_PACKED>{}), s, a); \
-            else                                                                                                      \
-                hipLaunchKernelGGL((last_rs_kernel<N, NBT, PS_REAL, PREC, R0, REST...>), grid, dim3(NBT * T),                   \
-                                   shm(std::integral_constant<int, NBT>{}, std::integral_constant<int, PS_REAL>{}), s, a); \
-            break;                                                                                                    \
-        } else {                                                                                                      \
-            return hipErrorInvalidValue;                                                                              \
+#define SB_LR(NBT)                                                                                                \
+    case NBT:                                                                                                      \
+        if constexpr ((NBT * T) % 64 == 0 && (PREC == 0 || NBT * T < 1024)) {                                                    \
+            const size_t lds = shm(std::integral_constant<int, NBT>{});                                            \
+            if (a.want_imag)                                                                                       \
+                hipLaunchKernelGGL((last_rs_kernel<N, NBT, true, PREC, R0, REST...>), grid, dim3(NBT * T), lds, s, a);  \
+            else                                                                                                   \
+                hipLaunchKernelGGL((last_rs_kernel<N, NBT, false, PREC, R0, REST...>), grid, dim3(NBT * T), lds, s, a); \
+            break;                                                                                                 \
+        } else {                                                                                                   \
+            return hipErrorInvalidValue;                                                                           \
         }
     switch (nbt) {
         SB_LR(4) SB_LR(8) SB_LR(12) SB_LR(16)
@@ -772,19 +788,19 @@ hipError_t launch_last_rs(const LastArgs &a, hipStream_t s) {
     return a.prec ? launch_last_rs_p<N, 1, R0, REST...>(a, s) : launch_last_rs_p<N, 0, R0, REST...>(a, s);
 }
 
-template <int N, int TPP, int NBT, int MODE, int... RAD>
+template <int N, int TPP, int NBT, bool CPLX, int... RAD>
 hipError_t launch_last_t(const LastArgs &a, hipStream_t s) {
     constexpr int R = fused_rows(N, TPP, NBT);
     constexpr int P = NBT * R, NT = P * TPP;
     if (a.rows != R) return hipErrorInvalidValue;
     const size_t tile = (size_t)(N * (P + 1) + N) * sizeof(float2) + (size_t)R * N * sizeof(float);
-    const size_t red = (size_t)PairSums<NBT, MODE>::red_doubles(NT / 64) * sizeof(double);
+    const size_t red = (size_t)PairSums<NBT, CPLX ? PS_COMPLEX : PS_PACKED>::red_doubles(NT / 64) * sizeof(double);
     const size_t shm = tile > red ? tile : red;
     dim3 grid((unsigned)a.nblocks, (unsigned)a.groups, (unsigned)(a.fields > 1 ? a.fields : 1));
     if (a.prec)
-        hipLaunchKernelGGL((last_contract_kernel<N, TPP, NBT, R, MODE, 1, RAD...>), grid, dim3(NT), shm, s, a);
+        hipLaunchKernelGGL((last_contract_kernel<N, TPP, NBT, R, CPLX, 1, RAD...>), grid, dim3(NT), shm, s, a);
     else
-        hipLaunchKernelGGL((last_contract_kernel<N, TPP, NBT, R, MODE, 0, RAD...>), grid, dim3(NT), shm, s, a);
+        hipLaunchKernelGGL((last_contract_kernel<N, TPP, NBT, R, CPLX, 0, RAD...>), grid, dim3(NT), shm, s, a);
     return hipGetLastError();
 }
 
@@ -792,11 +808,7 @@ constexpr int padded_bins(int nb) { return nb <= 4 ? 4 : nb <= 8 ? 8 : nb <= 10 
 
 template <int N, int TPP, int NBT, int... RAD>
 hipError_t launch_last_m(const LastArgs &a, hipStream_t s) {
-    switch (pair_mode(a)) {
-        case PS_COMPLEX: return launch_last_t<N, TPP, NBT, PS_COMPLEX, RAD...>(a, s);
-        case PS_PACKED: return launch_last_t<N, TPP, NBT, PS_PACKED, RAD...>(a, s);
-        default: return launch_last_t<N, TPP, NBT, PS_REAL, RAD...>(a, s);
-    }
+    return a.want_imag ? launch_last_t<N, TPP, NBT, true, RAD...>(a, s) : launch_last_t<N, TPP, NBT, false, RAD...>(a, s);
 }
 
 template <int N, int TPP, int... RAD>

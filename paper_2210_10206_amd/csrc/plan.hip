@@ -571,6 +571,7 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
     std::vector<double> gcoef;
     build_gather(p, gptr, gidx, gcoef);
     p->gather_nout = (int)gptr.size() - 1;
+    p->gather_terms = (int)gidx.size();
     p->off_gptr = put(gptr.data(), gptr.size() * sizeof(int));
     p->off_gidx = put(gidx.data(), gidx.size() * sizeof(int));
     p->off_gcoef = put(gcoef.data(), gcoef.size() * sizeof(double));
@@ -617,7 +618,8 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
         bool ok = true;
         if (prob->npcf == 3) {
             ok = p->fused;
-            for (const auto &G : p->groups) ok &= G.rows > 0;
+            // (no split form of the 1024-point rows of more than 12 bins)
+            for (const auto &G : p->groups) ok &= G.rows > 0 && (NB <= 12 || G.n[prob->ndim - 1] < 1024);
         } else if (prob->ndim == 3) {
             ok = p->quad_mfma;
         } else {
@@ -765,20 +767,64 @@ static sb_status axis0_corr(sb_plan *p, const ShapeGroup &G, const float2 *dhat,
     return SB_OK;
 }
 
-// Density ingest and spectrum (the first step of Alg. 3 / Alg. 4) of nf fields of shape G:
-// field i's density at w + i ng, its spectrum at dhat + i ng.
-sb_status density_spectrum(sb_plan *p, const ShapeGroup &G, const void *const *deltas, int nf, hipStream_t s) {
-    float *w = reinterpret_cast<float *>(p->scratch + p->off_w);
-    float2 *dhat = reinterpret_cast<float2 *>(p->scratch + p->off_dhat);
+// The float32 densities of nf fields of shape G, field i's at (returned) w + i ng: one float32 field
+// is read where the caller has it, several or float64 ones are copied to the scratch.
+static sb_status density_weights(sb_plan *p, const ShapeGroup &G, const void *const *deltas, int nf, const float **w,
+                                 hipStream_t s) {
+    if (nf == 1 && p->prob.input_dtype == SB_IN_F32) {
+        *w = static_cast<const float *>(deltas[0]);
+        return SB_OK;
+    }
+    float *copy = reinterpret_cast<float *>(p->scratch + p->off_w);
     for (int i = 0; i < nf; ++i) {
-        const hipError_t e = launch_to_f32(deltas[i], p->prob.input_dtype, G.ng, w + (int64_t)i * G.ng, s);
+        const hipError_t e = launch_to_f32(deltas[i], p->prob.input_dtype, G.ng, copy + (int64_t)i * G.ng, s);
         if (e != hipSuccess) return hip_fail(e, "density ingest");
     }
-    return fft_all_axes(p, G, -1, LOAD_R32, w, G.ng, dhat, G.ng, nf, s);
+    *w = copy;
+    return SB_OK;
 }
 
-sb_status density_spectrum(sb_plan *p, const ShapeGroup &G, const void *delta, hipStream_t s) {
-    return density_spectrum(p, G, &delta, 1, s);
+sb_status density_weights(sb_plan *p, const ShapeGroup &G, const void *delta, const float **w, hipStream_t s) {
+    return density_weights(p, G, &delta, 1, w, s);
+}
+
+// Density ingest and spectrum (the first step of Alg. 3 / Alg. 4) of nf fields of shape G:
+// field i's density at w + i ng, its spectrum at dhat + i ng.
+static sb_status density_spectrum(sb_plan *p, const ShapeGroup &G, const void *const *deltas, int nf, const float **w,
+                                  hipStream_t s) {
+    float2 *dhat = reinterpret_cast<float2 *>(p->scratch + p->off_dhat);
+    if (sb_status st = density_weights(p, G, deltas, nf, w, s); st != SB_OK) return st;
+    return fft_all_axes(p, G, -1, LOAD_R32, *w, G.ng, dhat, G.ng, nf, s);
+}
+
+sb_status density_spectrum(sb_plan *p, const ShapeGroup &G, const void *delta, const float **w, hipStream_t s) {
+    return density_spectrum(p, G, &delta, 1, w, s);
+}
+
+// Block partials -> FP64 sums -> result layout of nf fields (field i's partials at part + i part_fs,
+// its result at zout[i]): one launch where every block partial an output needs is quickly read
+// again for each of them, else the sums first and then the gather.
+static sb_status reduce_gather(sb_plan *p, const double *part, int64_t part_fs, int rows, int nblocks, double *const *zout,
+                               int nf, hipStream_t s) {
+    hipError_t e = hipSuccess;
+    // reads of the one launch, in partials (256^3, 10 bins, lmax 6: 2.9 M)
+    constexpr int64_t kDirect = 1 << 20;
+    if ((int64_t)p->gather_terms * nblocks <= kDirect) {
+        for (int i = 0; i < nf && e == hipSuccess; i += kGatherFields) {
+            GatherOut out{};
+            const int n = std::min(kGatherFields, nf - i);
+            for (int j = 0; j < n; ++j) out.z[j] = zout[i + j];
+            e = launch_sum_gather(part + i * part_fs, part_fs, nblocks, p->d_gptr, p->d_gidx, p->d_gcoef, p->gather_nout, out,
+                                  n, s);
+        }
+        return e == hipSuccess ? SB_OK : hip_fail(e, "reduction");
+    }
+    double *tot = reinterpret_cast<double *>(p->scratch + p->off_tot);
+    e = launch_block_sum(part, nf, rows, nblocks, tot, s);
+    if (e != hipSuccess) return hip_fail(e, "block sum");
+    for (int i = 0; i < nf && e == hipSuccess; ++i)
+        e = launch_gather(tot + (int64_t)i * rows, p->d_gptr, p->d_gidx, p->d_gcoef, p->gather_nout, zout[i], s);
+    return e == hipSuccess ? SB_OK : hip_fail(e, "gather");
 }
 
 // Coefficients of kernel groups [g0, g0 + ngr) of one field into scratch (Alg. 3 / Alg. 4
@@ -812,18 +858,13 @@ static sb_status fused_3pcf(sb_plan *p, const ShapeGroup &G, const void *const *
     const int nd = p->prob.ndim, NB = p->prob.nbins;
     float2 *dhat = reinterpret_cast<float2 *>(p->scratch + p->off_dhat);
     float2 *coef = reinterpret_cast<float2 *>(p->scratch + p->off_coef + coef_off);
-    const float *w = reinterpret_cast<const float *>(p->scratch + p->off_w);
+    const float *w = nullptr;
     double *part = reinterpret_cast<double *>(p->scratch + p->off_part);
-    double *tot = reinterpret_cast<double *>(p->scratch + p->off_tot);
     if (nf > 1 && p->chunk_groups < p->nlm) return fail(SB_EUNSUPPORTED, "fields batched with chunked kernel groups");
-    sb_status st = density_spectrum(p, G, deltas, nf, s);
+    sb_status st = density_spectrum(p, G, deltas, nf, &w, s);
     if (st != SB_OK) return st;
-    // bin counts without a fused last pass (more than 12 bins on a 1024-point last axis) run the
-    // plain last pass and the pair contraction
-    const bool fused_last = G.rows > 0;
     const int64_t nrows = G.ng / G.n[nd - 1];
-    const int nblocks = fused_last ? (int)((nrows + G.rows_per_block - 1) / G.rows_per_block)
-                                   : (int)((G.ng + p->cpb_pair - 1) / p->cpb_pair);
+    const int nblocks = (int)((nrows + G.rows_per_block - 1) / G.rows_per_block);
     const int nv = NB * (NB + 1) / 2 * (nd == 2 ? 2 : 1);
     const int64_t part_fs = (int64_t)p->nlm * nv * nblocks;   // one field's block partials
     hipError_t e = hipSuccess;
@@ -844,85 +885,44 @@ static sb_status fused_3pcf(sb_plan *p, const ShapeGroup &G, const void *const *
             st = fft_axes(p, G.n, nd, G.ng, axes, 1, +1, LOAD_C, coef, G.ng, coef, G.ng, nf * ngr * NB, s);
             if (st != SB_OK) return st;
         }
-        if (!fused_last) {
-            const int axes[1] = {nd - 1};
-            st = fft_axes(p, G.n, nd, G.ng, axes, 1, +1, LOAD_C, coef, G.ng, coef, G.ng, nf * ngr * NB, s);
-            if (st != SB_OK) return st;
-            PairArgs a{};
-            a.coef = coef;
-            a.gstride = (int64_t)NB * G.ng;
-            a.w = w;
-            a.ng = G.ng;
-            a.nbins = NB;
-            a.ngroups = ngr;
-            a.cells_per_block = p->cpb_pair;
-            a.want_imag = nd == 2;
-            a.partial = part + (int64_t)g0 * nv * nblocks;
-            a.nblocks = nblocks;
-            a.fields = nf;
-            a.coef_fs = (int64_t)ngr * NB * G.ng;
-            a.w_fs = G.ng;
-            a.part_fs = part_fs;
-            const double fl = (double)nf * G.ng * ngr * (2.0 + NB * (NB + 1) / 2.0 * (nd == 2 ? 8.0 : 4.0));
-            const double by = (double)nf * G.ng * (8.0 * ngr * NB + 4.0);
-            e = p->timed_launch(STAGE_CONTRACT, K_PAIR, s, [&]() { return launch_pair_contract(a, s); }, 0, 0, ngr,
-                                by, fl);
-            if (e != hipSuccess) return hip_fail(e, "pair contraction");
-            continue;
-        }
-        // last pass over array groups [gs, gs + cnt) of this chunk (all packed or none)
-        auto last = [&](int gs, int cnt, bool packed) -> hipError_t {
+        // last pass over the chunk's array groups, the packed ones first
+        {
             LastArgs a{};
             a.n = (int)G.n[nd - 1];
             a.ng = G.ng;
-            a.in = coef + (int64_t)(gs - g0) * NB * G.ng;
+            a.in = coef;
             a.w = w;
             a.nb = NB;
-            a.groups = cnt;
+            a.groups = ngr;
             a.rows = G.rows;
             a.rows_per_block = G.rows_per_block;
             a.nblocks = nblocks;
             a.want_imag = nd == 2;
-            a.packed = packed;
+            a.npk = packing ? std::max(0, std::min(g0 + ngr, p->npack) - g0) : 0;
             a.prec = p->prob.precision == SB_PREC_SPLIT_BF16 ? 1 : 0;
             // with packing the row map places each part's partials at its (l, m) row
-            a.rowmap = packing ? p->d_rowmap + 2 * gs : nullptr;
-            a.partial = packing ? part : part + (int64_t)gs * nv * nblocks;
+            a.rowmap = packing ? p->d_rowmap + 2 * g0 : nullptr;
+            a.partial = packing ? part : part + (int64_t)g0 * nv * nblocks;
             a.tw = p->tw.at(a.n);
             a.fields = nf;
             a.in_fs = (int64_t)ngr * NB * G.ng;
             a.w_fs = G.ng;
             a.part_fs = part_fs;
-            const double bytes = nf * ((double)cnt * NB * 8.0 * G.ng + (double)cnt * 4.0 * G.ng);
-            const double flops = (double)nf * G.ng * cnt * (2.0 * NB + NB * (NB + 1) / 2.0 * (nd == 2 ? 8.0 : 4.0));
-            return p->timed_launch(STAGE_CONTRACT, K_LAST, s, [&]() { return launch_last_contract(a, s); }, a.n, 1,
-                                   nf * cnt * NB, bytes, flops);
-        };
-        if (packing) {
-            const int pe = std::min(g0 + ngr, p->npack);
-            if (pe > g0) e = last(g0, pe - g0, true);
-            const int us = std::max(g0, p->npack);
-            if (e == hipSuccess && g0 + ngr > us) e = last(us, g0 + ngr - us, false);
-        } else {
-            e = last(g0, ngr, false);
+            const double bytes = nf * ((double)ngr * NB * 8.0 * G.ng + (double)ngr * 4.0 * G.ng);
+            const double flops = (double)nf * G.ng * ngr * (2.0 * NB + NB * (NB + 1) / 2.0 * (nd == 2 ? 8.0 : 4.0));
+            e = p->timed_launch(STAGE_CONTRACT, K_LAST, s, [&]() { return launch_last_contract(a, s); }, a.n, 1,
+                                nf * ngr * NB, bytes, flops);
         }
         if (e != hipSuccess) return hip_fail(e, "fused last pass");
     }
-    e = launch_block_sum(part, nf * p->nlm, nblocks, nv, tot, s);
-    if (e != hipSuccess) return hip_fail(e, "block sum");
-    for (int i = 0; i < nf && e == hipSuccess; ++i)
-        e = launch_gather(tot + (int64_t)i * p->nlm * nv, p->d_gptr, p->d_gidx, p->d_gcoef, p->gather_nout, zout[i], s);
-    if (e != hipSuccess) return hip_fail(e, "gather");
-    return SB_OK;
+    return reduce_gather(p, part, part_fs, p->nlm * nv, nblocks, zout, nf, s);
 }
 
 // Cell-parallel contraction of nf fields of shape G whose coefficient arrays are in scratch (field
-// i after the previous field's arrays); field i's result goes to zout[i].
-sb_status contract(sb_plan *p, const ShapeGroup &G, double *const *zout, int nf, hipStream_t s) {
-    const float *w = reinterpret_cast<const float *>(p->scratch + p->off_w);
+// i after the previous field's arrays), their densities at w + i ng; field i's result goes to zout[i].
+sb_status contract(sb_plan *p, const ShapeGroup &G, const float *w, double *const *zout, int nf, hipStream_t s) {
     const float2 *coef = reinterpret_cast<const float2 *>(p->scratch + p->off_coef);
     double *part = reinterpret_cast<double *>(p->scratch + p->off_part);
-    double *tot = reinterpret_cast<double *>(p->scratch + p->off_tot);
     int groups = 0, nvals = 0, nblocks = 0;
     contraction_shape(p, G.ng, &groups, &nvals, &nblocks);
     hipError_t e = hipSuccess;
@@ -1079,12 +1079,7 @@ sb_status contract(sb_plan *p, const ShapeGroup &G, double *const *zout, int nf,
         e = p->timed_launch(STAGE_CONTRACT, K_PROJ4, s, [&]() { return launch_proj4_contract(a, s); }, 0, 0, groups, by, fl);
     }
     if (e != hipSuccess) return hip_fail(e, "contraction");
-    e = launch_block_sum(part, nf * groups, nblocks, nvals, tot, s);
-    if (e != hipSuccess) return hip_fail(e, "block sum");
-    for (int i = 0; i < nf && e == hipSuccess; ++i)
-        e = launch_gather(tot + (int64_t)i * groups * nvals, p->d_gptr, p->d_gidx, p->d_gcoef, p->gather_nout, zout[i], s);
-    if (e != hipSuccess) return hip_fail(e, "gather");
-    return SB_OK;
+    return reduce_gather(p, part, part_fs, groups * nvals, nblocks, zout, nf, s);
 }
 
 sb_status check_finite(sb_plan *p, int count, const void *const *in, const int64_t *n, const int *dtype,
@@ -1142,11 +1137,12 @@ sb_status forward(sb_plan *p, const void *const *delta, double *zeta, hipStream_
             return fail(SB_EUNSUPPORTED, "this path needs every kernel array at once; raise the scratch limit");
         if (p->prob.npcf == 3 && p->fused)
             return fused_3pcf(p, G, dl.data(), zo.data(), nf, p->keep ? p->keep_off[fidx[0]] : 0, s);
-        sb_status st = density_spectrum(p, G, dl.data(), nf, s);
+        const float *w = nullptr;
+        sb_status st = density_spectrum(p, G, dl.data(), nf, &w, s);
         if (st == SB_OK)   // array groups (packed m = 0 pairs first) where the plan packs
             st = p->npack > 0 ? coefficients(p, fidx[0], 0, p->nag, s, true, p->d_kmap, nf)
                               : coefficients(p, fidx[0], 0, p->nlm, s, true, nullptr, nf);
-        if (st == SB_OK) st = contract(p, G, zo.data(), nf, s);
+        if (st == SB_OK) st = contract(p, G, w, zo.data(), nf, s);
         return st;
     };
     if (p->fbatch <= 1) {

@@ -126,8 +126,9 @@ struct LastArgs {
     int64_t rows_per_block;
     int nblocks;
     int want_imag;
-    int packed;           // each array carries two real coefficient fields (real and imaginary
-                          // part): their pair sums are kept apart (value = part * npairs + pair)
+    int npk;              // the first npk groups are packed: each array carries two real coefficient
+                          // fields (real and imaginary part), their pair sums kept apart
+                          // (value = part * npairs + pair)
     double *partial;      // [row][block]; row = group * nvalues + value, value = b1 <= b2 pair
                           // (then imaginary parts or the second packed field)
     const int *rowmap;    // optional: 2 per grid row, the group row of part 0 and part 1

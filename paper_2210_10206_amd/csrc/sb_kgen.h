@@ -148,12 +148,19 @@ hipError_t launch_proj4_contract(const Proj4Args &a, hipStream_t s);
 hipError_t launch_proj4_mfma(const Proj4Args &a, hipStream_t s);
 
 // ---- deterministic FP64 reduction of block partials: tot[g][v] = sum_blk partial[g][blk][v]
-hipError_t launch_block_sum(const double *partial, int ngroups, int nblocks, int nvals, double *tot,
-                            hipStream_t s);
+hipError_t launch_block_sum(const double *partial, int nf, int rows, int nblocks, double *tot, hipStream_t s);
 
 // ---- gather map: out[i] = sum_{t in ptr[i]..ptr[i+1]} coef[t] * src[idx[t]]
 hipError_t launch_gather(const double *src, const int *ptr, const int *idx, const double *coef,
                          int nout, double *out, hipStream_t s);
+
+// ---- both at once for up to kGatherFields fields: field f's partials at partial + f part_fs, out to z[f]
+constexpr int kGatherFields = 16;
+struct GatherOut {
+    double *z[kGatherFields];
+};
+hipError_t launch_sum_gather(const double *partial, int64_t part_fs, int nblocks, const int *ptr, const int *idx,
+                             const double *coef, int nout, const GatherOut &out, int fields, hipStream_t s);
 
 // ---- density ingest: float32 copy of the field (and float64 -> float32 cast)
 hipError_t launch_to_f32(const void *in, int dtype, int64_t n, float *out, hipStream_t s);

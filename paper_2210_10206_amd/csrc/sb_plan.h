@@ -86,7 +86,7 @@ struct sb_plan {
     const double *d_gcoef = nullptr;
     const sb::QuadGTerm *d_gterms = nullptr;
     const int *d_gtptr = nullptr, *d_glam = nullptr;
-    int gather_nout = 0;
+    int gather_nout = 0, gather_terms = 0;
     int max_cols = 0;
     // workspace (caller-owned)
     char *persist = nullptr, *scratch = nullptr;
@@ -132,13 +132,8 @@ struct sb_plan {
         else if (prob.ndim == 3) { *lo = 512; *hi = 4096; }
         else { *lo = 1024; *hi = 8192; }
     }
-    // a forward call runs the cell-parallel contraction on some field
-    bool uses_contract() const {
-        if (prob.npcf == 4 || !fused) return true;
-        for (const auto &G : groups)
-            if (G.rows <= 0) return true;
-        return false;
-    }
+    // a forward call runs the cell-parallel contraction
+    bool uses_contract() const { return prob.npcf == 4 || !fused; }
     const float *d_coefw = nullptr;   // weighted 3j values, every term, per canonical Lambda
     std::vector<int> coefw_off;
     bool quad_mfma = false;       // every canonical Lambda has a compile-time matrix-core kernel (l <= 4, <= 8 bins)
@@ -217,7 +212,10 @@ namespace sb {
 sb_status fail(sb_status s, const std::string &msg);
 sb_status hip_fail(hipError_t e, const char *what);
 sb_status forward(sb_plan *p, const void *const *delta, double *zeta, hipStream_t s);
-sb_status density_spectrum(sb_plan *p, const sb::ShapeGroup &G, const void *delta, hipStream_t s);
+// Spectrum of one field into scratch and (both) its float32 density: *w is the field itself where it is
+// float32, else a copy in scratch.
+sb_status density_spectrum(sb_plan *p, const sb::ShapeGroup &G, const void *delta, const float **w, hipStream_t s);
+sb_status density_weights(sb_plan *p, const sb::ShapeGroup &G, const void *delta, const float **w, hipStream_t s);
 // Coefficients of kernel groups [g0, g0 + ng) of field f into scratch (group g0 first); the
 // density spectrum must be in scratch already.  last_axis = false stops before the inverse
 // transform along the last axis.  kmap (device, optional): the kernel group of each of the ng
@@ -225,7 +223,7 @@ sb_status density_spectrum(sb_plan *p, const sb::ShapeGroup &G, const void *delt
 sb_status coefficients(sb_plan *p, int f, int g0, int ngroups, hipStream_t s, bool last_axis = true,
                        const int *kmap = nullptr, int nf = 1);
 void layout_scratch(sb_plan *p);
-sb_status contract(sb_plan *p, const ShapeGroup &G, double *const *zout, int nf, hipStream_t s);
+sb_status contract(sb_plan *p, const ShapeGroup &G, const float *w, double *const *zout, int nf, hipStream_t s);
 // Half kernel store (plan.hip): whether a shape keeps only the planes c_0 = 0 .. r0, the planes
 // stored per kernel, and the half-store fields of an axis-0 launch.
 bool half_store(const ShapeGroup &G, int ndim, int64_t r0, bool want);
