@@ -6,6 +6,7 @@ in the HIP library.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 
 import numpy as np
@@ -18,6 +19,11 @@ from ._lib import SbProblem, check
 def _stream_ptr(stream=None):
     s = stream if stream is not None else torch.cuda.current_stream()
     return ctypes.c_void_p(s.cuda_stream)
+
+
+def _on_device(device):
+    """The device made current; nothing to switch where it is (the usual case of one GPU a process)."""
+    return contextlib.nullcontext() if torch.cuda.current_device() == device.index else torch.cuda.device(device)
 
 
 def _aligned_buffer(nbytes: int, device) -> torch.Tensor:
@@ -95,7 +101,7 @@ class Plan:
         sh = np.ascontiguousarray(np.array(shapes, dtype=np.int64).ravel())
         self._shapes_arr = sh
         handle = ctypes.c_void_p()
-        with torch.cuda.device(self.device):
+        with _on_device(self.device):
             check(self.lib.sb_plan_create(ctypes.byref(self._prob), len(shapes),
                                           sh.ctypes.data_as(ctypes.POINTER(ctypes.c_int64)), ctypes.byref(handle)),
                   "sb_plan_create")
@@ -118,6 +124,7 @@ class Plan:
         n = ctypes.c_int64()
         check(self.lib.sb_zeta_size(self.handle, ctypes.byref(n)), "sb_zeta_size")
         self.zeta_doubles = n.value
+        self._index = self._read_index()
         self.prepared = False
         if prepare:
             self.prepare(stream)
@@ -136,7 +143,7 @@ class Plan:
             pass
 
     def prepare(self, stream=None):
-        with torch.cuda.device(self.device):
+        with _on_device(self.device):
             check(self.lib.sb_prepare(self.handle, _stream_ptr(stream)), "sb_prepare")
         self.prepared = True
 
@@ -144,17 +151,19 @@ class Plan:
         """Time the launch shapes (sb_autotune); cache_path: JSON file of tuned choices, read
         when it holds this plan's entry, extended otherwise."""
         path = None if cache_path is None else str(cache_path).encode()
-        with torch.cuda.device(self.device):
+        with _on_device(self.device):
             check(self.lib.sb_autotune(self.handle, _stream_ptr(stream), path), "sb_autotune")
 
     # ------------------------------------------------------------------ layout
-    def zeta_index(self):
+    def _read_index(self):
         rows, cols = ctypes.c_int32(), ctypes.c_int32()
         tab = ctypes.POINTER(ctypes.c_int32)()
         check(self.lib.sb_zeta_index(self.handle, ctypes.byref(rows), ctypes.byref(cols), ctypes.byref(tab)),
               "sb_zeta_index")
-        arr = np.array([tab[i] for i in range(rows.value * cols.value)], dtype=np.int32)
-        return arr.reshape(rows.value, cols.value)
+        return np.ctypeslib.as_array(tab, shape=(rows.value, cols.value)).copy()
+
+    def zeta_index(self):
+        return self._index.copy()   # fixed when the plan is created
 
     def bin_counts(self, field: int = 0):
         out = np.zeros(self.nbins, dtype=np.int64)
@@ -170,7 +179,7 @@ class Plan:
         return bits.value
 
     def zeta_shape(self):
-        rows = self.zeta_index().shape[0]
+        rows = self._index.shape[0]
         nb = self.nbins
         tail = (nb, nb) if self.npcf == 3 else (nb, nb, nb)
         return (rows,) + tail
@@ -196,7 +205,7 @@ class Plan:
             out = torch.empty((len(deltas), self.zeta_doubles), dtype=torch.float64, device=self.device)
         ptrs = self._ptrs(deltas)
         fn = self.lib.sb_forward_graph if graph else self.lib.sb_forward
-        with torch.cuda.device(self.device):
+        with _on_device(self.device):
             check(fn(self.handle, ptrs, ctypes.c_void_p(out.data_ptr()), _stream_ptr(stream)),
                   "sb_forward_graph" if graph else "sb_forward")
         return out
@@ -222,7 +231,7 @@ class Plan:
             raise ValueError("raw must be the contiguous (batch, zeta_doubles) float64 result of this plan")
         nt = self.nbins ** (self.npcf - 1)
         norm = torch.empty((len(self.shapes), nt), dtype=torch.float64, device=self.device) if want_norm else None
-        with torch.cuda.device(self.device):
+        with _on_device(self.device):
             check(self.lib.sb_normalize(self.handle, self._ptrs(deltas), ctypes.c_void_p(raw.data_ptr()),
                                         ctypes.c_void_p(norm.data_ptr() if norm is not None else None),
                                         _stream_ptr(stream)), "sb_normalize")
@@ -238,7 +247,7 @@ class Plan:
             raise ValueError(f"grad_zeta has {gz.numel()} values; this plan needs "
                              f"{len(self.shapes)} x {self.zeta_doubles}")
         grads = [torch.empty(s, dtype=torch.float32, device=self.device) for s in self.shapes]
-        with torch.cuda.device(self.device):
+        with _on_device(self.device):
             check(self.lib.sb_backward(self.handle, self._ptrs(deltas), ctypes.c_void_p(gz.data_ptr()),
                                        self._ptrs(grads), _stream_ptr(stream)), "sb_backward")
         return grads
@@ -338,8 +347,7 @@ def measure(delta, bin_edges, lmax, projected=False, npcf=3, precision="fp32", n
         plan.normalize_raw([delta], raw)
     z = plan.unpack(raw)[0]
     idx = plan.zeta_index()
-    torch.cuda.synchronize(delta.device)
-    plan.close()
+    plan.close()   # waits for the device
     return z, idx
 
 

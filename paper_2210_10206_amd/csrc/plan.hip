@@ -76,6 +76,11 @@ void mirror_args(const sb_plan *p, const ShapeGroup &G, int kgroup0, Axis0Args &
 static sb_status build_gather(sb_plan *p, std::vector<int> &gptr, std::vector<int> &gidx, std::vector<double> &gcoef) {
     const int NB = p->prob.nbins;
     gptr.assign(1, 0);
+    const size_t nout = (size_t)p->zeta_doubles;
+    gptr.reserve(nout + 1);
+    const size_t nterm = p->prob.ndim == 3 && p->prob.npcf == 3 ? (size_t)p->nlm * NB * NB : nout;
+    gidx.reserve(nterm);
+    gcoef.reserve(nterm);
     auto add = [&](int src, double c) { gidx.push_back(src); gcoef.push_back(c); };
     auto close = [&]() { gptr.push_back((int)gidx.size()); };
     const int NP = NB * (NB + 1) / 2;
@@ -399,27 +404,32 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
                 }
         }
     }
-    // bin counts per group (host enumeration of the same integer test as the kernels)
+    // bin counts per group: the kernels' integer test on every offset, taken once per triple of
+    // coordinate magnitudes, weighted by how many zero-centred coordinates have each magnitude
     for (auto &G : p->groups) {
         for (int b = 0; b < NB; ++b) G.counts[b] = 0;
-        int64_t lim[3];
-        for (int d = 0; d < 3; ++d) lim[d] = d < prob->ndim ? G.n[d] : 1;
         const int64_t rmax = (int64_t)std::floor(p->edges[NB]) + 1;
-        for (int64_t i = 0; i < lim[0]; ++i) {
-            const int64_t ci = (2 * i < lim[0]) ? i : i - lim[0];
-            if (std::llabs(ci) > rmax) continue;
-            for (int64_t j = 0; j < lim[1]; ++j) {
-                const int64_t cj = prob->ndim >= 2 ? ((2 * j < lim[1]) ? j : j - lim[1]) : 0;
-                if (std::llabs(cj) > rmax) continue;
-                for (int64_t k = 0; k < lim[2]; ++k) {
-                    const int64_t ck = prob->ndim == 3 ? ((2 * k < lim[2]) ? k : k - lim[2]) : 0;
-                    const int64_t s = ci * ci + cj * cj + ck * ck;
-                    if (s == 0) continue;
-                    for (int b = 0; b < NB; ++b)
-                        if (p->thr[b] < s && s <= p->thr[b + 1]) { G.counts[b]++; break; }
-                }
+        std::vector<int64_t> mult[3];
+        for (int d = 0; d < 3; ++d) {
+            const int64_t n = d < prob->ndim ? G.n[d] : 1;
+            mult[d].assign((size_t)std::min<int64_t>(rmax, n) + 1, 0);
+            for (int64_t i = 0; i < n; ++i) {
+                const int64_t c = 2 * i < n ? i : n - i;   // |c_i|
+                if (c <= rmax) mult[d][c]++;
             }
         }
+        const auto below = [&](int64_t s) { return (int)(std::lower_bound(p->thr, p->thr + NB + 1, s) - p->thr) - 1; };
+        for (size_t i = 0; i < mult[0].size(); ++i)
+            for (size_t j = 0; mult[0][i] && j < mult[1].size(); ++j) {
+                const int64_t sij = (int64_t)(i * i + j * j), m = mult[0][i] * mult[1][j];
+                if (sij > p->thr[NB]) break;
+                for (size_t k = 0; m && k < mult[2].size(); ++k) {
+                    const int64_t s = sij + (int64_t)(k * k);
+                    if (s > p->thr[NB]) break;
+                    const int b = below(s);   // thr[b] < s <= thr[b + 1]
+                    if (s > 0 && b >= 0) G.counts[b] += m * mult[2][k];
+                }
+            }
     }
     // result layout
     const int L = prob->lmax;
@@ -570,6 +580,7 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
     std::vector<int> gptr, gidx;
     std::vector<double> gcoef;
     build_gather(p, gptr, gidx, gcoef);
+    host.reserve(host.size() + 1024 + (gptr.size() + gidx.size()) * sizeof(int) + gcoef.size() * sizeof(double));
     p->gather_nout = (int)gptr.size() - 1;
     p->gather_terms = (int)gidx.size();
     p->off_gptr = put(gptr.data(), gptr.size() * sizeof(int));
