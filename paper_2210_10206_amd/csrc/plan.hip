@@ -122,11 +122,12 @@ static sb_status build_gather(sb_plan *p, std::vector<int> &gptr, std::vector<in
         for (const auto &pr : p->p4_pairs) {
             const P4Canon cn = p4_canonical(pr.first, pr.second);
             const int key = p->p4_canon_index.at({cn.m[0], cn.m[1]});
+            const auto &sl = p->p4_slot[key];
             for (int b1 = 0; b1 < NB; ++b1)
                 for (int b2 = 0; b2 < NB; ++b2)
                     for (int b3 = 0; b3 < NB; ++b3) {
                         const int b[3] = {b1, b2, b3};
-                        const int f = (b[cn.pos[0]] * NB + b[cn.pos[1]]) * NB + b[cn.pos[2]];
+                        const int f = (b[cn.pos[sl[0]]] * NB + b[cn.pos[sl[1]]]) * NB + b[cn.pos[sl[2]]];
                         add(key * NV2 + 2 * f, 1.0);
                         close();
                         add(key * NV2 + 2 * f + 1, cn.neg ? -1.0 : 1.0);
@@ -260,7 +261,10 @@ static void table_pointers(sb_plan *p) {
         p->d_gtptr = reinterpret_cast<const int *>(base + p->off_gtptr);
         p->d_glam = reinterpret_cast<const int *>(base + p->off_glam);
     }
-    if (p->prob.npcf == 4 && p->prob.ndim == 2) p->d_pairs = reinterpret_cast<const int *>(base + p->off_pairs);
+    if (p->prob.npcf == 4 && p->prob.ndim == 2) {
+        p->d_pairs = reinterpret_cast<const int *>(base + p->off_pairs);
+        p->d_items = reinterpret_cast<const int *>(base + p->off_items);
+    }
     if (p->npack > 0) {
         p->d_kmap = reinterpret_cast<const int *>(base + p->off_kmap);
         p->d_rowmap = reinterpret_cast<const int *>(base + p->off_rowmap);
@@ -452,7 +456,17 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
             const P4Canon cn = p4_canonical(pr.first, pr.second);
             if (!p->p4_canon_index.count({cn.m[0], cn.m[1]})) {
                 p->p4_canon_index[{cn.m[0], cn.m[1]}] = (int)p->p4_canon.size();
-                p->p4_canon.push_back({cn.m[0], cn.m[1]});
+                // the kernel's slots: two equal orders first, or a zero order last
+                std::array<int, 3> sl = {0, 1, 2};
+                int kind = P4_GENERAL;
+                for (int k = 0; k < 3 && kind != P4_REAL_B; ++k) {
+                    const int x = (k + 1) % 3, y = (k + 2) % 3;
+                    if (cn.m[k] == 0) { sl = {x, y, k}; kind = P4_REAL_B; }
+                    else if (cn.m[x] == cn.m[y]) { sl = {x, y, k}; kind = P4_SYM; }
+                }
+                p->p4_slot.push_back(sl);
+                p->p4_kind.push_back(kind);
+                p->p4_canon.push_back({cn.m[sl[0]], cn.m[sl[1]]});
             }
         }
         p->zeta_doubles = (int64_t)p->p4_pairs.size() * NB * NB * NB * 2;
@@ -571,6 +585,16 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
         std::vector<int> pr;
         for (const auto &x : p->p4_canon) { pr.push_back(x.first); pr.push_back(x.second); }
         p->off_pairs = put(pr.data(), pr.size() * sizeof(int));
+        // work items of a cell block, the general triples first (a launch ends on the short ones)
+        std::vector<int> items;
+        const int step = proj4_tiles_per_item(NB);
+        for (const bool sym : {false, true})
+            for (size_t c = 0; c < p->p4_canon.size(); ++c)
+                if ((p->p4_kind[c] != P4_GENERAL) == sym)
+                    for (int t = 0; t * 16 < (sym ? NB * (NB + 1) / 2 : NB * NB); t += step)
+                        items.insert(items.end(), {(int)c, t, p->p4_kind[c]});
+        p->p4_items = (int)items.size() / 3;
+        p->off_items = put(items.data(), items.size() * sizeof(int));
     }
     if (p->npack > 0) {
         p->off_kmap = put(p->ag_kmap.data(), p->ag_kmap.size() * sizeof(int));
@@ -1074,6 +1098,8 @@ sb_status contract(sb_plan *p, const ShapeGroup &G, const float *w, double *cons
         a.nbins = NB;
         a.npairs = groups;
         a.pairs = p->d_pairs;
+        a.items = p->d_items;
+        a.nitems = p->p4_items;
         a.mmax = p->prob.lmax;
         a.cells_per_block = contract_cells(p, G.ng);
         a.tile = p->proj4_tile;

@@ -15,17 +15,30 @@
 // of the four.
 //
 // The float32 kernel has one wave per M tile: every wave contracts all cells of a staged tile
-// against its own 16 pairs, so it holds one tile's three accumulators (12 registers), the waves
-// need no combine at the end, and the small register count leaves room for two workgroups per CU.
-// The float32 sums of each staged tile are combined into the real and imaginary parts in
-// float64 (exactly) and added to float64 totals.
+// against its own 16 pairs, so it holds one tile's three accumulators (12 registers) and the waves
+// need no combine at the end.  A workgroup takes up to four of a triple's M tiles (an item), a
+// wave for each SIMD; triples of more tiles are several items of the same cells.  The float32 sums of
+// 64 cells are combined into the real and imaginary parts in float64 (exactly) and added to float64
+// totals.
 //
-// Staging as in the full-4PCF matrix-core kernels: a tile of 64 cells in LDS, cell-major, one
+// Symmetric triples take less: (a, a, -2a) is symmetric in (b1, b2), and (m, -m, 0) goes to its
+// conjugate under b1 <-> b2 and has a real c_0 as B, so both compute the pairs b1 <= b2 only (4 tiles
+// instead of 7 at 10 bins) and the latter two products instead of three.  16 of the 36 triples at
+// m <= 10 are of these kinds: a quarter of the MFMAs.
+//
+// Measured on a 512^2 field, 10 bins, m <= 10: 1.07 ms (1.42 with seven-wave workgroups, every pair of
+// every triple, and the next tile's loads each waited for to take the sign of a negative order).  The
+// MFMAs alone take 0.55 ms; the rest is the chain LDS read -> complex product -> MFMA of a step.
+//
+// Staging as in the full-4PCF matrix-core kernels: a tile of 32 cells in LDS, cell-major, one
 // row per cell padded to a stride = 2 (mod 8) float2 (bank-conflict free stores and reads) that
 // holds per bin w c_m1, c_m2, (Br, Bi - Br) and (Br + Bi, 0); the next tile's global loads are
 // issued before the current one is contracted and staged into a second buffer after it.  Block
 // partials: partial[(pair * NB^3 * 2 + (p NB + b3) 2 + part) * nblocks + block], as for the
 // vector kernel.
+#include <algorithm>
+#include <type_traits>
+
 #include "sb_kgen.h"
 
 namespace sb {
@@ -51,56 +64,78 @@ __device__ __forceinline__ bool xcd_work(int b, int nblocks, int ntriples, int *
     return true;
 }
 
+// Waves (M tiles) of a float32 workgroup: at most four, so that every SIMD of a CU has its share.
 template <int NB>
-__global__ __launch_bounds__(64 * proj4_tiles<NB>()) void proj4_mfma_kernel(Proj4Args a) {
+constexpr int proj4_waves() { return proj4_tiles<NB>() < 4 ? proj4_tiles<NB>() : 4; }
+
+template <int NB>
+__global__ __launch_bounds__(64 * proj4_waves<NB>(), 4) void proj4_mfma_kernel(Proj4Args a) {
     a.coef += (int64_t)blockIdx.z * a.coef_fs;   // field of the launch (grid.z)
     a.w += (int64_t)blockIdx.z * a.w_fs;
     a.partial += (int64_t)blockIdx.z * a.part_fs;
-    int cb = 0, pr_ = 0;
-    if (!xcd_work(blockIdx.x, a.nblocks, a.npairs, &cb, &pr_)) return;
-    constexpr int NP = NB * NB;
-    constexpr int NMT = proj4_tiles<NB>();     // M tiles of 16 pairs = waves
-    constexpr int NT = 64 * NMT;
-    constexpr int TC = 64;                     // cells per staged tile
+    int cb = 0, it = 0;
+    if (!xcd_work(blockIdx.x, a.nblocks, a.nitems, &cb, &it)) return;
+    const int pr_ = a.items[3 * it], tile0 = a.items[3 * it + 1], kind = a.items[3 * it + 2];
+    const bool sym = kind != P4_GENERAL;
+    constexpr int NP = NB * NB, NPS = NB * (NB + 1) / 2;
+    constexpr int NT = 64 * proj4_waves<NB>();
+    constexpr int TC = 32;                     // cells per staged tile
     constexpr int WL = 3 * NB;                 // loaded float2 per cell (m1, m2, m3 columns)
     constexpr int W = 4 * NB;                  // staged float2 per cell (see stage)
     constexpr int S = (W + 7) / 8 * 8 + 2;     // padded row stride, = 2 (mod 8)
     constexpr int NLD = (TC * WL + NT - 1) / NT;   // loaded float2 per thread and tile
     constexpr int NV = NB * NB * NB * 2;
-    static_assert(NT % TC == 0, "every load of a thread is of the cell of its lane");
     __shared__ float2 tiles[2][TC * S];        // double-buffered: one barrier per staged tile
     const int tid = threadIdx.x, lane = tid & 63;
-    const int mt = __builtin_amdgcn_readfirstlane(tid >> 6);   // this wave's M tile
+    const int mt = tile0 + __builtin_amdgcn_readfirstlane(tid >> 6);   // this wave's M tile
     const int i = lane & 15, g = lane >> 4;
     const int m1 = a.pairs[2 * pr_], m2 = a.pairs[2 * pr_ + 1];
     const int ms[3] = {m1, m2, -(m1 + m2)};
+    // bins of pair p (symmetric triples: b1 <= b2, b1 outer)
+    auto pair_bins = [&](int p, int *b1, int *b2) {
+        if (!sym) {
+            *b1 = p / NB;
+            *b2 = p % NB;
+            return;
+        }
+        int x = 0, rem = p;
+        while (rem >= NB - x) rem -= NB - x++;
+        *b1 = x;
+        *b2 = x + rem;
+    };
+    const int np = sym ? NPS : NP;
     const int p = 16 * mt + i;                 // pair of this lane's row
     // rows past the last pair and columns past the last bin read bin 0 / bin NB - 1 (valid LDS
     // addresses, no branch in the cell loop); their sums are never written
-    const int b1 = p < NP ? p / NB : 0, b2 = p < NP ? p % NB : 0;
+    int b1 = 0, b2 = 0;
+    if (p < np) pair_bins(p, &b1, &b2);
     const int ib = i < NB ? i : NB - 1;
+    const bool busy = 16 * mt < np;            // (uniform) the wave has pairs
     f4v acc1 = f4v{0.f, 0.f, 0.f, 0.f}, acc2 = acc1, acc3 = acc1;
     double totr[4] = {0.0, 0.0, 0.0, 0.0}, toti[4] = {0.0, 0.0, 0.0, 0.0};
     const int64_t c0 = (int64_t)cb * a.cells_per_block;
     const int64_t c1 = min(c0 + a.cells_per_block, a.ng);
-    // load k of this thread: f = tid + NT k -> cell f % 64 (= lane), loaded column (slot, bin) f / 64
+    // load k of this thread: f = tid + NT k -> cell f % 32, loaded column (slot, bin) f / 32, from
+    // array col[k] (-1: none); c_{-m} = conj(c_m), the sign taken when staged, so that all loads are
+    // in flight at once
     float2 pf[NLD];
     float pw = 0.f;
-    auto gload = [&](int64_t tc) {
+    int col[NLD];
+    uint32_t conj[NLD];
 #pragma unroll
-        for (int k = 0; k < NLD; ++k) {
-            const int f = tid + NT * k;
-            const int c = f % TC, kb = f / TC;
-            float2 v = make_float2(0.f, 0.f);
-            if (kb < WL && tc + c < c1) {
-                const int slot = kb / NB, b = kb % NB;
-                const int m = ms[slot];
-                v = a.coef[((int64_t)(m < 0 ? -m : m) * NB + b) * a.ng + tc + c];
-                if (m < 0) v.y = -v.y;   // c_{-m} = conj(c_m)
-            }
-            pf[k] = v;
-        }
-        pw = tc + lane < c1 ? a.w[tc + lane] : 0.f;
+    for (int k = 0; k < NLD; ++k) {
+        const int kb = (tid + NT * k) / TC, slot = kb / NB, m = slot == 0 ? ms[0] : slot == 1 ? ms[1] : ms[2];
+        col[k] = kb < WL ? (m < 0 ? -m : m) * NB + kb % NB : -1;
+        conj[k] = m < 0 ? 0x80000000u : 0u;
+    }
+    auto gload = [&](int64_t tc) {
+        const bool in = tc + tid % TC < c1;
+        const float2 *src = a.coef + tc + tid % TC;
+#pragma unroll
+        for (int k = 0; k < NLD; ++k)
+            pf[k] = in && col[k] >= 0 ? src[(int64_t)col[k] * a.ng] : make_float2(0.f, 0.f);
+        const int c = tid % TC;
+        pw = tc + c < c1 ? a.w[tc + c] : 0.f;
     };
     // a staged row holds, per bin, w c_m1 (the weight folded in once here instead of in every
     // wave), c_m2, (Br, Bi - Br) and (Br + Bi, 0) of B = c_m3: every operand of the three
@@ -109,9 +144,9 @@ __global__ __launch_bounds__(64 * proj4_tiles<NB>()) void proj4_mfma_kernel(Proj
 #pragma unroll
         for (int k = 0; k < NLD; ++k) {
             const int f = tid + NT * k;
-            const int c = f % TC, kb = f / TC;
+            const int c = f % TC, kb = f / TC;   // NT is a multiple of TC: every load is of one cell
             float2 *row = tiles[buf] + c * S;
-            const float2 v = pf[k];
+            const float2 v = make_float2(pf[k].x, __uint_as_float(__float_as_uint(pf[k].y) ^ conj[k]));
             if (kb < NB) {
                 row[kb] = make_float2(pw * v.x, pw * v.y);
             } else if (kb < 2 * NB) {
@@ -133,41 +168,84 @@ __global__ __launch_bounds__(64 * proj4_tiles<NB>()) void proj4_mfma_kernel(Proj
         const bool more = tc + TC < c1;
         if (more) gload(tc + TC);
         const float2 *tile = tiles[buf];
-#pragma unroll 2
-        for (int cc = 0; cc < TC / 4; ++cc) {
-            const int c = 4 * cc + g;
-            const float2 *row = tile + c * S;
-            const float2 bv = row[2 * NB + ib];       // (Br, Bi - Br)
-            const float bs = row[3 * NB + ib].x;      // Br + Bi
-            const float2 u = row[b1], x2 = row[NB + b2];   // u = w c_m1
-            float2 L;
-            L.x = __builtin_fmaf(u.x, x2.x, -u.y * x2.y);
-            L.y = __builtin_fmaf(u.x, x2.y, u.y * x2.x);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(L.x + L.y, bv.x, acc1, 0, 0, 0);
-            acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(L.x, bv.y, acc2, 0, 0, 0);
-            acc3 = __builtin_amdgcn_mfma_f32_16x16x4f32(L.y, bs, acc3, 0, 0, 0);
-        }
+        // the operands of four cells (one per lane group), read a step ahead of their products
+        struct Ops {
+            float2 u, x2, bv;   // w c_m1, c_m2, (Br, Bi - Br)
+            float bs;           // Br + Bi
+        };
+        auto fetch = [&](int cc, auto real_c) {
+            const float2 *row = tile + (4 * cc + g) * S;
+            Ops o;
+            o.u = row[b1];
+            o.x2 = row[NB + b2];
+            if constexpr (decltype(real_c)::value) {
+                o.bv = make_float2(row[2 * NB + ib].x, 0.f);
+                o.bs = 0.f;
+            } else {
+                o.bv = row[2 * NB + ib];
+                o.bs = row[3 * NB + ib].x;
+            }
+            return o;
+        };
+        auto contract = [&](auto real_c) {
+            Ops nx = fetch(0, real_c);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {   // P1 - P3 and P1 + P2, exact in float64
-            const double p1 = (double)acc1[r];
-            totr[r] += p1 - (double)acc3[r];
-            toti[r] += p1 + (double)acc2[r];
+            for (int cc = 0; cc < TC / 4; ++cc) {
+                const Ops o = nx;
+                if (cc + 1 < TC / 4) nx = fetch(cc + 1, real_c);
+                float2 L;
+                L.x = __builtin_fmaf(o.u.x, o.x2.x, -o.u.y * o.x2.y);
+                L.y = __builtin_fmaf(o.u.x, o.x2.y, o.u.y * o.x2.x);
+                if constexpr (decltype(real_c)::value) {
+                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(L.x, o.bv.x, acc1, 0, 0, 0);
+                    acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(L.y, o.bv.x, acc2, 0, 0, 0);
+                } else {
+                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(L.x + L.y, o.bv.x, acc1, 0, 0, 0);
+                    acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(L.x, o.bv.y, acc2, 0, 0, 0);
+                    acc3 = __builtin_amdgcn_mfma_f32_16x16x4f32(L.y, o.bs, acc3, 0, 0, 0);
+                }
+            }
+        };
+        if (busy) {
+            if (kind == P4_REAL_B) contract(std::true_type{});
+            else contract(std::false_type{});
         }
-        acc1 = f4v{0.f, 0.f, 0.f, 0.f};
-        acc2 = acc1;
-        acc3 = acc1;
+        if (((tc - c0) & TC) != 0 || !more) {   // every 64 cells
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (kind != P4_REAL_B) {   // P1 - P3 and P1 + P2, exact in float64
+                    const double p1 = (double)acc1[r];
+                    totr[r] += p1 - (double)acc3[r];
+                    toti[r] += p1 + (double)acc2[r];
+                } else {
+                    totr[r] += (double)acc1[r];
+                    toti[r] += (double)acc2[r];
+                }
+            }
+            acc1 = f4v{0.f, 0.f, 0.f, 0.f};
+            acc2 = acc1;
+            acc3 = acc1;
+        }
         if (more) stage(buf ^ 1);
         __syncthreads();
     }
     // accumulator: lane l holds rows 4 g + r (pair 16 mt + 4 g + r), column i (bin b3); each
-    // (pair, b3, part) of the block is held by exactly one lane
+    // (pair, b3, part) of the block is held by exactly one lane, which also writes the mirrored pair
+    // (its conjugate for the real B)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int pp = 16 * mt + 4 * g + r;
-        if (pp < NP && i < NB) {
-            const int64_t v = (int64_t)pr_ * NV + (pp * NB + i) * 2;
+        if (pp < np && i < NB) {
+            int q1 = 0, q2 = 0;
+            pair_bins(pp, &q1, &q2);
+            const int64_t v = (int64_t)pr_ * NV + ((q1 * NB + q2) * NB + i) * 2;
             a.partial[v * a.nblocks + cb] = totr[r];
             a.partial[(v + 1) * a.nblocks + cb] = toti[r];
+            if (sym && q1 != q2) {
+                const int64_t vm = (int64_t)pr_ * NV + ((q2 * NB + q1) * NB + i) * 2;
+                a.partial[vm * a.nblocks + cb] = totr[r];
+                a.partial[(vm + 1) * a.nblocks + cb] = kind == P4_REAL_B ? -toti[r] : toti[r];
+            }
         }
     }
 }
@@ -314,16 +392,19 @@ __global__ __launch_bounds__(256, 2) void proj4_split_kernel(Proj4Args a) {
 
 template <int NB>
 hipError_t launch_nb(const Proj4Args &a, hipStream_t s) {
-    const int64_t total = (int64_t)a.nblocks * a.npairs;   // one block per item, 8 | grid.x (xcd_work)
+    // one block per item (float32) or triple and cell block, 8 | grid.x (xcd_work)
+    const int64_t total = (int64_t)a.nblocks * (a.precision == 1 ? a.npairs : a.nitems);
     dim3 grid((unsigned)((total + 7) / 8 * 8), 1, (unsigned)(a.fields > 1 ? a.fields : 1));
     if (a.precision == 1)
         hipLaunchKernelGGL((proj4_split_kernel<NB>), grid, dim3(256), 0, s, a);
     else
-        hipLaunchKernelGGL((proj4_mfma_kernel<NB>), grid, dim3(64 * proj4_tiles<NB>()), 0, s, a);
+        hipLaunchKernelGGL((proj4_mfma_kernel<NB>), grid, dim3(64 * proj4_waves<NB>()), 0, s, a);
     return hipGetLastError();
 }
 
 }  // namespace
+
+int proj4_tiles_per_item(int nbins) { return std::min(4, (nbins * nbins + 15) / 16); }
 
 hipError_t launch_proj4_mfma(const Proj4Args &a, hipStream_t s) {
     switch (a.nbins) {

@@ -126,6 +126,11 @@ struct QuadMArgs {
 hipError_t launch_quad_mfma(int la, int lb, int lc, const QuadMArgs &a, hipStream_t s);
 bool quad_mfma_available(int la, int lb, int lc, int nbins);
 
+// Kinds of canonical (m1, m2, m3): any; (a, a, -2a), symmetric in (b1, b2); (m, -m, 0), whose third
+// coefficient is real and which goes to its conjugate under b1 <-> b2.
+enum P4Kind : int { P4_GENERAL = 0, P4_SYM = 1, P4_REAL_B = 2 };
+int proj4_tiles_per_item(int nbins);   // M tiles (of 16 bin pairs) of a workgroup
+
 // ---- projected 4PCF: block partials of sum_x w c^{b1}_{m1} c^{b2}_{m2} c^{b3}_{m3} (complex)
 struct Proj4Args {
     const float2 *coef;       // [m][bin][ng], m >= 0
@@ -134,6 +139,9 @@ struct Proj4Args {
     int nbins;
     int npairs;               // canonical (m1, m2) pairs
     const int *pairs;         // 2 per pair
+    // float32 matrix-core kernel: its work items per cell block, 3 ints each: pair, first M tile, P4Kind
+    const int *items;
+    int nitems;
     int mmax;
     int cells_per_block;
     int tile;

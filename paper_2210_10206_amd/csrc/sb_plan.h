@@ -75,6 +75,11 @@ struct sb_plan {
     std::vector<char> host_tab;
     size_t tab_bytes = 0;
     std::map<int, size_t> tw_off;
+    std::vector<std::array<int, 3>> p4_slot;              // projected 4PCF: kernel slot k holds canonical slot p4_slot[c][k]
+    std::vector<int> p4_kind;                             // P4Kind of each canonical triple
+    size_t off_items = 0;
+    int p4_items = 0;
+    const int *d_items = nullptr;
     size_t off_gterms = 0, off_gtptr = 0, off_glam = 0;   // run-time matrix-core contraction
     int nglam = 0;                                        // its canonical Lambdas
     size_t off_terms = 0, off_tptr = 0, off_laml = 0, off_stage = 0, off_pairs = 0, off_coefw = 0;
