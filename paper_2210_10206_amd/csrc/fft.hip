@@ -4,9 +4,8 @@
 // arrays.  A workgroup owns P pencils: it stages them in LDS (coalesced: P
 // adjacent pencils along the fastest axis for a strided axis, P whole rows for
 // the contiguous axis), runs the radix stages in LDS with TPP threads per
-// pencil, and writes the tile back.  Loads can fuse the spectral product
-// (delta_hat * kernel_hat) or read a real field; stores can fuse a spectral
-// multiply-accumulate.  The radix stages are in fft_core.h.
+// pencil, and writes the tile back.  Loads can read a real field.  The radix
+// stages are in fft_core.h.
 #include <algorithm>
 #include <utility>
 
@@ -15,32 +14,6 @@
 namespace sb {
 namespace {
 using namespace fftcore;
-
-__device__ __forceinline__ float2 load_elem(const FftPass &a, int y, int64_t idx) {
-    switch (a.load) {
-        case LOAD_MUL: {
-            const float2 x = reinterpret_cast<const float2 *>(a.in)[y * a.in_bs + idx];
-            const float2 k = a.in2[y * a.in2_bs + idx];
-            return cmul(x, k);
-        }
-        case LOAD_R32:
-            return make_float2(reinterpret_cast<const float *>(a.in)[y * a.in_bs + idx], 0.f);
-        case LOAD_R64:
-            return make_float2((float)reinterpret_cast<const double *>(a.in)[y * a.in_bs + idx], 0.f);
-        default:
-            return reinterpret_cast<const float2 *>(a.in)[y * a.in_bs + idx];
-    }
-}
-
-__device__ __forceinline__ void store_elem(const FftPass &a, int y, int64_t idx, float2 v) {
-    float2 *o = a.out + y * a.out_bs + idx;
-    if (a.store == STORE_MACC) {
-        const float2 m = a.mul[y * a.mul_bs + idx];
-        *o = cadd(*o, cmul(v, m));
-    } else {
-        *o = v;
-    }
-}
 
 template <int N, int TPP, int NT, int SIGN, int... RAD>
 __global__ __launch_bounds__(NT) void fft_pass_kernel(FftPass a) {
@@ -59,33 +32,45 @@ __global__ __launch_bounds__(NT) void fft_pass_kernel(FftPass a) {
         base[tid] = (g / a.stride) * (int64_t)N * a.stride + (g % a.stride);
     }
     __syncthreads();
-    if (a.stride == 1) {
-        for (int f = tid; f < P * N; f += NT) {
-            const int p = f / N, j = f % N;
-            float2 v = make_float2(0.f, 0.f);
-            if (g0 + p < npencil) v = load_elem(a, y, base[p] + j);
-            sm[j * PITCH + p] = v;
+    // element e of this thread: f = tid + e NT -> (pencil, column) by the coalesced pattern; the plain
+    // loads of a thread are all in flight before the first is staged (a branch over the load kinds
+    // for every element waited for each)
+    constexpr int EPT = N / TPP;
+    const bool rows = a.stride == 1;
+    auto place = [&](int e, int &p, int &j) {
+        const int f = tid + e * NT;
+        if (rows) { p = f / N; j = f % N; } else { p = f % P; j = f / P; }
+    };
+    auto stage_all = [&](auto load) {
+        float2 v[EPT];
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            int p, j;
+            place(e, p, j);
+            v[e] = g0 + p < npencil ? load(base[p] + (int64_t)j * a.stride) : make_float2(0.f, 0.f);
         }
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            int p, j;
+            place(e, p, j);
+            sm[j * PITCH + p] = v[e];
+        }
+    };
+    if (a.load == LOAD_C) {
+        const float2 *in = reinterpret_cast<const float2 *>(a.in) + y * a.in_bs;
+        stage_all([&](int64_t idx) { return in[idx]; });
     } else {
-        for (int f = tid; f < P * N; f += NT) {
-            const int p = f % P, j = f / P;
-            float2 v = make_float2(0.f, 0.f);
-            if (g0 + p < npencil) v = load_elem(a, y, base[p] + (int64_t)j * a.stride);
-            sm[j * PITCH + p] = v;
-        }
+        const float *in = reinterpret_cast<const float *>(a.in) + y * a.in_bs;
+        stage_all([&](int64_t idx) { return make_float2(in[idx], 0.f); });
     }
     __syncthreads();
     stages<N, TPP, SIGN, 1, RAD...>(sm, tw, tid % P, tid / P, PITCH);
-    if (a.stride == 1) {
-        for (int f = tid; f < P * N; f += NT) {
-            const int p = f / N, j = f % N;
-            if (g0 + p < npencil) store_elem(a, y, base[p] + j, sm[j * PITCH + p]);
-        }
-    } else {
-        for (int f = tid; f < P * N; f += NT) {
-            const int p = f % P, j = f / P;
-            if (g0 + p < npencil) store_elem(a, y, base[p] + (int64_t)j * a.stride, sm[j * PITCH + p]);
-        }
+    float2 *out = a.out + y * a.out_bs;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        int p, j;
+        place(e, p, j);
+        if (g0 + p < npencil) out[base[p] + (int64_t)j * a.stride] = sm[j * PITCH + p];
     }
 }
 
@@ -138,15 +123,15 @@ struct UpperPlanes {
     }
 };
 
-// Stored-kernel value at axis-0 index j of this thread's cell g (gm: the cell of -k): `upper`
-// (compile-time in the callers) says whether j lies in the upper half of the axis.  Zero outside
-// the support |c_0| <= r0.
+// Stored-kernel value at axis-0 index j of this thread's cell g (gm: the cell of -k), without the
+// sign or conjugation of the upper half: the callers apply u.sx, u.sy where they use the value, so
+// that a load made ahead is not waited for where it is made.  `upper` (compile-time in the callers)
+// says whether j lies in the upper half of the axis.  Zero outside the support |c_0| <= r0.
 __device__ __forceinline__ float2 kernel_elem(const float2 *kc, int64_t plane, int r0, int j, int n, bool upper, int64_t g,
                                               int64_t gm, const UpperPlanes &u) {
     if (!upper) return (j <= r0 || u.dense) ? ld_stream(&kc[(int64_t)j * plane + g]) : make_float2(0.f, 0.f);
     if (j < n - r0 && !u.dense) return make_float2(0.f, 0.f);
-    const float2 v = ld_stream(&kc[(int64_t)(u.pa + u.pb * j) * plane + (u.mirrored ? gm : g)]);
-    return make_float2(u.sx * v.x, u.sy * v.y);
+    return ld_stream(&kc[(int64_t)(u.pa + u.pb * j) * plane + (u.mirrored ? gm : g)]);
 }
 
 // The rule of global kernel group grp in an axis-0 launch (0 for a full store).  The groups come
@@ -194,6 +179,9 @@ __global__ __launch_bounds__(NT) void axis0_kernel(Axis0Args a) {
         for (int e = 0; e < EPT; ++e)   // rows e >= EPT / 2 lie in the upper half of the axis
             dst[e] = ok ? kernel_elem(kc, a.plane, a.r0, q0 + e * TPP, N, 2 * e >= EPT, g, gm, up) : make_float2(0.f, 0.f);
     };
+    auto scaled = [&](const UpperPlanes &u, int e, float2 v) {
+        return 2 * e >= EPT ? make_float2(u.sx * v.x, u.sy * v.y) : v;
+    };
     float2 nx[EPT];
     if (a.mode == 0) {
         float2 dr[EPT];
@@ -203,11 +191,12 @@ __global__ __launch_bounds__(NT) void axis0_kernel(Axis0Args a) {
         const int64_t kbase = (int64_t)(a.kmap ? a.kmap[sh.grp] : sh.grp) * a.nb;   // kernel group
         const int kgrp = a.kgroup0 + (int)(a.kmap ? a.kmap[sh.grp] : sh.grp);       // its global index
         const int64_t obase = (int64_t)sh.grp * a.nb;                             // output arrays
+        const UpperPlanes up(a.half, SB_MIRROR_RULE(a, kgrp), a.np, N);
         load_kernel(kbase + sh.b0, kgrp, nx);
         for (int b = sh.b0; b < sh.b1; ++b) {
             __syncthreads();
 #pragma unroll
-            for (int e = 0; e < EPT; ++e) sm[(q0 + e * TPP) * PITCH + p] = nx[e];
+            for (int e = 0; e < EPT; ++e) sm[(q0 + e * TPP) * PITCH + p] = scaled(up, e, nx[e]);
             if (b + 1 < sh.b1) load_kernel(kbase + b + 1, kgrp, nx);   // in flight during the transforms
             __syncthreads();
             stages<N, TPP, -1, 1, RAD...>(sm, tw, p, q0, PITCH);
@@ -238,11 +227,12 @@ __global__ __launch_bounds__(NT) void axis0_kernel(Axis0Args a) {
         load_v(0, nv);
         load_kernel(acc_kernel(a, 0), acc_group(a, 0), nx);
         for (int t = 0; t < nt; ++t) {
+            const UpperPlanes up(a.half, SB_MIRROR_RULE(a, acc_group(a, t)), a.np, N);
             __syncthreads();
 #pragma unroll
             for (int e = 0; e < EPT; ++e) {
                 sm[(q0 + e * TPP) * PITCH + p] = nv[e];
-                kx[e] = nx[e];
+                kx[e] = scaled(up, e, nx[e]);
             }
             if (t + 1 < nt) {
                 load_v(t + 1, nv);
@@ -261,12 +251,13 @@ __global__ __launch_bounds__(NT) void axis0_kernel(Axis0Args a) {
 #pragma unroll
             for (int e = 0; e < EPT; ++e) acc[e] = cadd(acc[e], cmul(vr[e], sm[(q0 + e * TPP) * PITCH + p]));
             if (t % a.nb == a.nb - 1) {   // end of a group: out += its sum, as separate launches would
-                if (ok)
+                if (ok) {
+                    float2 o[EPT];   // read together: one after the other each waits for the last store
 #pragma unroll
-                    for (int e = 0; e < EPT; ++e) {
-                        float2 *o = out0 + (int64_t)(q0 + e * TPP) * a.plane + g;
-                        *o = cadd(*o, acc[e]);
-                    }
+                    for (int e = 0; e < EPT; ++e) o[e] = out0[(int64_t)(q0 + e * TPP) * a.plane + g];
+#pragma unroll
+                    for (int e = 0; e < EPT; ++e) out0[(int64_t)(q0 + e * TPP) * a.plane + g] = cadd(o[e], acc[e]);
+                }
 #pragma unroll
                 for (int e = 0; e < EPT; ++e) acc[e] = make_float2(0.f, 0.f);
             }
@@ -360,11 +351,18 @@ __global__ __launch_bounds__(P * R2, MODE == 0 ? (R1 < 32 && 2 * KR < R1 ? 3 : 2
                                                            : make_float2(0.f, 0.f);
             } else {
                 const int p0 = up.pb > 0 ? up.pa + R2 * r : up.pa - R2 * r - (R2 - 1);   // lowest plane of the row
-                const float2 v = (ok && (j >= N - a.r0 || up.dense)) ? ld_stream(at_bytes(kc + (int64_t)p0 * a.plane, lane_hi))
-                                                                     : make_float2(0.f, 0.f);
-                dst[r] = make_float2(up.sx * v.x, up.sy * v.y);
+                dst[r] = (ok && (j >= N - a.r0 || up.dense)) ? ld_stream(at_bytes(kc + (int64_t)p0 * a.plane, lane_hi))
+                                                             : make_float2(0.f, 0.f);
             }
         }
+    };
+    // the loaded rows with the sign or conjugation of the upper ones, taken where they are used: next
+    // to the loads it would wait for them, before the transforms that they are to overlap
+    auto take = [&](int grp, const float2 *src, float2 *dst) {
+        const UpperPlanes up(a.half, SB_MIRROR_RULE(a, grp), a.np, N);
+#pragma unroll
+        for (int r = 0; r < R1; ++r)
+            dst[r] = 2 * r < R1 || (r > KR && r < R1 - KR) ? src[r] : make_float2(up.sx * src[r].x, up.sy * src[r].y);
     };
     // one transform: radix-R1 DFT of the own rows, exchange, twiddle, radix-R2 DFTs -> own rows
     auto transform = [&](float2 *v, float2 *buf, auto sign_c) {
@@ -391,34 +389,35 @@ __global__ __launch_bounds__(P * R2, MODE == 0 ? (R1 < 32 && 2 * KR < R1 ? 3 : 2
     };
     float2 nx[R1];
     if constexpr (MODE == 1) {
-        // adjoint: out += sum_b FFT_0(v_b) FFT_0(kernel b); bin b + 1 loads during bin b
+        // adjoint: out += sum_b FFT_0(v_b) FFT_0(kernel b); v_b loads during its kernel's transform, and the
+        // next kernel during both
         auto load_v = [&](int b, float2 *dst) {
             const float2 *vb = a.vin + (int64_t)b * a.ng;
 #pragma unroll
             for (int r = 0; r < R1; ++r) dst[r] = ok ? *elem(vb, r) : make_float2(0.f, 0.f);
         };
-        float2 acc[R1], nv[R1];
+        float2 acc[R1];
 #pragma unroll
         for (int r = 0; r < R1; ++r) acc[r] = make_float2(0.f, 0.f);
         const int nt = (a.accgroups > 1 ? a.accgroups : 1) * a.nb;   // (group, bin) steps
-        load_v(0, nv);
         load_kernel(acc_kernel(a, 0), acc_group(a, 0), nx);
         for (int t = 0; t < nt; ++t) {
             float2 v[R1], k[R1];
-#pragma unroll
-            for (int r = 0; r < R1; ++r) { v[r] = nv[r]; k[r] = nx[r]; }
-            if (t + 1 < nt) { load_v(t + 1, nv); load_kernel(acc_kernel(a, t + 1), acc_group(a, t + 1), nx); }
-            transform(v, ex, std::integral_constant<int, -1>{});
+            load_v(t, v);   // in flight during the kernel's transform
+            take(acc_group(a, t), nx, k);
+            if (t + 1 < nt) load_kernel(acc_kernel(a, t + 1), acc_group(a, t + 1), nx);
             transform(k, ex, std::integral_constant<int, -1>{});
+            transform(v, ex, std::integral_constant<int, -1>{});
 #pragma unroll
             for (int r = 0; r < R1; ++r) acc[r] = cadd(acc[r], cmul(v[r], k[r]));
             if (t % a.nb == a.nb - 1) {   // end of a group: out += its sum, as separate launches would
-                if (ok)
+                if (ok) {
+                    float2 o[R1];   // read together: one after the other each waits for the last store
 #pragma unroll
-                    for (int r = 0; r < R1; ++r) {
-                        float2 *o = const_cast<float2 *>(elem(out0, r));
-                        *o = cadd(*o, acc[r]);
-                    }
+                    for (int r = 0; r < R1; ++r) o[r] = *const_cast<float2 *>(elem(out0, r));
+#pragma unroll
+                    for (int r = 0; r < R1; ++r) *const_cast<float2 *>(elem(out0, r)) = cadd(o[r], acc[r]);
+                }
 #pragma unroll
                 for (int r = 0; r < R1; ++r) acc[r] = make_float2(0.f, 0.f);
             }
@@ -439,11 +438,11 @@ __global__ __launch_bounds__(P * R2, MODE == 0 ? (R1 < 32 && 2 * KR < R1 ? 3 : 2
     for (int b = sh.b0; b < sh.b1; ++b) {
         float2 v[R1];
         if constexpr (PF) {
-#pragma unroll
-            for (int r = 0; r < R1; ++r) v[r] = nx[r];
+            take(kgrp, nx, v);
             if (b + 1 < sh.b1) load_kernel(kbase + b + 1, kgrp, nx);
         } else {
             load_kernel(kbase + b, kgrp, v);
+            take(kgrp, v, v);
         }
         transform(v, ex, std::integral_constant<int, -1>{});
 #pragma unroll
@@ -461,8 +460,9 @@ __global__ __launch_bounds__(P * R2, MODE == 0 ? (R1 < 32 && 2 * KR < R1 ? 3 : 2
 // pencil owns rows q + T s.  P adjacent pencils of the contiguous axes per workgroup.
 // KR as in axis0_reg_kernel: rows r <= KR and r >= R0 - KR of a thread are the only ones the
 // compact kernel support can reach (KR >= R0 / 2: all rows).
+// (the accumulation: two waves per SIMD, three where a compact kernel leaves the registers)
 template <int N, int P, int MODE, int KR, int R0, int... REST>
-__global__ __launch_bounds__(P * (N / R0)) void axis0_rs_kernel(Axis0Args a) {
+__global__ __launch_bounds__(P * (N / R0), MODE == 0 ? 1 : R0 < 20 && 2 * KR < R0 ? 3 : 2) void axis0_rs_kernel(Axis0Args a) {
     // field of the launch (grid.z); local pointers, so the argument struct is never written
     const float2 *dhat0 = a.dhat + (int64_t)blockIdx.z * a.dhat_fs;
     float2 *out0 = a.out + (int64_t)blockIdx.z * a.out_fs;
@@ -508,45 +508,53 @@ __global__ __launch_bounds__(P * (N / R0)) void axis0_rs_kernel(Axis0Args a) {
                                                            : make_float2(0.f, 0.f);
             } else {
                 const int p0 = up.pb > 0 ? up.pa + T * r : up.pa - T * r - (T - 1);   // lowest plane of the row
-                const float2 v = (ok && (j >= N - a.r0 || up.dense)) ? ld_stream(at_bytes(kc + (int64_t)p0 * a.plane, lane_hi))
-                                                                     : make_float2(0.f, 0.f);
-                dst[r] = make_float2(up.sx * v.x, up.sy * v.y);
+                dst[r] = (ok && (j >= N - a.r0 || up.dense)) ? ld_stream(at_bytes(kc + (int64_t)p0 * a.plane, lane_hi))
+                                                             : make_float2(0.f, 0.f);
             }
         }
     };
+    // the loaded rows with the sign or conjugation of the upper ones, taken where they are used: next
+    // to the loads it would wait for them, before the transforms that they are to overlap
+    auto take = [&](int grp, const float2 *src, float2 *dst) {
+        const UpperPlanes up(a.half, SB_MIRROR_RULE(a, grp), a.np, N);
+#pragma unroll
+        for (int r = 0; r < R0; ++r)
+            dst[r] = 2 * r < R0 || (r > KR && r < R0 - KR) ? src[r] : make_float2(up.sx * src[r].x, up.sy * src[r].y);
+    };
     float2 nx[R0];
     if constexpr (MODE == 1) {
-        // adjoint: out += sum_b FFT_0(v_b) FFT_0(kernel b); bin b + 1 loads during bin b
+        // adjoint: out += sum_b FFT_0(v_b) FFT_0(kernel b); v_b loads during its kernel's transform, and the
+        // next kernel during both
         auto load_v = [&](int b, float2 *dst) {
             const float2 *vb = a.vin + (int64_t)b * a.ng;
 #pragma unroll
             for (int r = 0; r < R0; ++r) dst[r] = ok ? *at_bytes(row(vb, r), lane_off) : make_float2(0.f, 0.f);
         };
-        float2 acc[R0], nv[R0];
+        float2 acc[R0];
 #pragma unroll
         for (int r = 0; r < R0; ++r) acc[r] = make_float2(0.f, 0.f);
         const int nt = (a.accgroups > 1 ? a.accgroups : 1) * a.nb;   // (group, bin) steps
-        load_v(0, nv);
         load_kernel(acc_kernel(a, 0), acc_group(a, 0), nx);
         __syncthreads();   // twiddle table
         for (int t = 0; t < nt; ++t) {
             float2 v[R0], k[R0];
-#pragma unroll
-            for (int r = 0; r < R0; ++r) { v[r] = nv[r]; k[r] = nx[r]; }
-            if (t + 1 < nt) { load_v(t + 1, nv); load_kernel(acc_kernel(a, t + 1), acc_group(a, t + 1), nx); }
+            load_v(t, v);   // in flight during the kernel's transform
+            take(acc_group(a, t), nx, k);
+            if (t + 1 < nt) load_kernel(acc_kernel(a, t + 1), acc_group(a, t + 1), nx);
             __syncthreads();   // the previous transform has read the buffer
-            reg_stages<N, -1, R0, REST...>(v, ex, ex, tw, q, p, PITCH);
-            __syncthreads();
             reg_stages<N, -1, R0, REST...>(k, ex, ex, tw, q, p, PITCH);
+            __syncthreads();
+            reg_stages<N, -1, R0, REST...>(v, ex, ex, tw, q, p, PITCH);
 #pragma unroll
             for (int r = 0; r < R0; ++r) acc[r] = cadd(acc[r], cmul(v[r], k[r]));
             if (t % a.nb == a.nb - 1) {   // end of a group: out += its sum, as separate launches would
-                if (ok)
+                if (ok) {
+                    float2 o[R0];   // read together: one after the other each waits for the last store
 #pragma unroll
-                    for (int r = 0; r < R0; ++r) {
-                        float2 *o = at_bytes(const_cast<float2 *>(row(out0, r)), lane_off);
-                        *o = cadd(*o, acc[r]);
-                    }
+                    for (int r = 0; r < R0; ++r) o[r] = *at_bytes(const_cast<float2 *>(row(out0, r)), lane_off);
+#pragma unroll
+                    for (int r = 0; r < R0; ++r) *at_bytes(const_cast<float2 *>(row(out0, r)), lane_off) = cadd(o[r], acc[r]);
+                }
 #pragma unroll
                 for (int r = 0; r < R0; ++r) acc[r] = make_float2(0.f, 0.f);
             }
@@ -564,8 +572,7 @@ __global__ __launch_bounds__(P * (N / R0)) void axis0_rs_kernel(Axis0Args a) {
     __syncthreads();   // twiddle table
     for (int b = sh.b0; b < sh.b1; ++b) {
         float2 v[R0];
-#pragma unroll
-        for (int r = 0; r < R0; ++r) v[r] = nx[r];
+        take(kgrp, nx, v);
         if (b + 1 < sh.b1) load_kernel(kbase + b + 1, kgrp, nx);   // in flight during the transforms
         __syncthreads();   // the previous transform has read the buffer
         reg_stages<N, -1, R0, REST...>(v, ex, ex, tw, q, p, PITCH);
@@ -855,7 +862,7 @@ hipError_t launch_fft_pass(const FftPass &a, hipStream_t s) {
     // (the register-resident kernels address a tile's n * stride elements by 32-bit byte offsets,
     // so those must span less than 4 GiB)
     const bool off32 = (int64_t)a.n * a.stride * (int64_t)sizeof(float2) <= (int64_t)UINT32_MAX;
-    if (v >= 6 && a.load == LOAD_C && a.store == STORE_C && a.stride > 1 && a.stride % 16 == 0 && off32) {
+    if (v >= 6 && a.load == LOAD_C && a.stride > 1 && a.stride % 16 == 0 && off32) {
         const bool x64 = v >= 8 && a.stride % 64 == 0;
         const bool wide = v != 7 && a.stride % 32 == 0;
         int tiles = v == 7 ? 16 : (v == 9 ? 4 : 8);
@@ -939,7 +946,7 @@ hipError_t launch_fft_pass(const FftPass &a, hipStream_t s) {
     }
     // variants 4 and 5: persistent with few, wide radix stages (64: 8 x 8, 96: 12 x 4 x 2,
     // 128: 16 x 8, 160: 20 x 4 x 2, 192: 12 x 4 x 4, 256: 16 x 16), 4 / 16 tiles
-    if (v >= 4 && a.load == LOAD_C && a.store == STORE_C) {
+    if (v >= 4 && a.load == LOAD_C) {
         const int tiles = v % 2 == 0 ? 4 : 16;
         if (a.n == 256) return launch_pf<256, 16, 256, 16, 16>(a, s, tiles);
         if (a.n == 128) return launch_pf<128, 8, 256, 16, 8>(a, s, tiles);
@@ -949,7 +956,7 @@ hipError_t launch_fft_pass(const FftPass &a, hipStream_t s) {
         if (a.n == 96) return launch_pf<96, 8, 256, 12, 4, 2>(a, s, tiles);
     }
     // variants 2 and 3: persistent passes with register prefetch (plain loads and stores only)
-    if (v >= 2 && a.load == LOAD_C && a.store == STORE_C) {
+    if (v >= 2 && a.load == LOAD_C) {
         const int tiles = v == 2 ? 4 : 16;
         switch (a.n) {
 #define SB_X(N, TPP, NT, ...) case N: return launch_pf<N, TPP, NT, __VA_ARGS__>(a, s, tiles);

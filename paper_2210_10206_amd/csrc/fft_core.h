@@ -4,9 +4,7 @@
 // arrays.  A workgroup owns P pencils: it stages them in LDS (coalesced: P
 // adjacent pencils along the fastest axis for a strided axis, P whole rows for
 // the contiguous axis), runs the radix stages in LDS with TPP threads per
-// pencil, and writes the tile back.  Loads can fuse the spectral product
-// (delta_hat * kernel_hat) or read a real field; stores can fuse a spectral
-// multiply-accumulate.  Twiddles come from a float64-computed table of the n-th
+// pencil, and writes the tile back.  Loads can read a real field.  Twiddles come from a float64-computed table of the n-th
 // roots of unity, so every twiddle is correctly rounded to float32.
 //
 // Stockham autosort (decimation in time): with the radices R_0..R_{S-1} and

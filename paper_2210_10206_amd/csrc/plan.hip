@@ -675,7 +675,7 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
 
 sb_status fft_axes(sb_plan *p, const int64_t *n, int ndim, int64_t ncell, const int *axes, int naxes, int sign,
                    int first_load, const void *in, int64_t in_bs, float2 *out, int64_t out_bs, int batch,
-                   hipStream_t s, int store, const float2 *mul, int64_t mul_bs, float2 *final_out) {
+                   hipStream_t s) {
     for (int i = 0; i < naxes; ++i) {
         const int d = axes[i];
         FftPass a{};
@@ -699,14 +699,8 @@ sb_status fft_axes(sb_plan *p, const int64_t *n, int ndim, int64_t ncell, const 
             a.in = out;
             a.in_bs = out_bs;
         }
-        const bool last = i == naxes - 1;
-        a.store = last ? store : STORE_C;
-        a.mul = mul;
-        a.mul_bs = mul_bs;
-        if (last && final_out) a.out = final_out;
         // algorithmic traffic: read + write of every transformed array
-        double bytes = 16.0 * (double)ncell * batch;
-        if (a.store == STORE_MACC) bytes += 16.0 * (double)ncell * batch;
+        const double bytes = 16.0 * (double)ncell * batch;
         const hipError_t e = p->timed_launch(STAGE_FFT, K_FFT, s, [&]() { return launch_fft_pass(a, s); }, a.n, sign,
                                              batch, bytes);
         if (e != hipSuccess) return hip_fail(e, "fft pass");

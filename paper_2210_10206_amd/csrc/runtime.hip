@@ -198,7 +198,6 @@ sb_status sb_autotune(sb_plan *p, void *stream, const char *cache_path) {
                 ps.ng = G.ng;
                 ps.sign = 1;
                 ps.load = LOAD_C;
-                ps.store = STORE_C;
                 ps.in = coef;
                 ps.out = coef;
                 ps.in_bs = ps.out_bs = G.ng;

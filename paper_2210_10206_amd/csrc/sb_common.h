@@ -41,13 +41,7 @@ __device__ __forceinline__ float2 *at_bytes(float2 *base, uint32_t bytes) {
 // extents); the pencils are g = 0 .. ng/n - 1 with base (g / stride) * n * stride + g % stride.
 enum FftLoad : int {
     LOAD_C = 0,        // complex float2 from in
-    LOAD_MUL = 1,      // in[idx] * in2[idx]           (spectral product)
-    LOAD_R32 = 2,      // real float  from in (imaginary part 0)
-    LOAD_R64 = 3       // real double from in
-};
-enum FftStore : int {
-    STORE_C = 0,       // out[idx] = value
-    STORE_MACC = 1     // out[idx] += value * mul[idx]   (spectral multiply-accumulate)
+    LOAD_R32 = 1       // real float from in (imaginary part 0)
 };
 
 struct FftPass {
@@ -56,12 +50,9 @@ struct FftPass {
     int64_t ng;        // cells per array
     int sign;          // -1 forward, +1 inverse (unnormalised)
     int load;          // FftLoad
-    int store;         // FftStore
     const void *in;    // input (batch stride in_bs elements)
-    const float2 *in2; // multiplier for LOAD_MUL (batch stride in2_bs)
     float2 *out;       // output (batch stride out_bs)
-    const float2 *mul; // multiplier for STORE_MACC (batch stride mul_bs)
-    int64_t in_bs, in2_bs, out_bs, mul_bs;
+    int64_t in_bs, out_bs;
     int batch;         // arrays transformed in one launch (grid.y)
     const float2 *tw;  // n roots of unity exp(-2 pi i j / n), float32 from float64
     int variant;       // launch-shape variant (autotuned)

@@ -241,11 +241,10 @@ sb_status check_finite(sb_plan *p, int count, const void *const *in, const int64
                        hipStream_t s);
 // FFT passes over the listed axes (in order) of arrays with extents n[0..ndim) and ncell
 // cells; the first pass reads `in` with load mode `first_load`, later passes work in place
-// on `out`; the last pass stores with `store` into final_out (or out).
+// on `out`.
 sb_status fft_axes(sb_plan *p, const int64_t *n, int ndim, int64_t ncell, const int *axes, int naxes, int sign,
                    int first_load, const void *in, int64_t in_bs, float2 *out, int64_t out_bs, int batch,
-                   hipStream_t s, int store = STORE_C, const float2 *mul = nullptr, int64_t mul_bs = 0,
-                   float2 *final_out = nullptr);
+                   hipStream_t s);
 sb_status fft_all_axes(sb_plan *p, const ShapeGroup &G, int sign, int first_load, const void *in, int64_t in_bs,
                        float2 *out, int64_t out_bs, int batch, hipStream_t s);
 }  // namespace sb
