@@ -18,7 +18,10 @@
 // h = G_{l_a} Re a - i G_{l_b} Im a.  D and v keep their form (w_m = 1), and since the packed
 // kernel is K_{l_a 0} + i K_{l_b 0}, 2 Re of its accumulation adds both fields' terms.
 #pragma once
+#include <type_traits>
+
 #include "fft_core.h"
+#include "sb_kgen.h"
 
 namespace sb {
 
@@ -31,8 +34,6 @@ struct AdjLastArgs {
     const float *w;         // density
     const double *gz;       // g_l (NB x NB)
     const double *gz2;      // packed groups: g_{l_b} for the imaginary parts (null: gz for both)
-    const float *gt;        // G_l as float, 16 x 16, zero beyond nb (register-resident form)
-    const float *gt2;       // packed groups: G_{l_b} likewise (null when gz2 is)
     float wm;               // 1 for m = 0, 2 for m > 0
     int nb;
     int64_t rows_per_block; // rows walked by one workgroup
@@ -42,6 +43,30 @@ struct AdjLastArgs {
     const float2 *tw;
 };
 hipError_t launch_adj_last(const AdjLastArgs &a, hipStream_t s);
+
+// The register-resident form: every group of a launch in turn for a pair of rows (x and its reflection).
+constexpr int kAdjGroups = kMaxLM;
+struct AdjRowsArgs {
+    int n;                  // last-axis length
+    int64_t n0, n1;         // the other extents
+    int64_t ng;
+    const float2 *in;       // [group][bin] arrays, transformed along every axis but the last
+    float2 *out;            // [group][bin] arrays: the reflected v; may start one group before in, whose
+                            // rows are then overwritten once their own pair has read them
+    const float *w;         // density
+    const float *gt;        // G_l of every l as float, 16 x 16 each, zero beyond nb
+    int nb;
+    int groups, npk;        // the first npk groups are packed
+    int l[kAdjGroups];      // l of a group; packed: l_a | l_b << 8; m > 0 (weight 2): + kAdjTwice
+    int64_t pairs;          // row pairs of the grid
+    int pairs_per_block;
+    int first;              // 1: D is written, 0: accumulated (later launches of a chunked plan)
+    float *dsum;            // D, one float per cell
+    const float2 *tw;
+};
+constexpr int kAdjTwice = 1 << 16;
+bool adj_rows_available(int n);
+hipError_t launch_adj_rows(const AdjRowsArgs &a, hipStream_t s);
 
 namespace adjlast {
 using namespace fftcore;
@@ -163,7 +188,10 @@ __global__ __launch_bounds__(NBT * R * TPP) void adj_last_kernel(AdjLastArgs a) 
 }
 
 // Register-resident form for the lengths with a radix list R0, REST... whose last radix
-// divides the first (reg_stages): a tile is one row of the NBT (padded) bins; thread q < T =
+// divides the first (reg_stages).  A workgroup takes pairs of reflected rows through every group of the
+// launch: D stays in registers, the density is read once, and no launch per group ends on idle
+// compute units.  The v of a group may go to the slot before its coefficients: the rows that it
+// overwrites there, the pair's own, were read for the previous group.  A tile is one row of the NBT (padded) bins; thread q < T =
 // N / R0 of pencil pp (= bin) holds elements q + T s of it, so the loads, both transforms and
 // the stores stay in registers and LDS is used for the stage exchanges and for the [cell][bin]
 // view of the per-cell phase.  The weights are read from the float table gt through the
@@ -184,11 +212,13 @@ __global__ __launch_bounds__(NBT * R * TPP) void adj_last_kernel(AdjLastArgs a) 
 // layout at 0.21 of the plain one's LDS cycles at 256 points, and the pass there runs 25 %
 // faster (8 bins: 9.8 -> 7.4 ms per 13 launches).  At 128 points (0.31 in the model) the time did
 // not move, and 64 and 160 points were slower with it, so the other lengths keep the plain layout.
+// waves per SIMD: three for the 256-point tiles of more than 8 bins, elsewhere what the registers give
+// (128 points, 8 bins: three waves spill 4 registers and take 1.42 ms where two take 1.14)
 constexpr int adj_rs_min_waves(int nstage, int nt) { return nstage == 2 && nt >= 192 ? 3 : 1; }
 
-template <int N, int NBT, bool PACK, int R0, int... REST>
+template <int N, int NBT, int R0, int... REST>
 __global__ __launch_bounds__(NBT * (N / R0), adj_rs_min_waves(1 + sizeof...(REST), NBT * (N / R0))) void adj_rs_kernel(
-    AdjLastArgs a) {
+    AdjRowsArgs a) {
     constexpr int T = N / R0;
     constexpr int P = NBT, PITCH = P + 1, NT = P * T;
     constexpr int SKEW = N == 256 ? 1 : 0, GSH = 4;   // layout above
@@ -203,92 +233,121 @@ __global__ __launch_bounds__(NBT * (N / R0), adj_rs_min_waves(1 + sizeof...(REST
     float2 *ex1 = ex[ONE ? 0 : 1];
     __shared__ float2 tw[N];
     typedef const __attribute__((address_space(4))) float cfloat;
-    cfloat *G = (cfloat *)a.gt;                   // 16 x 16, zero beyond nb
-    cfloat *G2 = PACK ? (cfloat *)a.gt2 : G;
     const int nb = a.nb;
     const int tid = threadIdx.x;
     const int q = tid % T, pp = tid / T;         // element column, pencil (= bin)
     for (int i = tid; i < N; i += NT) tw[i] = a.tw[i];
-    const int64_t nrows = a.ng / N;
-    const int64_t r_begin = (int64_t)blockIdx.x * a.rows_per_block;
-    const int64_t r_end = min(r_begin + a.rows_per_block, nrows);
     const bool live = pp < nb;
+    const int64_t gs = (int64_t)nb * a.ng;       // arrays of a group
     const float2 *in = a.in + (int64_t)(live ? pp : 0) * a.ng;
+    float2 *out = a.out + (int64_t)(live ? pp : 0) * a.ng;
     auto flip_row = [&](int64_t row) -> int64_t {
-        if (a.ndim == 3) {
-            const int64_t n1 = a.shape[1];
-            const int64_t i0 = row / n1, i1 = row % n1;
-            return ((a.shape[0] - i0) % a.shape[0]) * n1 + (n1 - i1) % n1;
-        }
-        return (a.shape[0] - row) % a.shape[0];
+        const int64_t i0 = row / a.n1, i1 = row % a.n1;
+        return (i0 ? a.n0 - i0 : 0) * a.n1 + (i1 ? a.n1 - i1 : 0);
     };
-    auto load_row = [&](int64_t row, float2 *x, float *wv, float *dv) {
-#pragma unroll
-        for (int r = 0; r < R0; ++r) x[r] = live ? ld_stream(&in[row * N + q + T * r]) : make_float2(0.f, 0.f);
-#pragma unroll
-        for (int k = 0; k < CPT; ++k) {
-            const int c = tid + k * NT;
-            wv[k] = c < N ? a.w[row * N + c] : 0.f;
-            dv[k] = (c < N && !a.first) ? a.dsum[row * N + c] : 0.f;
-        }
+    // lower row of pair t: the rows of 0 < i0 < n0 / 2, then those of i0 = 0 and n0 / 2 up to i1 = n1 / 2
+    // (the extents are even)
+    auto pair_row = [&](int64_t t) -> int64_t {
+        const int64_t inner = (a.n0 / 2 - 1) * a.n1, half = a.n1 / 2 + 1;
+        if (t < inner) return a.n1 + t;
+        const int64_t u = t - inner;
+        return u < half ? u : a.n0 / 2 * a.n1 + (u - half);
     };
+    auto load_row = [&](int g, int64_t row, float2 *x) {
+        const float2 *src = in + g * gs + row * N;
+#pragma unroll
+        for (int r = 0; r < R0; ++r) x[r] = live ? ld_stream(&src[q + T * r]) : make_float2(0.f, 0.f);
+    };
+    const int64_t t0 = (int64_t)blockIdx.x * a.pairs_per_block;
+    const int64_t t1 = min(t0 + a.pairs_per_block, a.pairs);
     float2 nx[R0];
-    float nw[CPT], nd[CPT];
-    if (r_begin < r_end) load_row(r_begin, nx, nw, nd);
-    for (int64_t row = r_begin; row < r_end; ++row) {
-        float2 v[R0];
-        float cw[CPT], cd[CPT];
+    if (t0 < t1) load_row(0, pair_row(t0), nx);
+    for (int64_t t = t0; t < t1; ++t) {
+        const int64_t rlo = pair_row(t), rhi = flip_row(rlo);
+        const int nrow = rhi == rlo ? 1 : 2;
+        float cw[2][CPT], cd[2][CPT];            // weights and D of the pair's rows
 #pragma unroll
-        for (int r = 0; r < R0; ++r) v[r] = nx[r];
+        for (int y = 0; y < 2; ++y)
 #pragma unroll
-        for (int k = 0; k < CPT; ++k) { cw[k] = nw[k]; cd[k] = nd[k]; }
-        if (row + 1 < r_end) load_row(row + 1, nx, nw, nd);   // next row in flight
-        __syncthreads();                                       // the previous row's buffers are free
-        reg_stages<N, 1, R0, REST...>(v, ex[0], ex1, tw, q, pp, PITCH, SKEW, GSH);   // inverse
-        float2 *cs = ex[CSB];
-        if constexpr (ONE) __syncthreads();   // the last stage has read the exchange buffer
+            for (int k = 0; k < CPT; ++k) {
+                const int c = tid + k * NT;
+                const int64_t cell = (y ? rhi : rlo) * N + c;
+                cw[y][k] = c < N ? a.w[cell] : 0.f;
+                cd[y][k] = c < N && !a.first ? a.dsum[cell] : 0.f;
+            }
+        for (int g = 0; g < a.groups; ++g) {
+            const int lw = a.l[g];
+            const float wm = lw & kAdjTwice ? 2.f : 1.f;
+            cfloat *G = (cfloat *)(a.gt + (lw & 255) * 256), *G2 = (cfloat *)(a.gt + (lw >> 8 & 255) * 256);
+            for (int y = 0; y < nrow; ++y) {
+                float2 v[R0];
 #pragma unroll
-        for (int r = 0; r < R0; ++r) cs[at(q + T * r, pp)] = v[r];
-        __syncthreads();
-        // per cell: h = G conj(a), the direct term and v = w_m delta h (whole cells per thread)
+                for (int r = 0; r < R0; ++r) v[r] = nx[r];
+                // the next row of this pair, group or pair in flight
+                if (y + 1 < nrow) load_row(g, rhi, nx);
+                else if (g + 1 < a.groups) load_row(g + 1, rlo, nx);
+                else if (t + 1 < t1) load_row(0, pair_row(t + 1), nx);
+                __syncthreads();                                       // the previous row's buffers are free
+                reg_stages<N, 1, R0, REST...>(v, ex[0], ex1, tw, q, pp, PITCH, SKEW, GSH);   // inverse
+                float2 *cs = ex[CSB];
+                if constexpr (ONE) __syncthreads();   // the last stage has read the exchange buffer
 #pragma unroll
-        for (int k = 0; k < CPT; ++k) {
-            const int c = tid + k * NT;
-            if (c >= N) continue;
-            float2 av[NBT];
+                for (int r = 0; r < R0; ++r) cs[at(q + T * r, pp)] = v[r];
+                __syncthreads();
+                // per cell: h = G conj(a), the direct term and v = w_m delta h (whole cells per thread)
+                auto cells = [&](auto pack_c) {
+                    constexpr bool PACK = decltype(pack_c)::value;
 #pragma unroll
-            for (int b = 0; b < NBT; ++b) av[b] = cs[at(c, b)];
-            const float dw = a.wm * cw[k];
-            float d = 0.f;
+                    for (int k = 0; k < CPT; ++k) {
+                        const int c = tid + k * NT;
+                        if (c >= N) continue;
+                        float2 av[NBT];
 #pragma unroll
-            for (int b1 = 0; b1 < NBT; ++b1) {
-                float hx = 0.f, hy = 0.f;
+                        for (int b = 0; b < NBT; ++b) av[b] = cs[at(c, b)];
+                        const float dw = wm * (y ? cw[1][k] : cw[0][k]);
+                        float d = 0.f;
 #pragma unroll
-                for (int b2 = 0; b2 < NBT; ++b2) {
-                    const float g = G[b1 * 16 + b2];
-                    const float g2 = PACK ? G2[b1 * 16 + b2] : g;
-                    hx = __builtin_fmaf(g, av[b2].x, hx);
-                    hy = __builtin_fmaf(-g2, av[b2].y, hy);   // conj(a)
+                        for (int b1 = 0; b1 < NBT; ++b1) {
+                            float hx = 0.f, hy = 0.f;
+#pragma unroll
+                            for (int b2 = 0; b2 < NBT; ++b2) {
+                                const float gv = G[b1 * 16 + b2];
+                                const float g2 = PACK ? G2[b1 * 16 + b2] : gv;
+                                hx = __builtin_fmaf(gv, av[b2].x, hx);
+                                hy = __builtin_fmaf(-g2, av[b2].y, hy);   // conj(a)
+                            }
+                            d = __builtin_fmaf(av[b1].x, hx, d);
+                            d = __builtin_fmaf(-av[b1].y, hy, d);
+                            cs[at(c, b1)] = make_float2(dw * hx, dw * hy);
+                        }
+                        if (y) cd[1][k] += wm * d;
+                        else cd[0][k] += wm * d;
+                    }
+                };
+                if (g < a.npk) cells(std::true_type{});
+                else cells(std::false_type{});
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < R0; ++r) v[r] = cs[at(q + T * r, pp)];
+                __syncthreads();                                       // cs may be the first exchange buffer
+                reg_stages<N, -1, R0, REST...>(v, ex[0], ex1, tw, q, pp, PITCH, SKEW, GSH);  // forward
+                if (live) {
+                    float2 *dst = out + g * gs + (y ? rlo : rhi) * N;   // the reflected row
+#pragma unroll
+                    for (int r = 0; r < R0; ++r) {
+                        const int k = q + T * r;
+                        st_stream(&dst[(N - k) % N], v[r]);
+                    }
                 }
-                d = __builtin_fmaf(av[b1].x, hx, d);
-                d = __builtin_fmaf(-av[b1].y, hy, d);
-                cs[at(c, b1)] = make_float2(dw * hx, dw * hy);
-            }
-            a.dsum[row * N + c] = cd[k] + a.wm * d;   // cd = 0 on the first group
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < R0; ++r) v[r] = cs[at(q + T * r, pp)];
-        __syncthreads();                                       // cs may be the first exchange buffer
-        reg_stages<N, -1, R0, REST...>(v, ex[0], ex1, tw, q, pp, PITCH, SKEW, GSH);  // forward
-        if (live) {
-            float2 *out = a.out + (int64_t)pp * a.ng + flip_row(row) * N;
-#pragma unroll
-            for (int r = 0; r < R0; ++r) {
-                const int k = q + T * r;
-                st_stream(&out[(N - k) % N], v[r]);
             }
         }
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) {
+                const int c = tid + k * NT;
+                if (c < N && y < nrow) a.dsum[(y ? rhi : rlo) * N + c] = cd[y][k];
+            }
     }
 }
 
@@ -300,19 +359,17 @@ constexpr int rs_padded_bins(int nb, int t) {
 }
 
 template <int N, int R0, int... REST>
-hipError_t launch_rs(const AdjLastArgs &a, hipStream_t s) {
+hipError_t launch_rs(const AdjRowsArgs &a, hipStream_t s) {
     constexpr int T = N / R0;
-    const int64_t nrows = a.ng / N;
-    dim3 grid((unsigned)((nrows + a.rows_per_block - 1) / a.rows_per_block));
+    dim3 grid((unsigned)((a.pairs + a.pairs_per_block - 1) / a.pairs_per_block));
     switch (rs_padded_bins(a.nb, T)) {
-#define SB_AR(NBT)                                                                               \
-    case NBT:                                                                                    \
-        if constexpr ((NBT * T) % 64 == 0 && NBT * T <= 1024) {                                  \
-            if (a.gz2) hipLaunchKernelGGL((adj_rs_kernel<N, NBT, true, R0, REST...>), grid, dim3(NBT * T), 0, s, a);  \
-            else hipLaunchKernelGGL((adj_rs_kernel<N, NBT, false, R0, REST...>), grid, dim3(NBT * T), 0, s, a); \
-            return hipGetLastError();                                                            \
-        } else {                                                                                 \
-            return hipErrorInvalidValue;                                                         \
+#define SB_AR(NBT)                                                                                                \
+    case NBT:                                                                                                     \
+        if constexpr ((NBT * T) % 64 == 0 && NBT * T <= 1024) {                                                   \
+            hipLaunchKernelGGL((adj_rs_kernel<N, NBT, R0, REST...>), grid, dim3(NBT * T), 0, s, a);               \
+            return hipGetLastError();                                                                             \
+        } else {                                                                                                  \
+            return hipErrorInvalidValue;                                                                          \
         }
         SB_AR(4) SB_AR(8) SB_AR(12) SB_AR(16)
 #undef SB_AR

@@ -91,20 +91,25 @@ __global__ void zero_c_kernel(float2 *x, int64_t n) {
 
 }  // namespace
 
-hipError_t launch_adj_last(const AdjLastArgs &a, hipStream_t s) {
-    // register-resident stages where the radix list allows (the forward fused pass uses the same
-    // lists), the LDS-staged tile kernel otherwise
-    hipError_t e = hipErrorInvalidValue;
+// Register-resident rows for the lengths with a radix list (those of the forward fused pass), the
+// LDS-staged tiles of launch_adj_last for the others.
+bool adj_rows_available(int n) {
+    return n == 64 || n == 96 || n == 128 || n == 160 || n == 192 || n == 256;
+}
+
+hipError_t launch_adj_rows(const AdjRowsArgs &a, hipStream_t s) {
     switch (a.n) {
-        case 64: e = adjlast::launch_rs<64, 8, 8>(a, s); break;
-        case 96: e = adjlast::launch_rs<96, 12, 4, 2>(a, s); break;
-        case 128: e = adjlast::launch_rs<128, 16, 8>(a, s); break;
-        case 160: e = adjlast::launch_rs<160, 20, 4, 2>(a, s); break;
-        case 192: e = adjlast::launch_rs<192, 12, 4, 4>(a, s); break;
-        case 256: e = adjlast::launch_rs<256, 16, 16>(a, s); break;
-        default: break;
+        case 64: return adjlast::launch_rs<64, 8, 8>(a, s);
+        case 96: return adjlast::launch_rs<96, 12, 4, 2>(a, s);
+        case 128: return adjlast::launch_rs<128, 16, 8>(a, s);
+        case 160: return adjlast::launch_rs<160, 20, 4, 2>(a, s);
+        case 192: return adjlast::launch_rs<192, 12, 4, 4>(a, s);
+        case 256: return adjlast::launch_rs<256, 16, 16>(a, s);
+        default: return hipErrorInvalidValue;
     }
-    if (e == hipSuccess) return e;
+}
+
+hipError_t launch_adj_last(const AdjLastArgs &a, hipStream_t s) {
     switch (a.n) {   // (none at 1024: a tile of every bin of a row would not fit the LDS)
 #define SB_X(N, TPP, ...)                                                             \
     case N:                                                                           \
@@ -228,7 +233,35 @@ sb_status backward(sb_plan *p, const void *const *delta, const double *grad_zeta
                 // the v arrays going to a region of their own.
                 float2 *vbase = use_kept ? reinterpret_cast<float2 *>(p->scratch + p->off_vkeep)
                                          : coef_w - (int64_t)NB * G.ng;
-                for (int g = g0; g < g0 + ngr; ++g) {
+                if (adj_rows_available((int)G.n[2])) {
+                    AdjRowsArgs a{};
+                    a.n = (int)G.n[2];
+                    a.n0 = G.n[0];
+                    a.n1 = G.n[1];
+                    a.ng = G.ng;
+                    a.in = cf;
+                    a.out = vbase;
+                    a.w = w;
+                    a.gt = gtab;
+                    a.nb = NB;
+                    a.groups = ngr;
+                    for (int g = g0; g < g0 + ngr; ++g) {
+                        int m = 0, l2 = -1;
+                        const int l = group_l(g, &m, &l2);
+                        a.l[g - g0] = l | (l2 >= 0 ? l2 << 8 : 0) | (m > 0 ? kAdjTwice : 0);
+                        if (l2 >= 0) a.npk = g - g0 + 1;
+                    }
+                    // about 16 rows a workgroup, fewer where that leaves under 4096 workgroups
+                    a.pairs = G.n[0] * G.n[1] / 2 + 2;
+                    a.pairs_per_block = (int)std::max<int64_t>(1, std::min<int64_t>(8 / ngr, a.pairs / 4096));
+                    a.first = g0 == 0;
+                    a.dsum = dsum;
+                    a.tw = p->tw.at(a.n);
+                    e = p->timed_launch(STAGE_OTHER, K_ADJPREP, s, [&]() { return launch_adj_rows(a, s); }, a.n, 0, ngr * NB,
+                                        16.0 * ngr * NB * G.ng + 8.0 * G.ng);
+                    if (e != hipSuccess) return hip_fail(e, "adjoint fused last pass");
+                }
+                for (int g = adj_rows_available((int)G.n[2]) ? g0 + ngr : g0; g < g0 + ngr; ++g) {
                     int m = 0, l2 = -1;
                     const int l = group_l(g, &m, &l2);
                     AdjLastArgs a{};
@@ -240,8 +273,6 @@ sb_status backward(sb_plan *p, const void *const *delta, const double *grad_zeta
                     a.w = w;
                     a.gz = gz_f + (int64_t)l * NB * NB;
                     a.gz2 = l2 >= 0 ? gz_f + (int64_t)l2 * NB * NB : nullptr;
-                    a.gt = gtab + (int64_t)l * 256;
-                    a.gt2 = l2 >= 0 ? gtab + (int64_t)l2 * 256 : nullptr;
                     a.wm = m == 0 ? 1.f : 2.f;
                     a.nb = NB;
                     const int64_t nrows = G.ng / a.n;

@@ -279,19 +279,28 @@ __global__ void gather_kernel(const double *src, const int *ptr, const int *idx,
     out[i] = s;
 }
 
-// block_sum_kernel and gather_kernel in one, a wave per output value: the sums in the same order.
-__global__ __launch_bounds__(64) void sum_gather_kernel(const double *partial, int64_t part_fs, int nblocks, const int *ptr,
-                                                        const int *idx, const double *coef, GatherOut out) {
-    const int i = blockIdx.x, f = blockIdx.y;
+// block_sum_kernel and gather_kernel in one, a workgroup per output value, its waves over the terms:
+// the sums in the same order (a term's over the blocks, then the terms).
+__global__ __launch_bounds__(256) void sum_gather_kernel(const double *partial, int64_t part_fs, int nblocks, const int *ptr,
+                                                         const int *idx, const double *coef, GatherOut out) {
+    __shared__ double term[kMaxGatherTerms];
+    const int i = blockIdx.x, f = blockIdx.y, lane = threadIdx.x & 63;
     const double *pf = partial + f * part_fs;
-    double s = 0.0;
-    for (int t = ptr[i]; t < ptr[i + 1]; ++t) {
-        const double *p = pf + (int64_t)idx[t] * nblocks;
+    const int t0 = ptr[i], nt = ptr[i + 1] - t0;
+    for (int t = threadIdx.x >> 6; t < nt; t += 4) {
+        const double *p = pf + (int64_t)idx[t0 + t] * nblocks;
         double v = 0.0;
-        for (int b = threadIdx.x; b < nblocks; b += 64) v += p[b];
-        s += coef[t] * wave_sum(v);
+#pragma unroll 8
+        for (int b = lane; b < nblocks; b += 64) v += p[b];
+        v = wave_sum(v);
+        if (lane == 0) term[t] = coef[t0 + t] * v;
     }
-    if (threadIdx.x == 0) out.z[f][i] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int t = 0; t < nt; ++t) s += term[t];
+        out.z[f][i] = s;
+    }
 }
 
 __global__ void to_f32_kernel(const void *in, int dtype, int64_t n, float *out) {
@@ -430,7 +439,7 @@ hipError_t launch_block_sum(const double *partial, int nf, int rows, int nblocks
 
 hipError_t launch_sum_gather(const double *partial, int64_t part_fs, int nblocks, const int *ptr, const int *idx,
                              const double *coef, int nout, const GatherOut &out, int fields, hipStream_t s) {
-    hipLaunchKernelGGL(sum_gather_kernel, dim3((unsigned)nout, (unsigned)fields), dim3(64), 0, s, partial, part_fs, nblocks,
+    hipLaunchKernelGGL(sum_gather_kernel, dim3((unsigned)nout, (unsigned)fields), dim3(256), 0, s, partial, part_fs, nblocks,
                        ptr, idx, coef, out);
     return hipGetLastError();
 }

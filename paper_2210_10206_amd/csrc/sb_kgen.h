@@ -164,6 +164,7 @@ hipError_t launch_gather(const double *src, const int *ptr, const int *idx, cons
 
 // ---- both at once for up to kGatherFields fields: field f's partials at partial + f part_fs, out to z[f]
 constexpr int kGatherFields = 16;
+constexpr int kMaxGatherTerms = kMaxL + 1;   // the (l, m >= 0) terms of a 3PCF value; the others have one
 struct GatherOut {
     double *z[kGatherFields];
 };
