@@ -390,6 +390,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 template <int R1, int R2> constexpr int reg_region(bool split) {
     return pencil_region(R2 * (R1 + 1), split ? R1 * R2 + 8 : R1 * R2);
 }
+// Whether the next row has registers of its own (see last_reg_body).
+constexpr bool reg_prefetch(int n, int nbt, bool cplx) { return cplx || n < 128 || nbt > 12; }
 template <int R1, int R2, int NBT, int MODE, int PREC>
 __device__ __forceinline__ void last_reg_body(const LastArgs &a, float2 *lds, float2 *twl, float *wsm) {
     using PS = PairSums<NBT, MODE, PREC>;
@@ -435,20 +437,28 @@ __device__ __forceinline__ void last_reg_body(const LastArgs &a, float2 *lds, fl
             wdst[e] = c < N ? a.w[row * N + c] : 0.f;
         }
     };
-    float2 nx[R1];
-    float nw[WPT];
-    if (r_begin < r_end) load_row(r_begin, nx, nw);
+    // PF: the next row loads into registers of its own during this one, else into the row's own ones
+    // during its pair sums.  With a region per live bin that leaves five or six waves per SIMD where
+    // prefetch registers leave four: 256^3, 10 bins, 25 groups 7.54 -> 7.25 ms; at 128 points the same
+    constexpr bool PF = reg_prefetch(N, NBT, MODE == PS_COMPLEX);
+    float2 nx[PF ? R1 : 1], v[R1];
+    float nw[PF ? WPT : 1], wv[WPT];
+    if (r_begin < r_end) {
+        if constexpr (PF) load_row(r_begin, nx, nw);
+        else load_row(r_begin, v, wv);
+    }
     for (int64_t row = r_begin; row < r_end; ++row) {
-        float2 v[R1];
+        if constexpr (PF) {
 #pragma unroll
-        for (int r = 0; r < R1; ++r) v[r] = nx[r];
-        float wv[WPT];
+            for (int r = 0; r < R1; ++r) v[r] = nx[r];
 #pragma unroll
-        for (int e = 0; e < WPT; ++e) wv[e] = nw[e];
-        if (row + 1 < r_end) load_row(row + 1, nx, nw);    // next row in flight
+            for (int e = 0; e < WPT; ++e) wv[e] = nw[e];
+            if (row + 1 < r_end) load_row(row + 1, nx, nw);    // next row in flight
+        }
         // first stage: radix-R1 butterfly q (elements q + R2 s) -> row q of the exchange
         Dft<R1, 1>::run(v);
         __syncthreads();                                    // the previous tile's pair sums are done
+        if (live) {
 #pragma unroll
         for (int r = 0; r < R1; ++r) own[q * EXR + r] = v[r];
         wave_lds_sync();
@@ -484,19 +494,21 @@ __device__ __forceinline__ void last_reg_body(const LastArgs &a, float2 *lds, fl
 #pragma unroll
                 for (int r = 0; r < R2; ++r) own[q + R2 * t + R1 * r] = v[t * R2 + r];
         }
+        }
 #pragma unroll
         for (int e = 0; e < WPT; ++e)
             if (tid + e * NT < N) wsm[tid + e * NT] = wv[e];
         __syncthreads();
+        if constexpr (!PF)
+            if (row + 1 < r_end) load_row(row + 1, v, wv);
         if constexpr (SPLIT)
-            ps.template accumulate<N, NW, PLANE>(lds, 2 * REG, wsm, [](int c) { return c; }, wave, lane);
+            ps.template accumulate<N, NW, PLANE>(lds, 2 * REG, wsm, [](int c) { return c; }, wave, lane, nb);
         else
-            ps.template accumulate<N, NW>(lds, REG, wsm, [](int c) { return c; }, wave, lane);
+            ps.template accumulate<N, NW>(lds, REG, wsm, [](int c) { return c; }, wave, lane, nb);
         if ((row - r_begin) % FLUSH == FLUSH - 1 || row + 1 == r_end) ps.flush(lane);
     }
     // float64 combine over the waves in wave order (as in last_contract_kernel)
     __syncthreads();
-    static_assert(PS::red_doubles(NW) * sizeof(double) <= P * REG * sizeof(float2), "block reduction fits");
     double *red = reinterpret_cast<double *>(lds);   // [wave][part][quad pair][4 x 4]
     ps.to_lds(red, wave, lane);
     __syncthreads();
@@ -507,8 +519,8 @@ __device__ __forceinline__ void last_reg_body(const LastArgs &a, float2 *lds, fl
 }
 
 template <int R1, int R2, int NBT, bool CPLX, int PREC>
-__global__ __launch_bounds__(NBT * R2, NBT <= 12 ? 4 : 3) void last_reg_kernel(LastArgs a) {
-    __shared__ float2 lds[NBT * reg_region<R1, R2>(!CPLX)];
+__global__ __launch_bounds__(NBT * R2, !reg_prefetch(R1 * R2, NBT, CPLX) ? 5 : NBT <= 12 ? 4 : 3) void last_reg_kernel(LastArgs a) {
+    extern __shared__ float2 lds[];        // one region per bin (dead pencils have none)
     __shared__ float2 twl[R1 * R2];
     __shared__ float wsm[R1 * R2];
 #define SB_BODY(M) last_reg_body<R1, R2, NBT, M, PREC>
@@ -528,16 +540,23 @@ template <int R1, int R2, int PREC>
 hipError_t launch_last_reg_p(const LastArgs &a, hipStream_t s) {
     dim3 grid((unsigned)a.nblocks, (unsigned)a.groups, (unsigned)(a.fields > 1 ? a.fields : 1));
     const int nbt = reg_padded_bins(a.nb, R2);
-#define SB_LR(NBT)                                                                                               \
-    case NBT:                                                                                                     \
-        if constexpr ((NBT * R2) % 64 == 0) {                                                                     \
-            if (a.want_imag)                                                                                      \
-                hipLaunchKernelGGL((last_reg_kernel<R1, R2, NBT, true, PREC>), grid, dim3(NBT * R2), 0, s, a);    \
-            else                                                                                                  \
-                hipLaunchKernelGGL((last_reg_kernel<R1, R2, NBT, false, PREC>), grid, dim3(NBT * R2), 0, s, a);   \
-            break;                                                                                                \
-        } else {                                                                                                  \
-            return hipErrorInvalidValue;                                                                          \
+    auto shm = [&](auto nbt_c) -> size_t {
+        constexpr int NW = decltype(nbt_c)::value * R2 / 64;
+        constexpr int red = std::max(PairSums<decltype(nbt_c)::value, PS_PACKED, PREC>::red_doubles(NW),
+                                     PairSums<decltype(nbt_c)::value, PS_COMPLEX, PREC>::red_doubles(NW));
+        return std::max<size_t>((size_t)a.nb * reg_region<R1, R2>(!a.want_imag) * sizeof(float2), red * sizeof(double));
+    };
+#define SB_LR(NBT)                                                                                                \
+    case NBT:                                                                                                      \
+        if constexpr ((NBT * R2) % 64 == 0) {                                                                      \
+            const size_t lds = shm(std::integral_constant<int, NBT>{});                                            \
+            if (a.want_imag)                                                                                       \
+                hipLaunchKernelGGL((last_reg_kernel<R1, R2, NBT, true, PREC>), grid, dim3(NBT * R2), lds, s, a);   \
+            else                                                                                                   \
+                hipLaunchKernelGGL((last_reg_kernel<R1, R2, NBT, false, PREC>), grid, dim3(NBT * R2), lds, s, a);  \
+            break;                                                                                                 \
+        } else {                                                                                                   \
+            return hipErrorInvalidValue;                                                                           \
         }
     switch (nbt) {
         SB_LR(4) SB_LR(8) SB_LR(12) SB_LR(16)
@@ -625,8 +644,8 @@ template <int N> constexpr int row_region(bool split) {
 // a few registers (16 bins with the complex sums hold 80 accumulators).
 constexpr int rs_waves(int n, int nbt, bool cplx) {
     if (n >= 1024) return 1;
-    if (nbt > 12) return cplx ? 2 : n == 160 ? 3 : 4;
-    return n == 96 || (n == 512 && nbt <= 8) ? 4 : 3;
+    if (cplx) return nbt > 12 ? 2 : n == 96 || (n == 512 && nbt <= 8) ? 4 : 3;
+    return n == 160 || (n == 512 && nbt == 12) ? 3 : n == 96 && nbt == 8 ? 5 : 4;
 }
 
 // Register-resident form for the three-stage radix lists R0, ... (the last radix divides R0): a tile
@@ -673,11 +692,11 @@ __device__ __forceinline__ void last_rs_body(const LastArgs &a, float2 *lds, flo
             wdst[e] = c < N ? a.w[row * N + c] : 0.f;
         }
     };
-    // PF: the next row's loads are in flight during this row.  From 512 points on its registers would
-    // cost a wave per SIMD (512^3, 6 bins: 26.6 ms against 21.6), so there the next row loads into the
-    // row's own registers once they are stored to LDS, its loads in flight during the pair sums; the
-    // complex sums of more than 8 bins at 512 hold too many registers for that wave anyway.
-    constexpr bool PF = N < 512 || (N == 512 && NBT > 8 && MODE == PS_COMPLEX);
+    // PF: the next row's loads are in flight during this row.  Its registers cost a wave per SIMD (512^3,
+    // 6 bins: 26.6 ms against 21.6; 192^3, 8 bins 1.40 against 1.27), so without it the next row loads
+    // into the row's own registers once they are stored to LDS, in flight during the pair sums; the
+    // complex sums hold too many registers for that wave anyway.
+    constexpr bool PF = MODE == PS_COMPLEX && (N < 512 || (N == 512 && NBT > 8));
     float2 nx[PF ? R0 : 1];
     float nw[PF ? WPT : 1];
     float2 v[R0];

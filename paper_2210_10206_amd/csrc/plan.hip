@@ -641,8 +641,11 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
         G.rows = NB <= kMaxBins ? fused_last_rows(nl, NB) : 0;
         if (G.rows > 0) {
             const int64_t nrows = G.ng / nl;
+            // at most about 1024 workgroups a group, of 16 rows or more; fewer rows where the groups
+            // together would not make 2048 workgroups (512^2, 11 groups: 352 of 16 rows)
+            const int nag = p->npack > 0 ? p->nag : p->nlm;
             int64_t rpb = (nrows + 1023) / 1024;
-            rpb = std::max<int64_t>(rpb, 16);
+            rpb = std::max<int64_t>(rpb, std::min<int64_t>(16, std::max<int64_t>(4, nrows * nag / 2048)));
             rpb = (rpb + G.rows - 1) / G.rows * G.rows;
             G.rows_per_block = rpb;
         }
