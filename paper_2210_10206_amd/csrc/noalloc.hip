@@ -9,7 +9,6 @@
 namespace sb {
 namespace {
 
-constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;   // 64 MiB per device
 constexpr int kMaxDevices = 64;
 
 // The working arrays of sb_forward_noalloc (one copy per device, held until the process ends).

@@ -142,11 +142,11 @@ static sb_status build_gather(sb_plan *p, std::vector<int> &gptr, std::vector<in
 // (cpb, 0: the plan's current choice), halved for the 4PCFs while the launch would have under 1024
 // workgroups (a launch of the full 4PCF covers one Lambda, one of the projected 4PCF every triple),
 // down to two of the 64-cell tiles that its kernels stage, or one where that leaves under 128.  A
-// 32^3 grid is 32 workgroups of 1024 cells for 256 compute units.  Depends on the grid alone, so that a field's sums do not depend
-// on the batch.
+// 32^3 grid is 32 workgroups of 1024 cells for 256 compute units.  Depends on the grid alone, so
+// that a field's sums do not depend on the batch, except where layout_scratch sets coarse_parts.
 static int contract_cells(const sb_plan *p, int64_t ng, int cpb = 0) {
     if (cpb == 0) cpb = p->contract_tile();
-    if (p->prob.npcf == 3) return cpb;
+    if (p->prob.npcf == 3 || p->coarse_parts) return cpb;
     const int64_t per = p->prob.ndim == 3 ? 1 : (int64_t)p->p4_canon.size();
     while ((cpb > 128 && (ng + cpb - 1) / cpb * per < 1024) || (cpb > 64 && (ng + cpb - 1) / cpb * per < 128)) cpb /= 2;
     return cpb;
@@ -169,10 +169,37 @@ static void contraction_shape(const sb_plan *p, int64_t ng, int *groups, int *nv
 }
 
 
+// Rows per workgroup of the fused last pass: at most about 1024 workgroups a group, of 16 rows or
+// more; fewer rows where the groups together would not make 2048 workgroups (512^2, 11 groups: 352
+// of 16 rows).
+static int64_t last_rows(const sb_plan *p, const ShapeGroup &G) {
+    const int64_t nrows = G.ng / G.n[p->prob.ndim - 1];
+    const int nag = p->npack > 0 ? p->nag : p->nlm;
+    const int64_t least = p->coarse_parts ? 16 : std::min<int64_t>(16, std::max<int64_t>(4, nrows * nag / 2048));
+    const int64_t rpb = std::max<int64_t>((nrows + 1023) / 1024, least);
+    return (rpb + G.rows - 1) / G.rows * G.rows;
+}
+
+static void layout_scratch_parts(sb_plan *p);
+
+// The shorter tiles and rows of short grids (contract_cells, last_rows) write more partials.  A plan
+// that fits the scratch of sb_forward_noalloc only without them goes without: 4PCF, 32^3, 10 bins,
+// lmax = 4 needs 66 MiB with 256 workgroups a launch and 45 MiB with 64.
+void layout_scratch(sb_plan *p) {
+    p->coarse_parts = false;
+    layout_scratch_parts(p);
+    if (p->scratch_need <= kNoAllocScratchBytes) return;
+    p->coarse_parts = true;
+    layout_scratch_parts(p);
+    if (p->scratch_need <= kNoAllocScratchBytes) return;
+    p->coarse_parts = false;
+    layout_scratch_parts(p);
+}
+
 // Scratch layout.  A 3PCF plan whose full set of kernel arrays exceeds coef_limit runs its
 // passes over chunks of kernel groups (the fused contraction and the adjoint only need one
 // group's bins at a time); every other plan keeps all arrays at once.
-void layout_scratch(sb_plan *p) {
+static void layout_scratch_parts(sb_plan *p) {
     const sb_problem *prob = &p->prob;
     const int NB = prob->nbins;
     const uint64_t per_group = (uint64_t)NB * p->max_ng * sizeof(float2);
@@ -228,6 +255,8 @@ void layout_scratch(sb_plan *p) {
         contraction_shape(p, G.ng, &groups, &nvals, &nb, tile_lo);
         nblocks = std::max(nblocks, nb);
     }
+    for (auto &G : p->groups)
+        if (G.rows > 0) G.rows_per_block = last_rows(p, G);
     for (const auto &G : p->groups)
         if (G.rows > 0 && prob->npcf == 3) {
             const int64_t nrows = G.ng / G.n[prob->ndim - 1];
@@ -639,16 +668,6 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
         // fused last pass: rows per tile fixed by the kernel's compile-time tile shape
         const int nl = (int)G.n[prob->ndim - 1];
         G.rows = NB <= kMaxBins ? fused_last_rows(nl, NB) : 0;
-        if (G.rows > 0) {
-            const int64_t nrows = G.ng / nl;
-            // at most about 1024 workgroups a group, of 16 rows or more; fewer rows where the groups
-            // together would not make 2048 workgroups (512^2, 11 groups: 352 of 16 rows)
-            const int nag = p->npack > 0 ? p->nag : p->nlm;
-            int64_t rpb = (nrows + 1023) / 1024;
-            rpb = std::max<int64_t>(rpb, std::min<int64_t>(16, std::max<int64_t>(4, nrows * nag / 2048)));
-            rpb = (rpb + G.rows - 1) / G.rows * G.rows;
-            G.rows_per_block = rpb;
-        }
     }
     p->persist_need = pers;
     // split-BF16 exists for the contractions on the matrix cores only

@@ -15,6 +15,7 @@ namespace sb {
 
 constexpr double kKernelCacheCap = 64.0 * 1024 * 1024 * 1024;   // bytes of kernel spectra kept at most
 constexpr double kBatchBytes = 32.0 * 1024 * 1024 * 1024;       // kernel arrays of a field batch by default
+constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;      // scratch that sb_forward_noalloc holds per device
 
 enum Stage : int { STAGE_FFT = 0, STAGE_CONTRACT = 1, STAGE_OTHER = 2, STAGE_COUNT = 3 };
 
@@ -25,7 +26,7 @@ struct ShapeGroup {
     int np = 0, r0 = 0;           // stored axis-0 planes of the kernels, support radius along axis 0
     bool half = false;            // only the planes c_0 = 0 .. r0 stored (the others by parity)
     int rows = 0;                 // rows per tile of the fused last pass (0: not available)
-    int64_t rows_per_block = 0;
+    int64_t rows_per_block = 0;   // of the fused last pass: 16 or more where the plan has coarse_parts
     std::vector<int> fields;
     size_t khat_off = 0;          // byte offset of this shape's kernel spectra in the persistent buffer
     int64_t counts[kMaxBins] = {};
@@ -96,6 +97,7 @@ struct sb_plan {
     // workspace (caller-owned)
     char *persist = nullptr, *scratch = nullptr;
     size_t persist_need = 0, scratch_need = 0;
+    bool coarse_parts = false;   // short grids keep the tile and the rows of long ones (layout_scratch)
     size_t off_w = 0, off_dhat = 0, off_coef = 0, off_part = 0, off_tot = 0, off_grad = 0;
     size_t off_vtmp = 0, off_dsum = 0, off_gtab = 0;
     size_t off_flag = 0;          // 256 B: the non-finite counter of SB_FLAG_CHECK_FINITE
