@@ -77,8 +77,8 @@ enum {
     SB_FLAG_UNFUSED = 2u,     /* 3PCFs: write every coefficient array, then contract in a separate
                                  pass (the plain path; the default fuses the contraction into the
                                  last FFT pass and never writes the coefficients) */
-    SB_FLAG_NO_MFMA = 4u,     /* full 4PCF: use the plain float32 vector-ALU contraction even where
-                                 the matrix-core one exists (lmax <= 4, nbins <= 8); projected
+    SB_FLAG_NO_MFMA = 4u,     /* full 4PCF: use the plain float32 vector-ALU contraction
+                                 instead of the matrix-core ones; projected
                                  4PCF: the vector-ALU contraction instead of the matrix cores */
     SB_FLAG_ODD_PARITY = 8u,  /* full 4PCF: the odd-parity Lambda (l1 + l2 + l3 odd, Sec. 2.3, the
                                  ones Alg. 6 skips) instead of the even ones; each value is the

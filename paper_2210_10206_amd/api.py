@@ -48,7 +48,7 @@ class Plan:
     npcf       : 3 or 4
     precision  : "fp32" or "split_bf16" (contraction arithmetic of the 4PCF paths)
     input_dtype: torch.float32 or torch.float64 (the density arrays' dtype)
-    mfma       : full 4PCF: use the matrix-core contraction where it exists (l <= 4, <= 8 bins);
+    mfma       : full 4PCF: the matrix-core contractions (False = the vector-ALU kernel);
                  projected 4PCF: the matrix-core contraction (False = the vector-ALU kernel)
     parity     : full 4PCF: "even" (Alg. 6) or "odd" Lambda (the imaginary part of those sums)
     pack       : full 3PCF (fused path) and full 4PCF: carry the real m = 0 coefficient fields two
