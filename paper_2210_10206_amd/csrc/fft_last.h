@@ -72,11 +72,14 @@ __device__ __forceinline__ s4v split_col(float v) {
 
 // PREC 0: float32 4 x 4 x 1 MFMA.  PREC 1: split-BF16 4 x 4 x 4 MFMA (split_row / split_col),
 // float32 accumulation; the blocks, slots and lanes are the same.
-template <int NBT, int MODE, int PREC = 0>
+// PARTS (PS_COMPLEX, an even number of waves): the even waves sum the real parts and the odd ones the
+// imaginary parts, each over twice the cells, so a wave holds one accumulator set.
+template <int NBT, int MODE, int PREC = 0, bool PARTS = false>
 struct PairSums {
+    static_assert(!PARTS || MODE == PS_COMPLEX, "two parts to divide");
     static constexpr int Q = (NBT + 3) / 4;           // bin quads (bins >= NBT read as zero)
     static constexpr int NPB = Q * (Q + 1) / 2;       // quad pairs qa <= qb
-    static constexpr int NACC = MODE == PS_COMPLEX ? 2 : 1;   // accumulator sets
+    static constexpr int NACC = MODE == PS_COMPLEX && !PARTS ? 2 : 1;   // accumulator sets
     static constexpr int NOUT = MODE == PS_REAL ? 1 : 2;      // output parts
     static constexpr int CPG = 8;                     // cells per group
     static_assert(NBT >= 1 && NBT <= 16, "at most 16 bins");
@@ -119,15 +122,20 @@ struct PairSums {
         const int slot = lane >> 2, j = lane & 3;
         const int cg = slot >> 1;
         const bool im_slot = (slot & 1) != 0;
-        constexpr int UNROLL = MODE == PS_COMPLEX ? 1 : 2;   // the complex form has no registers to spare
+        static_assert(!PARTS || NW % 2 == 0, "as many waves for each part");
+        constexpr int GW = PARTS ? NW / 2 : NW;               // waves that share the cells
+        const bool other = PARTS && (wave & 1) != 0;          // the imaginary part: B of the other slot part,
+        const bool minus = other && !im_slot;                // Re a Im b with a minus sign
+        constexpr int UNROLL = NACC == 2 ? 1 : 2;   // two accumulator sets leave no registers to spare
 #pragma unroll UNROLL
-        for (int k = 0; k < (NG + NW - 1) / NW; ++k) {
-            const int grp = wave + k * NW;
+        for (int k = 0; k < (NG + GW - 1) / GW; ++k) {
+            const int grp = (PARTS ? wave >> 1 : wave) + k * GW;
             if (grp < NG) {
                 const int c = grp * CPG + cg;
                 const bool ok = NCELL % CPG == 0 || c < NCELL;
-                const float w = ok ? wsm[c] : 0.f;
-                float x[Q], xo[Q];
+                float w = ok ? wsm[c] : 0.f;
+                if constexpr (PARTS) w = minus ? -w : w;
+                float x[Q], xo[Q];   // xo: the other part (PARTS: the B operand)
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
                     const bool in = ok && 4 * q + j < nbl;
@@ -138,7 +146,7 @@ struct PairSums {
                     } else {
                         const float2 v = in ? stage[off(c) + (4 * q + j) * bstride] : make_float2(0.f, 0.f);
                         x[q] = im_slot ? v.y : v.x;
-                        xo[q] = im_slot ? v.x : v.y;
+                        xo[q] = im_slot != (PARTS && !other) ? v.x : v.y;
                     }
                 }
                 int p = 0;
@@ -148,8 +156,8 @@ struct PairSums {
                         const float aw = w * x[qa];
 #pragma unroll
                         for (int qb = qa; qb < Q; ++qb, ++p) {
-                            acc[0][p] = __builtin_amdgcn_mfma_f32_4x4x1f32(aw, x[qb], acc[0][p], 0, 0, 0);
-                            if constexpr (MODE == PS_COMPLEX)
+                            acc[0][p] = __builtin_amdgcn_mfma_f32_4x4x1f32(aw, PARTS ? xo[qb] : x[qb], acc[0][p], 0, 0, 0);
+                            if constexpr (NACC == 2)
                                 acc[NACC - 1][p] = __builtin_amdgcn_mfma_f32_4x4x1f32(im_slot ? aw : -aw, xo[qb],
                                                                                       acc[NACC - 1][p], 0, 0, 0);
                         }
@@ -158,8 +166,8 @@ struct PairSums {
                     s4v bx[Q], bxo[Q];
 #pragma unroll
                     for (int q = 0; q < Q; ++q) {
-                        bx[q] = split_col(x[q]);
-                        if constexpr (MODE == PS_COMPLEX) bxo[q] = split_col(xo[q]);
+                        bx[q] = split_col(PARTS ? xo[q] : x[q]);
+                        if constexpr (NACC == 2) bxo[q] = split_col(xo[q]);
                     }
 #pragma unroll
                     for (int qa = 0; qa < Q; ++qa) {
@@ -169,7 +177,7 @@ struct PairSums {
 #pragma unroll
                         for (int qb = qa; qb < Q; ++qb, ++p) {
                             acc[0][p] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ar, bx[qb], acc[0][p], 0, 0, 0);
-                            if constexpr (MODE == PS_COMPLEX)
+                            if constexpr (NACC == 2)
                                 acc[NACC - 1][p] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(im_slot ? ar : an, bxo[qb],
                                                                                           acc[NACC - 1][p], 0, 0, 0);
                         }
@@ -234,7 +242,7 @@ struct PairSums {
 
     // Writes this wave's totals to red[((wave * NOUT + part) * NPB + p) * 16 + r * 4 + j] (lane j
     // of a block holds column j; part: the accumulator set, or for PS_PACKED the lane's slot part).
-    // Each (part, pair, r, j) is held by exactly one lane of the wave after the flushes.
+    // Each (part, pair, r, j) of the wave is held by exactly one lane after the flushes.
     __device__ __forceinline__ void to_lds(double *red, int wave, int lane) {
         const int j = lane & 3;
         const int v0 = value_index(lane);
@@ -244,7 +252,7 @@ struct PairSums {
             const int v = v0 + k;
             if (v < NV) {
                 const int u = v / (NPB * 4), p = (v / 4) % NPB, r = v % 4;
-                const int part = MODE == PS_PACKED ? lane_part : u;
+                const int part = MODE == PS_PACKED ? lane_part : PARTS ? wave & 1 : u;
                 red[((wave * NOUT + part) * NPB + p) * 16 + r * 4 + j] = tot[k];
             }
         }
@@ -260,7 +268,8 @@ struct PairSums {
         const int qa = b1 >> 2, qb = b2 >> 2;
         const int p = qa * Q - qa * (qa - 1) / 2 + (qb - qa);
         double sum = 0.0;
-        for (int w = 0; w < nw; ++w) sum += red[((w * NOUT + part) * NPB + p) * 16 + (b1 & 3) * 4 + (b2 & 3)];
+        for (int w = PARTS ? part : 0; w < nw; w += PARTS ? 2 : 1)
+            sum += red[((w * NOUT + part) * NPB + p) * 16 + (b1 & 3) * 4 + (b2 & 3)];
         return sum;
     }
 };
@@ -658,8 +667,12 @@ constexpr int rs_waves(int n, int nbt, bool cplx) {
 // groups (2.5 TB/s read), now 21.6 (3.9 TB/s); 1.66 -> 1.43 ms at 192^3, 8 bins, 13 groups.
 template <int N, int NBT, int MODE, int PREC, int R0, int... REST>
 __device__ __forceinline__ void last_rs_body(const LastArgs &a, float2 *lds, float2 *tws, float *wsm) {
-    using PS = PairSums<NBT, MODE, PREC>;
     constexpr int T = N / R0;
+    // The complex sums of 1024 points in parts: both sets of 16 bins are 80 registers beside the row's 32
+    // (62 spilled, 0.65 ms for a 1024^2 map to m = 5; now 0.44).  Shorter rows have the registers, and
+    // twice the steps of half the MFMAs lose there: 512 points, 12 bins 183 us against 155.
+    constexpr bool PARTS = MODE == PS_COMPLEX && N >= 1024 && NBT * T / 64 % 2 == 0;
+    using PS = PairSums<NBT, MODE, PREC, PARTS>;
     constexpr int P = NBT;
     constexpr int NT = P * T;
     constexpr int NW = NT / 64;
@@ -670,7 +683,7 @@ __device__ __forceinline__ void last_rs_body(const LastArgs &a, float2 *lds, flo
     constexpr int REG = row_region<N>(SPLIT);
     constexpr int WPT = (N + NT - 1) / NT;
     static_assert(NT % 64 == 0 && 64 % T == 0 && sizeof...(REST) >= 1, "whole waves, a pencil in one of them");
-    constexpr int FLUSH = NBT * PS::NACC <= 12 ? 8 : 1;   // larger accumulators would not stay in registers
+    constexpr int FLUSH = NBT * (MODE == PS_COMPLEX ? 2 : 1) <= 12 ? 8 : 1;   // larger sums would not stay in registers
     const int nb = a.nb;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int q = tid % T, pp = tid / T;        // element column, pencil (= bin)

@@ -43,3 +43,12 @@ def test_2d(n, nb, precision):
     edges = linear_edges(7.5, nb)
     d, z = _run((16, n), edges, 3, precision)
     check(z, oracle.zeta3_proj(d, edges, 3), TOL32 if precision == "fp32" else TOL_SPLIT, print, f"16x{n} {nb} bins {precision}: ")
+
+
+@pytest.mark.parametrize("nb", [3, 10])
+@pytest.mark.parametrize("precision", ["fp32", "split_bf16"])
+def test_2d_parts_by_wave(nb, precision):
+    """Real and imaginary sums on different waves: the smallest workgroup (4 waves) and 12 padded bins."""
+    edges = linear_edges(3.9, nb)
+    d, z = _run((8, 1024), edges, 3, precision)
+    check(z, oracle.zeta3_proj(d, edges, 3), TOL32 if precision == "fp32" else TOL_SPLIT, print, f"8x1024 {nb} bins {precision}: ")
