@@ -62,8 +62,7 @@ def write_traffic(counter_dir, n=256, copy_mib=1024, min_gib=1.0):
     size); the passes over all kernel arrays are the dispatches of each kernel family with at
     least min_gib GiB of either counter, and of the axis-0 and middle passes only the variant
     of the run's last dispatch (the one the autotuner picked and the timed step used).  The
-    last pass is two launches per field (packed m = 0 pairs, other groups): their bytes are
-    summed."""
+    bytes of a pass that is several launches per field are summed."""
     import csv
     import re
     reg = {256: 16}.get(n)   # lengths with the register-resident forms (n = r * r)
@@ -105,8 +104,7 @@ def write_traffic(counter_dir, n=256, copy_mib=1024, min_gib=1.0):
             continue
         # one pass over a field's arrays: for the axis-0 and middle passes the variant of the
         # last dispatch (the timed step runs last, with the variant the autotuner chose), for
-        # the last pass every dispatch name launched as often as the most frequent one (the
-        # packed m = 0 pairs and the other groups are two launches per field), summed
+        # the last pass every dispatch name launched as often as the most frequent one, summed
         if k != 2:
             names = [last_name]
             nmax = len(per_name[last_name])
@@ -806,8 +804,8 @@ def main():
                     + " (axis-0 pass: kernel-spectrum regeneration + product + inverse transform)",
                  2: (f"last_reg_kernel<16,16,{(nbins + 3) // 4 * 4},PS_PACKED+PS_REAL,0>" if n == 256
                      else f"last_contract_kernel<{n},...>")
-                    + " (last inverse pass fused with the MFMA pair sums; two launches per field: the packed "
-                      "m = 0 pairs, then the rest)",
+                    + " (last inverse pass fused with the MFMA pair sums; one launch for the packed m = 0 pairs "
+                      "and the rest)",
                  3: "pair_kernel (unfused 3PCF contraction)"}
         srcs = TRAFFIC_SRCS
         per = {}
