@@ -382,7 +382,8 @@ __global__ __launch_bounds__(P * R2, MODE == 0 ? (R1 < 32 && 2 * KR < R1 ? 3 : 2
                 const float2 w = SIGN < 0 ? tv : make_float2(tv.x, -tv.y);
                 u[r] = r == 0 ? x : cmul(x, w);
             }
-            Dft<R2, SIGN>::run(u);
+            if constexpr (R1 == 32 && R2 == 16) Dft16<SIGN, true>::run(u);   // pairs, as in its 32-point stage
+            else Dft<R2, SIGN>::run(u);
 #pragma unroll
             for (int r = 0; r < R2; ++r) v[t + T * r] = u[r];   // element q + R2 t + R1 r
         }
