@@ -661,10 +661,12 @@ constexpr int rs_waves(int n, int nbt, bool cplx) {
 // is one row of the NBT (padded) bins of one (l, m); thread q < T = n / R0 of a pencil loads elements
 // q + T s.  As in last_reg_kernel a pencil's threads are lanes of one wave and its exchanges go
 // through its own LDS region, so the workgroup meets at two barriers a row, and the row ends in the
-// region as real and imaginary planes for the pair sums, flushed to float64 every FLUSH rows.  The
-// sequence of one row, not the bytes, bounds the pass: with one exchange buffer of all pencils it met
-// at seven barriers a row and flushed after each, 33.6 ms per 512^3 field of 6 bins and 13 array
-// groups (2.5 TB/s read), now 21.6 (3.9 TB/s); 1.66 -> 1.43 ms at 192^3, 8 bins, 13 groups.
+// region as real and imaginary planes for the pair sums, flushed to float64 after every row (every
+// eighth saved 1.1 ms of a 512^3 call of 82, but the roundings of a sum of 128 like terms do not average
+// out: on constant maps up to 3.6e-6 of the sums of 512-point rows, 4.8e-7 now).  The sequence of one row,
+// not the bytes, bounds the pass: with one exchange buffer of all pencils, seven barriers a row, it took
+// 33.6 ms per 512^3 field of 6 bins and 13 array groups (2.5 TB/s read), now 23.1 (3.65 TB/s);
+// 1.66 -> 1.30 ms at 192^3, 8 bins, 13 groups.
 template <int N, int NBT, int MODE, int PREC, int R0, int... REST>
 __device__ __forceinline__ void last_rs_body(const LastArgs &a, float2 *lds, float2 *tws, float *wsm) {
     constexpr int T = N / R0;
@@ -683,7 +685,6 @@ __device__ __forceinline__ void last_rs_body(const LastArgs &a, float2 *lds, flo
     constexpr int REG = row_region<N>(SPLIT);
     constexpr int WPT = (N + NT - 1) / NT;
     static_assert(NT % 64 == 0 && 64 % T == 0 && sizeof...(REST) >= 1, "whole waves, a pencil in one of them");
-    constexpr int FLUSH = NBT * (MODE == PS_COMPLEX ? 2 : 1) <= 12 ? 8 : 1;   // larger sums would not stay in registers
     const int nb = a.nb;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int q = tid % T, pp = tid / T;        // element column, pencil (= bin)
@@ -756,11 +757,16 @@ __device__ __forceinline__ void last_rs_body(const LastArgs &a, float2 *lds, flo
         __syncthreads();
         if constexpr (!PF)
             if (row + 1 < r_end) load_row(row + 1, v, wv);   // in flight during the pair sums
-        if constexpr (SPLIT)
+        if constexpr (SPLIT) {
             ps.template accumulate<N, NW, PLANE>(lds, 2 * REG, wsm, [](int c) { return c; }, wave, lane, nb);
-        else
+        } else if constexpr (PARTS && NBT <= 12) {   // half as many waves for a sum: to float64 after half a row
+            ps.template accumulate<N / 2, NW>(lds, REG, wsm, [](int c) { return c; }, wave, lane, nb);
+            ps.flush(lane);   // (16 bins: 16 cells a wave and sum without that, and 5 % of the maps' call with it)
+            ps.template accumulate<N / 2, NW>(lds, REG, wsm + N / 2, [](int c) { return c + N / 2; }, wave, lane, nb);
+        } else {
             ps.template accumulate<N, NW>(lds, REG, wsm, [](int c) { return c; }, wave, lane, nb);
-        if ((row - r_begin) % FLUSH == FLUSH - 1 || row + 1 == r_end) ps.flush(lane);
+        }
+        ps.flush(lane);
     }
     // float64 combine over the waves in wave order (as in last_contract_kernel)
     __syncthreads();

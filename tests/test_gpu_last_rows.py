@@ -52,3 +52,28 @@ def test_2d_parts_by_wave(nb, precision):
     edges = linear_edges(3.9, nb)
     d, z = _run((8, 1024), edges, 3, precision)
     check(z, oracle.zeta3_proj(d, edges, 3), TOL32 if precision == "fp32" else TOL_SPLIT, print, f"8x1024 {nb} bins {precision}: ")
+
+
+@pytest.mark.parametrize("n,orders,adds", [(512, 17, 32), (1024, 17, 32)])
+def test_every_row_reaches_float64(n, orders, adds):
+    """A constant map: every cell adds the same product to its float32 sum, so the roundings of a run of
+    additions are of one sign and nothing averages out: k equal terms after one another err by at most
+    (k + 1) / 2 ulps of 2^-24 of their sum.  A wave adds at most `adds` cells of a row to each of its sums
+    before they go to float64 (9.8e-7 for 32; eight rows together, 7.7e-6).  Everything before the sums
+    is exact: powers of two, whole numbers of cells and one rounding of density times cells."""
+    from paper_2210_10206_amd import api
+    shape, nb = (1024, n), 3
+    edges = linear_edges(6.0, nb)
+    plan = api.Plan([shape], edges, orders - 1)   # as many orders as give eight rows a workgroup
+    cells = plan.bin_counts(0)
+    errs = []
+    for c in np.random.default_rng(11).uniform(0.5, 2.0, 16).astype(np.float32):
+        z = plan.forward([torch.full(shape, float(c), dtype=torch.float32, device="cuda")]).cpu().numpy()[0]
+        for b in range(nb):
+            v = np.float32(c * np.float32(cells[b]))
+            exact = float(np.float32(c * v)) * float(v) * shape[0] * shape[1]
+            errs.append(abs(z[0, b, b].real / exact - 1))
+    plan.close()
+    bound = (adds + 1) / 2 * 2.0 ** -24
+    print(f"{shape} constant maps: worst {max(errs):.3e} (bound {bound:.2e})", flush=True)
+    assert max(errs) < bound
