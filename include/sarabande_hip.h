@@ -198,8 +198,9 @@ sb_status sb_plan_set_scratch_limit(sb_plan *plan, uint64_t bytes);
  * batch (the field is the launch's third grid dimension), in batches of up to `max_fields`:
  * 0 (the default) takes as many as 32 GiB of kernel arrays allow, 1 runs every field through
  * its own launch sequence in field order.  Plans whose passes run in chunks of kernel groups,
- * and SB_FLAG_KEEP_COEFFS plans, use 1.  Results do not depend on the batch (each field's sums
- * are computed by the same launches in the same order).  Call before sb_plan_bind (SB_ESTATE
+ * and SB_FLAG_KEEP_COEFFS plans, use 1; a plan takes fewer than it may where that keeps its
+ * scratch within the 64 MiB of sb_forward_noalloc.  Results do not depend on the batch (each
+ * field's sums are computed by the same launches in the same order).  Call before sb_plan_bind (SB_ESTATE
  * afterwards); sb_plan_workspace then reports the scratch for the batch.  get: the batch the
  * plan uses.  Errors: SB_EINVAL (null plan, max_fields < 0), SB_ESTATE. */
 sb_status sb_plan_set_field_batch(sb_plan *plan, int32_t max_fields);

@@ -138,23 +138,21 @@ static sb_status build_gather(sb_plan *p, std::vector<int> &gptr, std::vector<in
     return SB_OK;
 }
 
-// Cells per workgroup of the cell-parallel contraction on a grid of ng cells: the contraction tile
-// (cpb, 0: the plan's current choice), halved for the 4PCFs while the launch would have under 1024
-// workgroups (a launch of the full 4PCF covers one Lambda, one of the projected 4PCF every triple),
-// down to two of the 64-cell tiles that its kernels stage, or one where that leaves under 128.  A
-// 32^3 grid is 32 workgroups of 1024 cells for 256 compute units.  Depends on the grid alone, so
-// that a field's sums do not depend on the batch, except where layout_scratch sets coarse_parts.
-static int contract_cells(const sb_plan *p, int64_t ng, int cpb = 0) {
-    if (cpb == 0) cpb = p->contract_tile();
-    if (p->prob.npcf == 3 || p->coarse_parts) return cpb;
-    const int64_t per = p->prob.ndim == 3 ? 1 : (int64_t)p->p4_canon.size();
+// Cells per workgroup of the cell-parallel contraction on shape G: the contraction tile, halved for the
+// 4PCFs while a launch would have under 1024 workgroups (one Lambda of the compile-time kernels is a launch
+// and the run-time one is cut alike; one of the projected 4PCF covers every triple), down to two of the
+// 64-cell tiles that the kernels stage, or one where that leaves under 128.  A 32^3 grid is 32 workgroups
+// of 1024 cells for 256 compute units.
+static int contract_cells(const sb_plan *p, const ShapeGroup &G, int cpb) {
+    if (p->prob.npcf == 3 || !G.short_parts) return cpb;
+    const int64_t per = p->prob.ndim == 3 ? 1 : (int64_t)p->p4_canon.size(), ng = G.ng;
     while ((cpb > 128 && (ng + cpb - 1) / cpb * per < 1024) || (cpb > 64 && (ng + cpb - 1) / cpb * per < 128)) cpb /= 2;
     return cpb;
 }
+static int contract_cells(const sb_plan *p, const ShapeGroup &G) { return contract_cells(p, G, p->contract_tile()); }
 
-static void contraction_shape(const sb_plan *p, int64_t ng, int *groups, int *nvals, int *nblocks, int cpb = 0) {
+static void contraction_shape(const sb_plan *p, int *groups, int *nvals) {
     const int NB = p->prob.nbins;
-    cpb = contract_cells(p, ng, cpb);
     if (p->prob.npcf == 3) {
         *groups = p->nlm;
         *nvals = NB * (NB + 1) / 2 * (p->prob.ndim == 2 ? 2 : 1);
@@ -165,66 +163,91 @@ static void contraction_shape(const sb_plan *p, int64_t ng, int *groups, int *nv
         *groups = (int)p->p4_canon.size();
         *nvals = 2 * NB * NB * NB;
     }
-    *nblocks = (int)((ng + cpb - 1) / cpb);
 }
 
+static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// The adjoint's regions are part of the scratch.
+static bool has_adjoint(const sb_plan *p) { return p->prob.ndim == 3 && p->prob.npcf == 3 && !p->regen; }
 
 // Rows per workgroup of the fused last pass: at most about 1024 workgroups a group, of 16 rows or
-// more; fewer rows where the groups together would not make 2048 workgroups (512^2, 11 groups: 352
-// of 16 rows).
+// more; fewer rows where the groups together would not make 2048 workgroups (us, 16 rows / fewer: maps
+// of 128^2 and 192 x 96, 8 and 6 bins, 81 / 38 and 77 / 42; 96 x 32 x 64, 5 bins 91 / 82).  Plans with an
+// adjoint keep the partials of the shorter blocks within those of 16 rows and one group's v arrays,
+// which the forward does not use (place_scratch).
 static int64_t last_rows(const sb_plan *p, const ShapeGroup &G) {
     const int64_t nrows = G.ng / G.n[p->prob.ndim - 1];
     const int nag = p->npack > 0 ? p->nag : p->nlm;
-    const int64_t least = p->coarse_parts ? 16 : std::min<int64_t>(16, std::max<int64_t>(4, nrows * nag / 2048));
-    const int64_t rpb = std::max<int64_t>((nrows + 1023) / 1024, least);
-    return (rpb + G.rows - 1) / G.rows * G.rows;
+    const auto tiled = [&](int64_t rpb) { return ceil_div(rpb, G.rows) * G.rows; };
+    const int64_t most = ceil_div(nrows, 1024), rpb16 = tiled(std::max<int64_t>(most, 16));
+    if (!G.short_parts) return rpb16;
+    int64_t least = std::min<int64_t>(16, std::max<int64_t>(4, nrows * nag / 2048));
+    if (has_adjoint(p)) {
+        int groups = 0, nvals = 0;
+        contraction_shape(p, &groups, &nvals);
+        const int64_t blocks = ceil_div(nrows, rpb16) + p->prob.nbins * G.ng / ((int64_t)groups * nvals);
+        least = std::max(least, ceil_div(nrows, blocks));
+    }
+    return std::min(rpb16, tiled(std::max(most, least)));
 }
 
-static void layout_scratch_parts(sb_plan *p);
-
-// The shorter tiles and rows of short grids (contract_cells, last_rows) write more partials.  A plan
-// that fits the scratch of sb_forward_noalloc only without them goes without: 4PCF, 32^3, 10 bins,
-// lmax = 4 needs 66 MiB with 256 workgroups a launch and 45 MiB with 64.
-void layout_scratch(sb_plan *p) {
-    p->coarse_parts = false;
-    layout_scratch_parts(p);
-    if (p->scratch_need <= kNoAllocScratchBytes) return;
-    p->coarse_parts = true;
-    layout_scratch_parts(p);
-    if (p->scratch_need <= kNoAllocScratchBytes) return;
-    p->coarse_parts = false;
-    layout_scratch_parts(p);
+// Block partials of every group of one field of shape G: the most of the contraction tiles that the plan
+// may take and of the fused last pass.
+static int64_t part_blocks(const sb_plan *p, const ShapeGroup &G) {
+    int tile_lo = 0, tile_hi = 0;
+    p->contract_tile_range(&tile_lo, &tile_hi);
+    int64_t n = ceil_div(G.ng, contract_cells(p, G, tile_lo));
+    if (G.rows > 0 && p->prob.npcf == 3) n = std::max(n, ceil_div(G.ng / G.n[p->prob.ndim - 1], last_rows(p, G)));
+    return n;
 }
 
-// Scratch layout.  A 3PCF plan whose full set of kernel arrays exceeds coef_limit runs its
-// passes over chunks of kernel groups (the fused contraction and the adjoint only need one
-// group's bins at a time); every other plan keeps all arrays at once.
-static void layout_scratch_parts(sb_plan *p) {
+// Kernel groups at once for fields of up to max_ng cells.
+static int chunk_of(const sb_plan *p, int64_t max_ng) {
+    const uint64_t per_group = (uint64_t)p->prob.nbins * max_ng * sizeof(float2);
+    const bool chunkable = p->prob.npcf == 3 && (p->prob.flags & SB_FLAG_KEEP_COEFFS) == 0 && !p->keep;
+    if (!chunkable || per_group * p->nlm <= p->coef_limit) return p->nlm;
+    return (int)std::max<uint64_t>(1, std::min<uint64_t>(p->nlm, p->coef_limit / per_group));
+}
+
+// Offsets of the scratch regions for batches of fbatch fields of any of the plan's shapes, or of shape
+// `only`; returns the bytes they take.
+static size_t place_scratch(sb_plan *p, const ShapeGroup *only = nullptr) {
     const sb_problem *prob = &p->prob;
     const int NB = prob->nbins;
-    const uint64_t per_group = (uint64_t)NB * p->max_ng * sizeof(float2);
-    p->chunk_groups = p->nlm;
-    p->kept = false;
-    const bool chunkable = prob->npcf == 3 && (prob->flags & SB_FLAG_KEEP_COEFFS) == 0 && !p->keep;
-    if (chunkable && per_group * p->nlm > p->coef_limit)
-        p->chunk_groups = (int)std::max<uint64_t>(1, std::min<uint64_t>(p->nlm, p->coef_limit / per_group));
-    // fields per batch (the region of each per-field buffer below is fbatch fields long)
-    int maxf = 1;
-    for (const auto &G : p->groups) maxf = std::max<int>(maxf, (int)G.fields.size());
-    p->fbatch = 1;
-    if (p->chunk_groups == p->nlm && !p->regen && (prob->flags & SB_FLAG_KEEP_COEFFS) == 0) {
-        const double per_field = (double)per_group * p->nlm;
-        p->fbatch = p->fbatch_req > 0 ? std::min(maxf, p->fbatch_req)
-                                      : std::max(1, std::min(maxf, (int)(kBatchBytes / per_field)));
-    }
     const size_t FB = (size_t)p->fbatch;
+    const size_t max_ng = (size_t)(only ? only->ng : p->max_ng);
+    int groups = 0, nvals = 0;
+    contraction_shape(p, &groups, &nvals);
+    int64_t nblocks = 0, kc = 0;
+    for (const auto &G : p->groups) {
+        if (only && &G != only) continue;
+        nblocks = std::max(nblocks, part_blocks(p, G));
+        kc = std::max<int64_t>(kc, (int64_t)G.np * G.plane);
+    }
+    const size_t part = align256(std::max<size_t>(FB * groups * nvals * nblocks, kNormParts) * sizeof(double));
     size_t sc = 0;
-    p->off_w = sc; sc += align256(FB * p->max_ng * sizeof(float));
-    p->off_dhat = sc; sc += align256(FB * p->max_ng * sizeof(float2));
-    const bool adjoint = prob->ndim == 3 && prob->npcf == 3 && !p->regen;
-    // the adjoint's v arrays directly before the coefficient arrays: its fused pass writes the v
-    // of each group into the slot before that group's coefficients
-    if (adjoint) { p->off_vtmp = sc; sc += align256((size_t)NB * p->max_ng * sizeof(float2)); }
+    p->off_w = sc; sc += align256(FB * max_ng * sizeof(float));
+    p->off_dhat = sc; sc += align256(FB * max_ng * sizeof(float2));
+    p->off_part = sc;
+    if (has_adjoint(p)) {
+        // the adjoint's v arrays directly before the coefficient arrays: its fused pass writes the v
+        // of each group into the slot before that group's coefficients.  The forward's partials may
+        // reach into them.
+        int64_t long_blocks = 0;
+        for (auto &G : p->groups) {
+            if (only && &G != only) continue;
+            const bool sp = G.short_parts;
+            G.short_parts = false;
+            long_blocks = std::max(long_blocks, part_blocks(p, G));
+            G.short_parts = sp;
+        }
+        const size_t vtmp = align256((size_t)NB * max_ng * sizeof(float2));
+        const size_t long_part = align256(std::max<size_t>(FB * groups * nvals * long_blocks, kNormParts) * sizeof(double));
+        sc += std::max(part, long_part + vtmp);
+        p->off_vtmp = sc - vtmp;
+    } else {
+        sc += part;
+    }
     p->off_coef = sc;
     if (p->keep) {
         // one region per field: the forward's array groups (packed m = 0 pairs first) of all bins
@@ -237,42 +260,83 @@ static void layout_scratch_parts(sb_plan *p) {
                 k += (size_t)nag * NB * G.ng * sizeof(float2);
             }
         // at least the region the recomputing backward uses (one field of every (l, m) group)
-        sc += align256(std::max(k, (size_t)p->nlm * NB * p->max_ng * sizeof(float2)));
+        sc += align256(std::max(k, (size_t)p->nlm * NB * max_ng * sizeof(float2)));
         p->off_vkeep = sc;
-        sc += align256((size_t)nag * NB * p->max_ng * sizeof(float2));
+        sc += align256((size_t)nag * NB * max_ng * sizeof(float2));
     } else {
-        sc += align256(FB * p->chunk_groups * NB * p->max_ng * sizeof(float2));
+        sc += align256(FB * p->chunk_groups * NB * max_ng * sizeof(float2));
     }
     if (p->regen) {   // the stored axis-0 planes of one chunk's kernels
-        int64_t kc = 0;
-        for (const auto &G : p->groups) kc = std::max<int64_t>(kc, (int64_t)G.np * G.plane);
         p->off_kc = sc; sc += align256((size_t)p->chunk_groups * NB * kc * sizeof(float2));
     }
-    int groups = 0, nvals = 0, nblocks = 0, tile_lo = 0, tile_hi = 0;
-    p->contract_tile_range(&tile_lo, &tile_hi);
-    for (const auto &G : p->groups) {
-        int nb = 0;
-        contraction_shape(p, G.ng, &groups, &nvals, &nb, tile_lo);
-        nblocks = std::max(nblocks, nb);
-    }
-    for (auto &G : p->groups)
-        if (G.rows > 0) G.rows_per_block = last_rows(p, G);
-    for (const auto &G : p->groups)
-        if (G.rows > 0 && prob->npcf == 3) {
-            const int64_t nrows = G.ng / G.n[prob->ndim - 1];
-            nblocks = std::max<int>(nblocks, (int)((nrows + G.rows_per_block - 1) / G.rows_per_block));
-        }
-    p->off_part = sc;
-    sc += align256(std::max<size_t>(FB * groups * nvals * nblocks, kNormParts) * sizeof(double));
     p->off_tot = sc; sc += align256(FB * groups * nvals * sizeof(double));
-    p->off_grad = sc; sc += align256((size_t)p->max_ng * sizeof(float2));
+    p->off_grad = sc; sc += align256(max_ng * sizeof(float2));
     p->off_flag = sc; sc += 256;
     p->off_zt = sc; sc += align256((size_t)p->zeta_doubles * sizeof(double));
-    if (adjoint) {
-        p->off_dsum = sc; sc += align256((size_t)p->max_ng * sizeof(float));
+    if (has_adjoint(p)) {
+        p->off_dsum = sc; sc += align256(max_ng * sizeof(float));
         p->off_gtab = sc; sc += align256((size_t)(prob->lmax + 1) * 256 * sizeof(float));   // G_l, 16 x 16
     }
-    p->scratch_need = sc;
+    return sc;
+}
+
+void use_shape(sb_plan *p, const ShapeGroup &G) {
+    if (p->by_shape) place_scratch(p, &G);
+}
+
+// Scratch layout.  A 3PCF plan whose full set of kernel arrays exceeds coef_limit runs its
+// passes over chunks of kernel groups (the fused contraction and the adjoint only need one
+// group's bins at a time); every other plan keeps all arrays at once.
+//
+// The shorter tiles and rows of short grids (contract_cells, last_rows) write more partials.  A shape goes
+// without where one field of it fits the scratch of sb_forward_noalloc only so (4PCF, 32^3, 10 bins,
+// lmax = 4: 66 MiB with 256 workgroups a launch, 45 MiB with 64): by the problem and the shape alone,
+// because a field's sums are not to depend on the other fields of its plan.  A plan that then exceeds
+// that scratch, and would not with long tiles and rows throughout, runs fewer fields at a time, and with
+// one of them at a time lays the scratch out for each shape by itself: neither changes a sum.
+void layout_scratch(sb_plan *p) {
+    p->kept = false;
+    p->by_shape = false;
+    p->fbatch = 1;
+    for (auto &G : p->groups) {
+        G.short_parts = true;
+        if (!has_adjoint(p)) {
+            p->chunk_groups = chunk_of(p, G.ng);
+            const size_t with = place_scratch(p, &G);
+            G.short_parts = false;
+            G.short_parts = with <= kNoAllocScratchBytes || place_scratch(p, &G) > kNoAllocScratchBytes;
+        }
+        if (G.rows > 0) G.rows_per_block = last_rows(p, G);
+    }
+    p->chunk_groups = chunk_of(p, p->max_ng);
+    // fields per batch (the region of each per-field buffer is fbatch fields long)
+    int maxf = 1;
+    for (const auto &G : p->groups) maxf = std::max<int>(maxf, (int)G.fields.size());
+    if (p->chunk_groups == p->nlm && !p->regen && (p->prob.flags & SB_FLAG_KEEP_COEFFS) == 0) {
+        const double per_field = (double)p->prob.nbins * p->max_ng * sizeof(float2) * p->nlm;
+        p->fbatch = p->fbatch_req > 0 ? std::min(maxf, p->fbatch_req)
+                                      : std::max(1, std::min(maxf, (int)(kBatchBytes / per_field)));
+    }
+    std::vector<bool> shorts;
+    for (auto &G : p->groups) {
+        shorts.push_back(G.short_parts);
+        G.short_parts = false;
+    }
+    const size_t plain = place_scratch(p);   // what decides whether sb_forward_noalloc takes the plan
+    for (size_t g = 0; g < p->groups.size(); ++g) p->groups[g].short_parts = shorts[g];
+    size_t need = place_scratch(p);
+    if (plain <= kNoAllocScratchBytes) {
+        while (need > kNoAllocScratchBytes && p->fbatch > 1) {
+            --p->fbatch;
+            need = place_scratch(p);
+        }
+        if (need > kNoAllocScratchBytes && !has_adjoint(p)) {
+            p->by_shape = true;
+            need = 0;
+            for (const auto &G : p->groups) need = std::max(need, place_scratch(p, &G));
+        }
+    }
+    p->scratch_need = std::max(plain, need);
 }
 
 // Device addresses of the tables in the bound persistent buffer (filled by sb_prepare).
@@ -974,8 +1038,9 @@ static sb_status fused_3pcf(sb_plan *p, const ShapeGroup &G, const void *const *
 sb_status contract(sb_plan *p, const ShapeGroup &G, const float *w, double *const *zout, int nf, hipStream_t s) {
     const float2 *coef = reinterpret_cast<const float2 *>(p->scratch + p->off_coef);
     double *part = reinterpret_cast<double *>(p->scratch + p->off_part);
-    int groups = 0, nvals = 0, nblocks = 0;
-    contraction_shape(p, G.ng, &groups, &nvals, &nblocks);
+    int groups = 0, nvals = 0;
+    contraction_shape(p, &groups, &nvals);
+    const int cells = contract_cells(p, G), nblocks = (int)ceil_div(G.ng, cells);
     hipError_t e = hipSuccess;
     const int NB = p->prob.nbins;
     // field strides: every array group of a field, its density, its block partials
@@ -1013,7 +1078,7 @@ sb_status contract(sb_plan *p, const ShapeGroup &G, const float *w, double *cons
         a.terms = p->d_terms;
         a.stage = p->d_stage;
         a.max_cols = p->max_cols;
-        a.cells_per_block = contract_cells(p, G.ng);
+        a.cells_per_block = cells;
         a.tile = p->quad_tile;
         a.nlm = p->nlm;
         a.partial = part;
@@ -1117,7 +1182,7 @@ sb_status contract(sb_plan *p, const ShapeGroup &G, const float *w, double *cons
         a.items = p->d_items;
         a.nitems = p->p4_items;
         a.mmax = p->prob.lmax;
-        a.cells_per_block = contract_cells(p, G.ng);
+        a.cells_per_block = cells;
         a.tile = p->proj4_tile;
         a.partial = part;
         a.nblocks = nblocks;
@@ -1188,6 +1253,7 @@ sb_status forward(sb_plan *p, const void *const *delta, double *zeta, hipStream_
         }
         if (p->chunk_groups < p->nlm && !(p->prob.npcf == 3 && p->fused))
             return fail(SB_EUNSUPPORTED, "this path needs every kernel array at once; raise the scratch limit");
+        use_shape(p, G);
         if (p->prob.npcf == 3 && p->fused)
             return fused_3pcf(p, G, dl.data(), zo.data(), nf, p->keep ? p->keep_off[fidx[0]] : 0, s);
         const float *w = nullptr;

@@ -180,10 +180,11 @@ sb_status sb_autotune(sb_plan *p, void *stream, const char *cache_path) {
     }
     hipEvent_t a, b;
     if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess) return fail(SB_EHIP, "event create");
-    float2 *coef = reinterpret_cast<float2 *>(p->scratch + p->off_coef);
     const bool was_timing = p->timing;
     p->timing = false;
     for (const auto &G : p->groups) {
+        use_shape(p, G);
+        float2 *coef = reinterpret_cast<float2 *>(p->scratch + p->off_coef);
         for (int d = 0; d < p->prob.ndim; ++d) {
             const int n = (int)G.n[d];
             const int nv = fft_num_variants(n);
@@ -232,6 +233,7 @@ sb_status sb_autotune(sb_plan *p, void *stream, const char *cache_path) {
         int f0 = 0;
         for (int f = 0; f < p->batch; ++f)
             if (p->groups[p->field_group[f]].ng > p->groups[p->field_group[f0]].ng) f0 = f;
+        use_shape(p, p->groups[p->field_group[f0]]);
         double *zt = reinterpret_cast<double *>(p->scratch + p->off_zt);
         int lo = 0, hi = 0;
         p->contract_tile_range(&lo, &hi);

@@ -26,7 +26,8 @@ struct ShapeGroup {
     int np = 0, r0 = 0;           // stored axis-0 planes of the kernels, support radius along axis 0
     bool half = false;            // only the planes c_0 = 0 .. r0 stored (the others by parity)
     int rows = 0;                 // rows per tile of the fused last pass (0: not available)
-    int64_t rows_per_block = 0;   // of the fused last pass: 16 or more where the plan has coarse_parts
+    bool short_parts = false;     // shorter contraction tiles and last-pass blocks where the grid is short (layout_scratch)
+    int64_t rows_per_block = 0;   // of the fused last pass
     std::vector<int> fields;
     size_t khat_off = 0;          // byte offset of this shape's kernel spectra in the persistent buffer
     int64_t counts[kMaxBins] = {};
@@ -97,7 +98,7 @@ struct sb_plan {
     // workspace (caller-owned)
     char *persist = nullptr, *scratch = nullptr;
     size_t persist_need = 0, scratch_need = 0;
-    bool coarse_parts = false;   // short grids keep the tile and the rows of long ones (layout_scratch)
+    bool by_shape = false;       // the offsets below are those of one shape, use_shape sets them
     size_t off_w = 0, off_dhat = 0, off_coef = 0, off_part = 0, off_tot = 0, off_grad = 0;
     size_t off_vtmp = 0, off_dsum = 0, off_gtab = 0;
     size_t off_flag = 0;          // 256 B: the non-finite counter of SB_FLAG_CHECK_FINITE
@@ -230,6 +231,7 @@ sb_status density_weights(sb_plan *p, const sb::ShapeGroup &G, const void *delta
 sb_status coefficients(sb_plan *p, int f, int g0, int ngroups, hipStream_t s, bool last_axis = true,
                        const int *kmap = nullptr, int nf = 1);
 void layout_scratch(sb_plan *p);
+void use_shape(sb_plan *p, const ShapeGroup &G);   // scratch offsets for fields of shape G (by_shape plans)
 sb_status contract(sb_plan *p, const ShapeGroup &G, const float *w, double *const *zout, int nf, hipStream_t s);
 // Half kernel store (plan.hip): whether a shape keeps only the planes c_0 = 0 .. r0, the planes
 // stored per kernel, and the half-store fields of an axis-0 launch.
