@@ -310,9 +310,16 @@ sb_status sb_plan_get_fft_variant(const sb_plan *plan, int32_t n, int32_t axis, 
  * A power of two within [lo, hi] = [512, 4096] (full 4PCF), [1024, 8192] (projected
  * 4PCF), [2048, 16384] (3PCF); the workspace of sb_plan_workspace holds the partial sums
  * of lo.  sb_autotune sets it by timing; set returns SB_EINVAL outside the range.  The
- * choice only reorders the FP64 sum of per-workgroup partials.  get: lo and hi may be NULL. */
+ * choice only changes which cells each workgroup sums.  get: lo and hi may be NULL.
+ *
+ * Short tiles (on in a new plan): the 4PCFs halve the tile, down to 64 cells, on grids too
+ * small to fill the device with it.  sb_plan_set_contract_tile turns that off, so that the
+ * tile it sets is the one that runs; sb_autotune times the tile of a new plan with it and
+ * the others without, and keeps the fastest. */
 sb_status sb_plan_set_contract_tile(sb_plan *plan, int32_t cells);
 sb_status sb_plan_get_contract_tile(const sb_plan *plan, int32_t *cells, int32_t *lo, int32_t *hi);
+sb_status sb_plan_set_short_tiles(sb_plan *plan, int32_t on);
+sb_status sb_plan_get_short_tiles(const sb_plan *plan, int32_t *on);
 
 /* Forward pass replayed from a HIP graph captured on first use for these exact
  * pointers (re-captured when they change).  Same contract and results as sb_forward; needs a

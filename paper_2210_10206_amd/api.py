@@ -280,8 +280,9 @@ class Plan:
 
     def choices(self):
         """The tuned launch shapes of this plan: {"fft": {"n,axis": variant} for every (length,
-        axis) of its shapes, "contract_tile": cells per workgroup}; set_choices() restores them
-        (e.g. tuned once, saved as JSON)."""
+        axis) of its shapes, "contract_tile": cells per workgroup, "short_tiles": whether short grids
+        take fewer (sb_plan_set_short_tiles)}; set_choices() restores them (e.g. tuned once, saved as
+        JSON)."""
         fft = {}
         for shape in self.shapes:
             for axis, n in enumerate(shape):
@@ -289,7 +290,9 @@ class Plan:
                 check(self.lib.sb_plan_get_fft_variant(self.handle, int(n), axis, ctypes.byref(v)),
                       "sb_plan_get_fft_variant")
                 fft[f"{n},{axis}"] = v.value
-        return {"fft": fft, "contract_tile": self.contract_tile()[0]}
+        short = ctypes.c_int32()
+        check(self.lib.sb_plan_get_short_tiles(self.handle, ctypes.byref(short)), "sb_plan_get_short_tiles")
+        return {"fft": fft, "contract_tile": self.contract_tile()[0], "short_tiles": bool(short.value)}
 
     def set_choices(self, choices):
         for key, v in choices.get("fft", {}).items():
@@ -297,6 +300,8 @@ class Plan:
             self.set_fft_variant(n, axis, int(v))
         if "contract_tile" in choices:
             self.set_contract_tile(choices["contract_tile"])
+        if "short_tiles" in choices:
+            check(self.lib.sb_plan_set_short_tiles(self.handle, int(choices["short_tiles"])), "sb_plan_set_short_tiles")
 
     def profile(self, enable: bool):
         check(self.lib.sb_profile(self.handle, int(bool(enable))), "sb_profile")

@@ -138,18 +138,18 @@ static sb_status build_gather(sb_plan *p, std::vector<int> &gptr, std::vector<in
     return SB_OK;
 }
 
-// Cells per workgroup of the cell-parallel contraction on shape G: the contraction tile, halved for the
-// 4PCFs while a launch would have under 1024 workgroups (one Lambda of the compile-time kernels is a launch
+// Cells per workgroup of the cell-parallel contraction on shape G: the contraction tile, and where nobody
+// set one halved for the 4PCFs while a launch would have under 1024 workgroups (one Lambda of the compile-time kernels is a launch
 // and the run-time one is cut alike; one of the projected 4PCF covers every triple), down to two of the
 // 64-cell tiles that the kernels stage, or one where that leaves under 128.  A 32^3 grid is 32 workgroups
 // of 1024 cells for 256 compute units.
-static int contract_cells(const sb_plan *p, const ShapeGroup &G, int cpb) {
-    if (p->prob.npcf == 3 || !G.short_parts) return cpb;
+static int contract_cells(const sb_plan *p, const ShapeGroup &G, int cpb, bool shorter) {
+    if (p->prob.npcf == 3 || !G.short_parts || !shorter) return cpb;
     const int64_t per = p->prob.ndim == 3 ? 1 : (int64_t)p->p4_canon.size(), ng = G.ng;
     while ((cpb > 128 && (ng + cpb - 1) / cpb * per < 1024) || (cpb > 64 && (ng + cpb - 1) / cpb * per < 128)) cpb /= 2;
     return cpb;
 }
-static int contract_cells(const sb_plan *p, const ShapeGroup &G) { return contract_cells(p, G, p->contract_tile()); }
+int contract_cells(const sb_plan *p, const ShapeGroup &G) { return contract_cells(p, G, p->contract_tile(), p->short_tiles); }
 
 static void contraction_shape(const sb_plan *p, int *groups, int *nvals) {
     const int NB = p->prob.nbins;
@@ -196,7 +196,7 @@ static int64_t last_rows(const sb_plan *p, const ShapeGroup &G) {
 static int64_t part_blocks(const sb_plan *p, const ShapeGroup &G) {
     int tile_lo = 0, tile_hi = 0;
     p->contract_tile_range(&tile_lo, &tile_hi);
-    int64_t n = ceil_div(G.ng, contract_cells(p, G, tile_lo));
+    int64_t n = ceil_div(G.ng, contract_cells(p, G, tile_lo, true));
     if (G.rows > 0 && p->prob.npcf == 3) n = std::max(n, ceil_div(G.ng / G.n[p->prob.ndim - 1], last_rows(p, G)));
     return n;
 }

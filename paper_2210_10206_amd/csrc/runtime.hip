@@ -89,7 +89,8 @@ std::string tune_key(const sb_plan *p) {
 }
 
 // The cache is a JSON object with one entry per line:
-//   "<key>": {"fft": [[n, axis, variant], ...], "contract_tile": cells},
+//   "<key>": {"fft": [[n, axis, variant], ...], "contract_tile": cells, "short_tiles": 0 or 1},
+// (without "short_tiles": 0).
 // read_entries returns the (key, entry text) pairs of an existing file.
 std::vector<std::pair<std::string, std::string>> read_entries(const char *path) {
     std::vector<std::pair<std::string, std::string>> out;
@@ -115,8 +116,8 @@ std::vector<std::pair<std::string, std::string>> read_entries(const char *path) 
     return out;
 }
 
-// Integers of an entry's "fft" list and its "contract_tile" value; false when malformed.
-bool parse_entry(const std::string &e, std::vector<int> &fft, int *tile) {
+// Integers of an entry's "fft" list, its "contract_tile" and "short_tiles" values; false when malformed.
+bool parse_entry(const std::string &e, std::vector<int> &fft, int *tile, bool *short_tiles) {
     const size_t f0 = e.find("\"fft\""), t0 = e.find("\"contract_tile\"");
     if (f0 == std::string::npos || t0 == std::string::npos || t0 < f0) return false;
     fft.clear();
@@ -135,6 +136,8 @@ bool parse_entry(const std::string &e, std::vector<int> &fft, int *tile) {
     while (*tc && !(*tc == '-' || (*tc >= '0' && *tc <= '9'))) ++tc;
     if (!*tc) return false;
     *tile = (int)std::strtol(tc, nullptr, 10);
+    const size_t s0 = e.find("\"short_tiles\"", t0);
+    *short_tiles = s0 != std::string::npos && e.find('1', s0) != std::string::npos;
     return true;
 }
 
@@ -162,7 +165,8 @@ sb_status sb_autotune(sb_plan *p, void *stream, const char *cache_path) {
             if (kv.first != key) continue;
             std::vector<int> fft;
             int tile = 0;
-            if (!parse_entry(kv.second, fft, &tile)) return fail(SB_EINVAL, "malformed autotune cache entry");
+            bool short_tiles = false;
+            if (!parse_entry(kv.second, fft, &tile, &short_tiles)) return fail(SB_EINVAL, "malformed autotune cache entry");
             for (size_t i = 0; i < fft.size(); i += 3) {
                 if (!fft_supported(fft[i]) || fft[i + 1] < 0 || fft[i + 1] >= p->prob.ndim || fft[i + 2] < 0 ||
                     fft[i + 2] >= fft_num_variants(fft[i]))
@@ -174,6 +178,7 @@ sb_status sb_autotune(sb_plan *p, void *stream, const char *cache_path) {
             if (tile < lo || tile > hi || (tile & (tile - 1)) != 0)
                 return fail(SB_EINVAL, "autotune cache entry has a contraction tile out of range");
             p->contract_tile() = tile;
+            p->short_tiles = short_tiles;
             p->release_graph();
             return SB_OK;
         }
@@ -237,16 +242,26 @@ sb_status sb_autotune(sb_plan *p, void *stream, const char *cache_path) {
         double *zt = reinterpret_cast<double *>(p->scratch + p->off_zt);
         int lo = 0, hi = 0;
         p->contract_tile_range(&lo, &hi);
+        // 4PCFs: the tile of an untuned plan, shorter on short grids, then the others as they are
+        const ShapeGroup &G0 = p->groups[p->field_group[f0]];
+        std::vector<std::pair<int, bool>> tiles;
+        if (p->prob.npcf == 4) tiles.push_back({sb_plan::untuned_tile(4, p->prob.ndim), true});
+        for (int c = lo; c <= hi; c *= 2) tiles.push_back({c, false});
         float best = 1e30f;
-        int bestc = p->contract_tile();
+        std::pair<int, bool> bestc = {p->contract_tile(), p->short_tiles};
+        int untuned_cells = 0;
         sb_status st = SB_OK;
-        for (int c = lo; c <= hi && st == SB_OK; c *= 2) {
-            p->contract_tile() = c;
+        for (const auto &c : tiles) {
+            if (st != SB_OK) break;
+            p->contract_tile() = c.first;
+            p->short_tiles = c.second;
+            if (c.second) untuned_cells = contract_cells(p, G0);
+            else if (c.first == untuned_cells) continue;   // the same launch
             float tot = 0.f;
             for (int rep = 0; rep < 3 && st == SB_OK; ++rep) {
                 (void)hipEventRecord(a, s);
                 double *zo[1] = {zt};
-                st = contract(p, p->groups[p->field_group[f0]], reinterpret_cast<const float *>(p->scratch + p->off_w), zo, 1, s);
+                st = contract(p, G0, reinterpret_cast<const float *>(p->scratch + p->off_w), zo, 1, s);
                 (void)hipEventRecord(b, s);
                 (void)hipEventSynchronize(b);
                 float ms = 0.f;
@@ -255,7 +270,8 @@ sb_status sb_autotune(sb_plan *p, void *stream, const char *cache_path) {
             }
             if (tot < best) { best = tot; bestc = c; }
         }
-        p->contract_tile() = bestc;
+        p->contract_tile() = bestc.first;
+        p->short_tiles = bestc.second;
         if (st != SB_OK) {
             (void)hipEventDestroy(a);
             (void)hipEventDestroy(b);
@@ -275,7 +291,8 @@ sb_status sb_autotune(sb_plan *p, void *stream, const char *cache_path) {
                      ", " + std::to_string(kv.second) + "]";
             first = false;
         }
-        entry += "], \"contract_tile\": " + std::to_string(p->contract_tile()) + "}";
+        entry += "], \"contract_tile\": " + std::to_string(p->contract_tile()) + ", \"short_tiles\": " +
+                 (p->short_tiles ? "1}" : "0}");
         bool found = false;
         for (auto &kv : entries)
             if (kv.first == key) { kv.second = entry; found = true; }
@@ -322,7 +339,21 @@ sb_status sb_plan_set_contract_tile(sb_plan *p, int32_t cells) {
     if (cells < lo || cells > hi || (cells & (cells - 1)) != 0)
         return fail(SB_EINVAL, "contraction tile must be a power of two within the plan's range");
     p->contract_tile() = cells;
+    p->short_tiles = false;
     p->release_graph();
+    return SB_OK;
+}
+
+sb_status sb_plan_set_short_tiles(sb_plan *p, int32_t on) {
+    if (!p) return fail(SB_EINVAL, "null plan");
+    p->short_tiles = on != 0;
+    p->release_graph();
+    return SB_OK;
+}
+
+sb_status sb_plan_get_short_tiles(const sb_plan *p, int32_t *on) {
+    if (!p || !on) return fail(SB_EINVAL, "null argument");
+    *on = p->short_tiles ? 1 : 0;
     return SB_OK;
 }
 

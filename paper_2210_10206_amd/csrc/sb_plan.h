@@ -132,7 +132,10 @@ struct sb_plan {
     // launch shapes (autotuned): cells per workgroup of the cell-parallel contractions (unfused
     // 3PCF pair sums, full 4PCF, projected 4PCF); the scratch holds the partial sums of the
     // smallest candidate of contract_tile_range
-    int cpb_pair = 8192, cpb_quad = 1024, cpb_proj4 = 4096;
+    static constexpr int untuned_tile(int npcf, int ndim) { return npcf == 3 ? 8192 : ndim == 3 ? 1024 : 4096; }
+    int cpb_pair = untuned_tile(3, 3), cpb_quad = untuned_tile(4, 3), cpb_proj4 = untuned_tile(4, 2);
+    bool short_tiles = true;      // shapes with short_parts halve the tile (contract_cells); a tile that the caller
+                                  // or the autotuner sets is taken as it is
     int &contract_tile() { return prob.npcf == 3 ? cpb_pair : (prob.ndim == 3 ? cpb_quad : cpb_proj4); }
     int contract_tile() const { return prob.npcf == 3 ? cpb_pair : (prob.ndim == 3 ? cpb_quad : cpb_proj4); }
     void contract_tile_range(int *lo, int *hi) const {
@@ -231,6 +234,7 @@ sb_status density_weights(sb_plan *p, const sb::ShapeGroup &G, const void *delta
 sb_status coefficients(sb_plan *p, int f, int g0, int ngroups, hipStream_t s, bool last_axis = true,
                        const int *kmap = nullptr, int nf = 1);
 void layout_scratch(sb_plan *p);
+int contract_cells(const sb_plan *p, const ShapeGroup &G);   // cells per workgroup of the contraction on shape G
 void use_shape(sb_plan *p, const ShapeGroup &G);   // scratch offsets for fields of shape G (by_shape plans)
 sb_status contract(sb_plan *p, const ShapeGroup &G, const float *w, double *const *zout, int nf, hipStream_t s);
 // Half kernel store (plan.hip): whether a shape keeps only the planes c_0 = 0 .. r0, the planes
