@@ -57,7 +57,7 @@ __global__ void kgen_kernel(KgenArgs a) {
     }
     const double r = sqrt((double)s);
     const double ux = (double)c[0] / r, uy = (double)c[1] / r;
-    const double sc = a.scale;
+    const double sc = (double)a.scale;
     if (a.ndim == 2) {
         double pr = 1.0, pi = 0.0;  // ((x - i y)/r)^m
         for (int m = 0; m <= a.lmax; ++m) {

@@ -821,7 +821,7 @@ static sb_status gen_kernels(sb_plan *p, const ShapeGroup &G, int g0, int count,
     if (nd == 3)
         for (int l = 0; l <= p->prob.lmax; ++l)
             for (int m = 0; m <= l; ++m) a.norm[l * (l + 1) / 2 + m] = ylm_norm(l, m);
-    a.scale = 1.0 / (double)G.ng;
+    a.scale = (float)(1.0 / (double)G.ng);
     a.gfirst = g0;
     a.gcount = count;
     a.out = out;

@@ -21,7 +21,7 @@ struct KgenArgs {
     int lmax;                    // 3D lmax or 2D mmax
     int nlm;                     // kernels per bin: (lmax+1)(lmax+2)/2 in 3D, mmax+1 in 2D
     double norm[kMaxLM];         // N_lm = sqrt((2l+1)/(4 pi) (l-m)!/(l+m)!), index l(l+1)/2 + m
-    double scale;                // 1 / N_g
+    float scale;                 // 1 / N_g
     int npack;                   // 3D: packed m = 0 pairs written after the nlm groups
     int pack_l[2 * kMaxPack];    // (l_a, l_b) of each pair: K_{l_a 0} + i K_{l_b 0}
     int gfirst, gcount;          // kernel groups written: gfirst .. gfirst + gcount - 1 of the

@@ -15,8 +15,7 @@ import torch
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
 
-import oracle  # noqa: E402
-from fieldgen import lognormal_field, linear_edges  # noqa: E402
+from fieldgen import linear_edges  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -45,20 +44,3 @@ def test_long_axis_0(n):
     plan.close()
     print(f"{n} x {width}: gain - 1 = {num / den - 1:.3e} (bound 5e-8)", flush=True)
     assert abs(num / den - 1) < 5e-8
-
-
-def test_kernel_scale():
-    """The kernels carry 1 / N_g, which at 160^3 is 4.7e-8 from the nearest float: evaluated in float64 it
-    costs nothing, as a float it puts 9.5e-8 on every sum.  The transforms' constants put 2e-8 to 5e-8 on
-    them (radices 20, 4, 2; the three transforms of each axis, weighted by the spectrum): 7e-8 with their
-    scatter.  Rows l >= 1 only: the l = 0 kernel is one value, rounded once for all cells."""
-    from paper_2210_10206_amd import api
-    d = lognormal_field((160, 160, 160), seed=5, sigma=1.0)
-    edges = linear_edges(20.0, 3)
-    plan = api.Plan([d.shape], edges, 1)
-    z = plan.forward([torch.from_numpy(d).cuda()]).cpu().numpy()[0][1:]
-    plan.close()
-    ref = oracle.zeta3_full(d.astype(np.float64), edges, 1).real[1:]
-    bias = float((z * ref).sum() / (ref * ref).sum() - 1)
-    print(f"160^3, l = 1: bias {bias:.3e} (bound 7e-8)", flush=True)
-    assert abs(bias) < 7e-8
