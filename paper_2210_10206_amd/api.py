@@ -21,6 +21,17 @@ def _stream_ptr(stream=None):
     return ctypes.c_void_p(s.cuda_stream)
 
 
+def _used_on(stream, tensors):
+    """Tensors that a call on `stream` reads or writes: freed before it is done, their memory is not given
+    out again until it is (the library reads a float32 field where it lies, through the whole call)."""
+    if stream is None or stream.cuda_stream == torch.cuda.current_stream(tensors[0].device).cuda_stream:
+        return
+    if not isinstance(stream, torch.Stream):   # any object with a cuda_stream
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=tensors[0].device)
+    for t in tensors:
+        t.record_stream(stream)
+
+
 def _on_device(device):
     """The device made current; nothing to switch where it is (the usual case of one GPU a process)."""
     return contextlib.nullcontext() if torch.cuda.current_device() == device.index else torch.cuda.device(device)
@@ -208,6 +219,7 @@ class Plan:
         with _on_device(self.device):
             check(fn(self.handle, ptrs, ctypes.c_void_p(out.data_ptr()), _stream_ptr(stream)),
                   "sb_forward_graph" if graph else "sb_forward")
+        _used_on(stream, [*deltas, out])
         return out
 
     def forward(self, deltas, stream=None, graph=False):
@@ -235,6 +247,7 @@ class Plan:
             check(self.lib.sb_normalize(self.handle, self._ptrs(deltas), ctypes.c_void_p(raw.data_ptr()),
                                         ctypes.c_void_p(norm.data_ptr() if norm is not None else None),
                                         _stream_ptr(stream)), "sb_normalize")
+        _used_on(stream, [*deltas, raw] + ([] if norm is None else [norm]))
         if norm is not None:
             return norm.reshape((len(self.shapes),) + (self.nbins,) * (self.npcf - 1))
         return None
@@ -250,6 +263,7 @@ class Plan:
         with _on_device(self.device):
             check(self.lib.sb_backward(self.handle, self._ptrs(deltas), ctypes.c_void_p(gz.data_ptr()),
                                        self._ptrs(grads), _stream_ptr(stream)), "sb_backward")
+        _used_on(stream, [*deltas, gz, *grads])
         return grads
 
     def coeffs(self, k: int, shape=None):
