@@ -77,3 +77,13 @@ def test_every_row_reaches_float64(n, orders, adds):
     bound = (adds + 1) / 2 * 2.0 ** -24
     print(f"{shape} constant maps: worst {max(errs):.3e} (bound {bound:.2e})", flush=True)
     assert max(errs) < bound
+
+
+@pytest.mark.parametrize("n", [64, 96, 128, 160, 192, 256, 512, 1024])
+@pytest.mark.parametrize("nb", [3, 7])
+def test_blocks_of_eleven_rows(n, nb):
+    """41 array groups of 576 rows: some eleven rows a workgroup, fewer in the last one, which ends off every
+    eighth row (the two-stage lengths add to float64 there)."""
+    edges = linear_edges(2.9, nb)
+    d, z = _run((12, 48, n), edges, 8, "fp32")
+    check(z, oracle.zeta3_full(d, edges, 8).real, TOL32, print, f"12x48x{n} {nb} bins: ")
