@@ -91,31 +91,38 @@ __global__ void zero_c_kernel(float2 *x, int64_t n) {
 
 }  // namespace
 
-// Register-resident rows for the lengths with a radix list (those of the forward fused pass), the
-// LDS-staged tiles of launch_adj_last for the others.
+// Adjoint last pass by length: register-resident rows (length, radices) where the forward's last pass is
+// too, LDS-staged tiles (length, threads per pencil, radices) for the others.  None at 1024: a tile of
+// every bin of a row would not fit the LDS.
+#define SB_ADJ_ROWS(X)                                                                          \
+    X(64, 8, 8) X(96, 12, 4, 2) X(128, 16, 8) X(160, 20, 4, 2) X(192, 12, 4, 4) X(256, 16, 16)
+#define SB_ADJ_TILES(X)                                                                         \
+    X(8, 1, 8) X(12, 1, 4, 3) X(16, 4, 4, 4) X(24, 2, 4, 2, 3) X(32, 4, 4, 8) X(48, 4, 4, 4, 3) \
+    X(512, 32, 8, 8, 8)
+
 bool adj_rows_available(int n) {
-    return n == 64 || n == 96 || n == 128 || n == 160 || n == 192 || n == 256;
+    switch (n) {
+#define SB_X(N, ...) case N:
+        SB_ADJ_ROWS(SB_X)
+#undef SB_X
+        return true;
+        default: return false;
+    }
 }
 
 hipError_t launch_adj_rows(const AdjRowsArgs &a, hipStream_t s) {
     switch (a.n) {
-        case 64: return adjlast::launch_rs<64, 8, 8>(a, s);
-        case 96: return adjlast::launch_rs<96, 12, 4, 2>(a, s);
-        case 128: return adjlast::launch_rs<128, 16, 8>(a, s);
-        case 160: return adjlast::launch_rs<160, 20, 4, 2>(a, s);
-        case 192: return adjlast::launch_rs<192, 12, 4, 4>(a, s);
-        case 256: return adjlast::launch_rs<256, 16, 16>(a, s);
+#define SB_X(N, ...) case N: return adjlast::launch_rs<N, __VA_ARGS__>(a, s);
+        SB_ADJ_ROWS(SB_X)
+#undef SB_X
         default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t launch_adj_last(const AdjLastArgs &a, hipStream_t s) {
-    switch (a.n) {   // (none at 1024: a tile of every bin of a row would not fit the LDS)
-#define SB_X(N, TPP, ...)                                                             \
-    case N:                                                                           \
-        if constexpr (N <= 512) return adjlast::launch_n<N, TPP, __VA_ARGS__>(a, s); \
-        else return hipErrorInvalidValue;
-        SB_LAST_CONFIGS(SB_X)
+    switch (a.n) {
+#define SB_X(N, ...) case N: return adjlast::launch_n<N, __VA_ARGS__>(a, s);
+        SB_ADJ_TILES(SB_X)
 #undef SB_X
         default: return hipErrorInvalidValue;
     }
@@ -130,7 +137,7 @@ sb_status backward(sb_plan *p, const void *const *delta, const double *grad_zeta
     if (p->regen) return fail(SB_EUNSUPPORTED, "the adjoint reads cached kernel spectra; this plan regenerates them");
     if (p->adj_fused)
         for (const auto &G : p->groups)
-            if (fused_last_rows((int)G.n[2], p->prob.nbins) <= 0 || G.n[2] > 512)
+            if (G.n[2] > 512)
                 return fail(SB_EUNSUPPORTED, "no fused adjoint last pass for a last axis of " + std::to_string(G.n[2]) +
                                                  " (use SB_FLAG_UNFUSED)");
     const int NB = p->prob.nbins;

@@ -8,6 +8,6 @@ namespace sb {
 template <> hipError_t launch_last_for<256>(const LastArgs &a, hipStream_t s) {
     return fftlast::launch_last_reg<16, 16>(a, s);
 }
-template <> int last_rows<256>(int nb) { return nb <= 16 ? 1 : 0; }
+template <> int last_rows<256>(int) { return 1; }
 
 }  // namespace sb

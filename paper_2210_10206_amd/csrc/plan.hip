@@ -197,7 +197,7 @@ static int64_t part_blocks(const sb_plan *p, const ShapeGroup &G) {
     int tile_lo = 0, tile_hi = 0;
     p->contract_tile_range(&tile_lo, &tile_hi);
     int64_t n = ceil_div(G.ng, contract_cells(p, G, tile_lo, true));
-    if (G.rows > 0 && p->prob.npcf == 3) n = std::max(n, ceil_div(G.ng / G.n[p->prob.ndim - 1], last_rows(p, G)));
+    if (p->prob.npcf == 3) n = std::max(n, ceil_div(G.ng / G.n[p->prob.ndim - 1], last_rows(p, G)));
     return n;
 }
 
@@ -306,7 +306,7 @@ void layout_scratch(sb_plan *p) {
             G.short_parts = false;
             G.short_parts = with <= kNoAllocScratchBytes || place_scratch(p, &G) > kNoAllocScratchBytes;
         }
-        if (G.rows > 0) G.rows_per_block = last_rows(p, G);
+        G.rows_per_block = last_rows(p, G);
     }
     p->chunk_groups = chunk_of(p, p->max_ng);
     // fields per batch (the region of each per-field buffer is fbatch fields long)
@@ -468,8 +468,6 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
         if (prob->npcf == 3) {
             if (prob->flags & SB_FLAG_UNFUSED) pack = false;
             if (p->regen) pack = false;
-            for (const auto &G : p->groups)
-                if (fused_last_rows((int)G.n[prob->ndim - 1], NB) <= 0) pack = false;
         }
         if (pack) {
             p->npack = (prob->lmax + 1) / 2;
@@ -731,7 +729,7 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
         if (!p->regen) pers += align256((size_t)p->kernel_groups() * NB * G.np * G.plane * sizeof(float2));
         // fused last pass: rows per tile fixed by the kernel's compile-time tile shape
         const int nl = (int)G.n[prob->ndim - 1];
-        G.rows = NB <= kMaxBins ? fused_last_rows(nl, NB) : 0;
+        G.rows = fused_last_rows(nl, NB);
     }
     p->persist_need = pers;
     // split-BF16 exists for the contractions on the matrix cores only
@@ -740,7 +738,7 @@ sb_status plan_create(const sb_problem *prob, int32_t batch, const int64_t *shap
         if (prob->npcf == 3) {
             ok = p->fused;
             // (no split form of the 1024-point rows of more than 12 bins)
-            for (const auto &G : p->groups) ok &= G.rows > 0 && (NB <= 12 || G.n[prob->ndim - 1] < 1024);
+            for (const auto &G : p->groups) ok &= NB <= 12 || G.n[prob->ndim - 1] < 1024;
         } else if (prob->ndim == 3) {
             ok = p->quad_mfma;
         } else {

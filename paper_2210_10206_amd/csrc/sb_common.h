@@ -130,6 +130,6 @@ struct LastArgs {
     int64_t in_fs, w_fs, part_fs;   // strides between the fields' in, w and partial
 };
 hipError_t launch_last_contract(const LastArgs &a, hipStream_t s);
-int fused_last_rows(int n, int nb);   // rows per tile the fused last pass uses (0: no kernel)
+int fused_last_rows(int n, int nb);   // rows per tile the fused last pass uses (every supported length, up to 16 bins)
 
 }  // namespace sb

@@ -25,7 +25,7 @@ struct ShapeGroup {
     int64_t plane = 0;            // cells per axis-0 plane
     int np = 0, r0 = 0;           // stored axis-0 planes of the kernels, support radius along axis 0
     bool half = false;            // only the planes c_0 = 0 .. r0 stored (the others by parity)
-    int rows = 0;                 // rows per tile of the fused last pass (0: not available)
+    int rows = 0;                 // rows per tile of the fused last pass
     bool short_parts = false;     // shorter contraction tiles and last-pass blocks where the grid is short (layout_scratch)
     int64_t rows_per_block = 0;   // of the fused last pass
     std::vector<int> fields;
