@@ -171,6 +171,8 @@ class Plan:
         tab = ctypes.POINTER(ctypes.c_int32)()
         check(self.lib.sb_zeta_index(self.handle, ctypes.byref(rows), ctypes.byref(cols), ctypes.byref(tab)),
               "sb_zeta_index")
+        if rows.value == 0:   # odd Lambda to l = 0: none, and no table either
+            return np.zeros((0, cols.value), dtype=np.int32)
         return np.ctypeslib.as_array(tab, shape=(rows.value, cols.value)).copy()
 
     def zeta_index(self):

@@ -155,6 +155,28 @@ def test_split_bf16_only_where_a_split_form_exists(kw, expect):
         lib.sb_plan_destroy(h)
 
 
+def _plan_object(shape, **kw):
+    """A Plan around a handle without a device buffer (what its constructor holds before it binds any)."""
+    from paper_2210_10206_amd import _lib, api
+    import numpy as np
+    plan = api.Plan.__new__(api.Plan)
+    plan.lib, prob = _lib.load(), _problem(**kw)
+    plan.ndim, plan.npcf, plan.nbins, plan.handle = kw.get("ndim", 3), kw["npcf"], prob[0].nbins, ctypes.c_void_p()
+    sh = np.array(shape, dtype=np.int64)
+    assert plan.lib.sb_plan_create(ctypes.byref(prob[0]), 1, sh.ctypes.data_as(ctypes.POINTER(ctypes.c_int64)),
+                                   ctypes.byref(plan.handle)) == 0
+    plan._index = plan._read_index()
+    return plan
+
+
+def test_index_of_a_plan_without_rows():
+    """Odd Lambda to l = 0: there is none, so the table is empty."""
+    plan = _plan_object((16, 16, 16), npcf=4, lmax=0, flags=8)
+    assert plan.zeta_index().shape == (0, 3) and plan.zeta_shape() == (0, 2, 2, 2)
+    plan.lib.sb_plan_destroy(plan.handle)
+    plan.handle = None
+
+
 def test_autotune_and_normalize_reject_an_unbound_plan():
     from paper_2210_10206_amd import _lib
     lib = _lib.load()
