@@ -176,7 +176,8 @@ class Plan:
         return np.ctypeslib.as_array(tab, shape=(rows.value, cols.value)).copy()
 
     def zeta_index(self):
-        return self._index.copy()   # fixed when the plan is created
+        # fixed when the plan is created; a closed plan has none (SB_EINVAL)
+        return self._index.copy() if self.handle else self._read_index()
 
     def bin_counts(self, field: int = 0):
         out = np.zeros(self.nbins, dtype=np.int64)
@@ -192,7 +193,7 @@ class Plan:
         return bits.value
 
     def zeta_shape(self):
-        rows = self._index.shape[0]
+        rows = (self._index if self.handle else self._read_index()).shape[0]
         nb = self.nbins
         tail = (nb, nb) if self.npcf == 3 else (nb, nb, nb)
         return (rows,) + tail

@@ -177,6 +177,15 @@ def test_index_of_a_plan_without_rows():
     plan.handle = None
 
 
+def test_index_of_a_closed_plan_is_refused():
+    plan = _plan_object((16, 16, 16), npcf=3)
+    plan.lib.sb_plan_destroy(plan.handle)
+    plan.handle = None   # as close() leaves it
+    for ask in (plan.zeta_index, plan.zeta_shape):
+        with pytest.raises(RuntimeError):
+            ask()
+
+
 def test_autotune_and_normalize_reject_an_unbound_plan():
     from paper_2210_10206_amd import _lib
     lib = _lib.load()
