@@ -649,12 +649,16 @@ template <int N> constexpr int row_region(bool split) {
     return pencil_region(N + ((N - 1) >> row_skew(N)), split ? (row_plane(N) + N + 1) / 2 : N);
 }
 
-// Waves per SIMD last_rs_kernel is compiled for: as many as its LDS allows without spilling more than
-// a few registers (16 bins with the complex sums hold 80 accumulators).
-constexpr int rs_waves(int n, int nbt, bool cplx) {
+// Waves per SIMD that last_rs_kernel is compiled for: the most for which the compiler spills nothing, which
+// R0 points a thread and NBT bins decide (128 registers a wave at four).  The real and packed sums of 16
+// bins at 512 points take four all the same, with 18 registers spilled: at three, one of their eight-wave
+// workgroups fits a compute unit instead of two (64 x 64 x 512, l <= 4: 1.25 ms against 1.10).  12 bins there,
+// at three / four waves, 0.96 / 0.78 ms.
+constexpr int rs_waves(int n, int r0, int nbt, bool cplx) {
     if (n >= 1024) return 1;
-    if (cplx) return nbt > 12 ? 2 : n == 96 || (n == 512 && nbt <= 8) ? 4 : 3;
-    return n == 160 || (n == 512 && nbt == 12) ? 3 : n == 96 && nbt == 8 ? 5 : 4;
+    if (nbt <= 8) return cplx ? (r0 > 16 ? 3 : 4) : (r0 <= 12 ? 5 : 4);
+    if (nbt <= 12) return cplx && r0 > 12 ? 3 : 4;
+    return cplx ? (r0 <= 12 ? 3 : 2) : (r0 > 16 ? 3 : 4);
 }
 
 // Register-resident form for the three-stage radix lists R0, ... (the last radix divides R0): a tile
@@ -780,7 +784,7 @@ __device__ __forceinline__ void last_rs_body(const LastArgs &a, float2 *lds, flo
 }
 
 template <int N, int NBT, bool CPLX, int PREC, int R0, int... REST>
-__global__ __launch_bounds__(NBT * (N / R0), rs_waves(N, NBT, CPLX)) void last_rs_kernel(LastArgs a) {
+__global__ __launch_bounds__(NBT * (N / R0), rs_waves(N, R0, NBT, CPLX)) void last_rs_kernel(LastArgs a) {
     extern __shared__ float2 lds[];        // one region per bin (dead pencils have none)
     __shared__ float2 tws[wave_twiddles<R0, REST...>()];
     __shared__ float wsm[N];
