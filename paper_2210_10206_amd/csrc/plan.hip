@@ -173,8 +173,8 @@ static bool has_adjoint(const sb_plan *p) { return p->prob.ndim == 3 && p->prob.
 // Rows per workgroup of the fused last pass: at most about 1024 workgroups a group, of 16 rows or
 // more; fewer rows where the groups together would not make 2048 workgroups (us, 16 rows / fewer: maps
 // of 128^2 and 192 x 96, 8 and 6 bins, 81 / 38 and 77 / 42; 96 x 32 x 64, 5 bins 91 / 82).  Plans with an
-// adjoint keep the partials of the shorter blocks within those of 16 rows and one group's v arrays,
-// which the forward does not use (place_scratch).
+// adjoint keep the partials of the shorter blocks within those of 16 rows or within one group's v
+// arrays, which the forward does not use (place_scratch).
 static int64_t last_rows(const sb_plan *p, const ShapeGroup &G) {
     const int64_t nrows = G.ng / G.n[p->prob.ndim - 1];
     const int nag = p->npack > 0 ? p->nag : p->nlm;
@@ -185,7 +185,7 @@ static int64_t last_rows(const sb_plan *p, const ShapeGroup &G) {
     if (has_adjoint(p)) {
         int groups = 0, nvals = 0;
         contraction_shape(p, &groups, &nvals);
-        const int64_t blocks = ceil_div(nrows, rpb16) + p->prob.nbins * G.ng / ((int64_t)groups * nvals);
+        const int64_t blocks = std::max(ceil_div(nrows, rpb16), p->prob.nbins * G.ng / ((int64_t)groups * nvals));
         least = std::max(least, ceil_div(nrows, blocks));
     }
     return std::min(rpb16, tiled(std::max(most, least)));
@@ -224,30 +224,16 @@ static size_t place_scratch(sb_plan *p, const ShapeGroup *only = nullptr) {
         nblocks = std::max(nblocks, part_blocks(p, G));
         kc = std::max<int64_t>(kc, (int64_t)G.np * G.plane);
     }
-    const size_t part = align256(std::max<size_t>(FB * groups * nvals * nblocks, kNormParts) * sizeof(double));
+    const auto part_bytes = [&](int64_t blocks) {
+        return align256(std::max<size_t>(FB * groups * nvals * blocks, kNormParts) * sizeof(double));
+    };
     size_t sc = 0;
     p->off_w = sc; sc += align256(FB * max_ng * sizeof(float));
     p->off_dhat = sc; sc += align256(FB * max_ng * sizeof(float2));
-    p->off_part = sc;
-    if (has_adjoint(p)) {
-        // the adjoint's v arrays directly before the coefficient arrays: its fused pass writes the v
-        // of each group into the slot before that group's coefficients.  The forward's partials may
-        // reach into them.
-        int64_t long_blocks = 0;
-        for (auto &G : p->groups) {
-            if (only && &G != only) continue;
-            const bool sp = G.short_parts;
-            G.short_parts = false;
-            long_blocks = std::max(long_blocks, part_blocks(p, G));
-            G.short_parts = sp;
-        }
-        const size_t vtmp = align256((size_t)NB * max_ng * sizeof(float2));
-        const size_t long_part = align256(std::max<size_t>(FB * groups * nvals * long_blocks, kNormParts) * sizeof(double));
-        sc += std::max(part, long_part + vtmp);
-        p->off_vtmp = sc - vtmp;
-    } else {
-        sc += part;
-    }
+    // the adjoint's v arrays directly before the coefficient arrays: its fused pass writes the v
+    // of each group into the slot before that group's coefficients
+    if (has_adjoint(p)) { p->off_vtmp = sc; sc += align256((size_t)NB * max_ng * sizeof(float2)); }
+    const size_t vtmp = has_adjoint(p) ? sc - p->off_vtmp : 0;
     p->off_coef = sc;
     if (p->keep) {
         // one region per field: the forward's array groups (packed m = 0 pairs first) of all bins
@@ -269,6 +255,25 @@ static size_t place_scratch(sb_plan *p, const ShapeGroup *only = nullptr) {
     if (p->regen) {   // the stored axis-0 planes of one chunk's kernels
         p->off_kc = sc; sc += align256((size_t)p->chunk_groups * NB * kc * sizeof(float2));
     }
+    // block partials; those of short blocks where the v arrays hold them: in their place, beside the
+    // room of long blocks (which the sizes of such plans have always had)
+    p->off_part = sc;
+    size_t part = part_bytes(nblocks);
+    if (part <= vtmp) {
+        int64_t long_blocks = 0;
+        for (auto &G : p->groups) {
+            if (only && &G != only) continue;
+            const bool sp = G.short_parts;
+            G.short_parts = false;
+            long_blocks = std::max(long_blocks, part_blocks(p, G));
+            G.short_parts = sp;
+        }
+        if (long_blocks < nblocks) {
+            p->off_part = p->off_vtmp;
+            part = part_bytes(long_blocks);
+        }
+    }
+    sc += part;
     p->off_tot = sc; sc += align256(FB * groups * nvals * sizeof(double));
     p->off_grad = sc; sc += align256(max_ng * sizeof(float2));
     p->off_flag = sc; sc += 256;
