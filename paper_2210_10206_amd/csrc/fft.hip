@@ -288,7 +288,7 @@ inline int support_rows(const Axis0Args &a, int r1, int r2) {
 // VGPRs), so that one's loads and stores run during the other's transforms.  With 16 x 8 x 4 stages
 // and two exchange buffers (143 KB, one workgroup a CU) the 512-point pass took 39.4 ms for 13 groups of
 // 6 bins at 512^3, now 27.3 (4.0 TB/s); 8 x 8 x 4 x 4 at 1024 points 962 us for the maps above
-// share_groups, now 447.
+// share_groups, now 467 (447 before the constants became pairs, see cmul_pair).
 // A compact kernel is nonzero on rows r <= KR and r >= R1 - KR of each thread at most (KR from
 // the support radius, see support_rows; KR >= R1 / 2 for a dense axis): the other rows are
 // compile-time zeros, so they are neither loaded nor held, and the first forward stage folds

@@ -710,8 +710,8 @@ __device__ __forceinline__ void last_rs_body(const LastArgs &a, float2 *lds, flo
             wdst[e] = c < N ? a.w[row * N + c] : 0.f;
         }
     };
-    // PF: the next row's loads are in flight during this row.  Its registers cost a wave per SIMD (512^3,
-    // 6 bins: 26.6 ms against 21.6; 192^3, 8 bins 1.40 against 1.27), so without it the next row loads
+    // PF: the next row's loads are in flight during this row.  Its registers cost a wave per SIMD (with sums
+    // flushed every eighth row 512^3, 6 bins: 26.6 ms against 21.6; 192^3, 8 bins 1.40 against 1.27), so without it the next row loads
     // into the row's own registers once they are stored to LDS, in flight during the pair sums; the
     // complex sums hold too many registers for that wave anyway.
     constexpr bool PF = MODE == PS_COMPLEX && (N < 512 || (N == 512 && NBT > 8));

@@ -26,7 +26,7 @@
 // instead of 7 at 10 bins) and the latter two products instead of three.  16 of the 36 triples at
 // m <= 10 are of these kinds: a quarter of the MFMAs.
 //
-// Measured on a 512^2 field, 10 bins, m <= 10: 1.07 ms (1.42 with seven-wave workgroups, every pair of
+// Measured on a 512^2 field, 10 bins, m <= 10: 1.10 ms (1.42 with seven-wave workgroups, every pair of
 // every triple, and the next tile's loads each waited for to take the sign of a negative order).  The
 // MFMAs alone take 0.55 ms; the rest is the chain LDS read -> complex product -> MFMA of a step.
 //

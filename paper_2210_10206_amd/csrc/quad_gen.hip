@@ -16,9 +16,10 @@
 // table comes kGRun terms to a scalar load, a run ahead (read one by one, each term waited for its
 // scalar load: 2.8 ms against 2.3).
 // Measured on 64^3 cells, 10 bins, lmax 5, odd parity (14 canonical Lambda): 2.3 ms, where the vector
-// kernel (quad_kernel), with its two LDS reads for every product, takes 13.8.  What bounds it is the
-// issue of the coupling (at 3.5 waves a SIMD the vector ALUs are busy 41 % of the cycles, the LDS 37 %,
-// the matrix cores 24 %), 30 % of it spent on the bins that pad 10 to 12.
+// kernel (quad_kernel), with its two LDS reads for every product, takes 13.8.  No unit is
+// full (at 3.5 waves a SIMD the vector ALUs are busy 42 % of the cycles, at two an instruction, the LDS 37 %,
+// the matrix cores 23 %): staging 16 cells at a time leaves nothing to overlap with, and 30 % of the
+// coupling is spent on the bins that pad 10 to 12.
 //
 // LDS: one row of ncol x 4 T float2 per cell padded to an odd length; lane group g reads cells 4 apart,
 // so the 16 values of a read (4 cells, 4 bins) and the 16 cells of a store fall on distinct banks.
