@@ -269,6 +269,7 @@ sb_status sb_autotune(sb_plan *p, void *stream, const char *cache_path) {
                 if (rep > 0) tot += ms;
             }
             if (tot < best) { best = tot; bestc = c; }
+            if (tot > 2.f * best) break;   // a grid too short for this tile is so for the longer ones
         }
         p->contract_tile() = bestc.first;
         p->short_tiles = bestc.second;
